@@ -14,31 +14,19 @@
 //   A[m][k]: m = l % 16, k = 8 (l / 16) + j, j = 0..7  (8 bf16 per lane)
 //   B[k][n]: n = l % 16, k = 8 (l / 16) + j
 //   D[m][n]: n = l % 16, m = 4 (l / 16) + i, i = 0..3  (4 floats per lane)
-// The backward data pass is the same convolution with flipped, transposed
-// weights; weight gradients put pixels on the reduction axis.
+// The backward pass is in cnn_bwd.hip.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
 
 #include "cnn.hpp"
+#include "cnn_device.hpp"
 
 namespace sl {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-
 constexpr int TH = 8, TW = 32;                 // output tile
 constexpr int HH = TH + 2, HW2 = TW + 2;       // input halo tile
-constexpr int CH = 32;
-
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);             // round to nearest even
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // ---------------------------------------------------------------------------
 // x0 planes from the coefficients
@@ -74,8 +62,8 @@ template <int NB, int MODE>
 __global__ void __launch_bounds__(256)
 k_conv3x3(const uint16_t *__restrict__ in, const uint16_t *__restrict__ Wp,
           const float *__restrict__ bias, int bias_stride, CnnPlanes pl, int H, int W,
-          uint16_t *__restrict__ out, const uint16_t *__restrict__ mask,
-          const float *__restrict__ coef, float *__restrict__ coef_out, float *__restrict__ gain) {
+          uint16_t *__restrict__ out, const float *__restrict__ coef, float *__restrict__ coef_out,
+          float *__restrict__ gain) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[HH * HW2 * kConvCP];
   const int p = blockIdx.z;
   const int ty0 = blockIdx.y * TH, tx0 = blockIdx.x * TW;
@@ -140,16 +128,6 @@ k_conv3x3(const uint16_t *__restrict__ in, const uint16_t *__restrict__ Wp,
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (__bf16)fmaxf(acc[nb][e], 0.f);
-        *(bf16x4 *)(out + opix * CH + 16 * nb + 4 * g) = o;
-      }
-    } else if constexpr (MODE == CONV_MASKED) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const uint2 mk = *(const uint2 *)(mask + opix * CH + 16 * nb + 4 * g);
-        const uint16_t *mh = (const uint16_t *)&mk;
-        bf16x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (__bf16)(mh[e] != 0 ? acc[nb][e] : 0.f);
         *(bf16x4 *)(out + opix * CH + 16 * nb + 4 * g) = o;
       }
     } else {   // CONV_GAIN: channel 0 sits in lane group 0, element 0
@@ -500,166 +478,20 @@ k_cnn_fused(const float *__restrict__ coef, CnnPlanes pl, int H, int W, int ntil
   }
 }
 
-// ---------------------------------------------------------------------------
-// backward helpers
-// ---------------------------------------------------------------------------
-// dz = dL/dc' * c * g (1 - g) on channel 0 of a zero-padded bf16 tensor;
-// dbias3 partial sums are reduced later from dzf (float copy).
-__global__ void k_cnn_dz(const float *__restrict__ dcoef, const float *__restrict__ coef,
-                         const float *__restrict__ gain, CnnPlanes pl, int HWn,
-                         uint16_t *__restrict__ dz, float *__restrict__ dzf) {
-  const int p = blockIdx.y;
-  const int px = blockIdx.x * blockDim.x + threadIdx.x;
-  if (px >= HWn) return;
-  int b, i, j;
-  plane_info(pl, p, b, i, j);
-  const size_t co = ((size_t)b * pl.R + i) * HWn + px;
-  const size_t o = (size_t)p * HWn + px;
-  const float g = gain[co];
-  const float v = dcoef[co] * coef[co] * g * (1.f - g);
-  if (dzf) dzf[o] = v;
-  uint4 *dst = (uint4 *)(dz + o * CH);
-  dst[0] = make_uint4((uint32_t)f2bf(v), 0u, 0u, 0u);
-  dst[1] = make_uint4(0u, 0u, 0u, 0u);
-  dst[2] = make_uint4(0u, 0u, 0u, 0u);
-  dst[3] = make_uint4(0u, 0u, 0u, 0u);
-}
-
-// Weight gradients dW[t][ci][co] = sum_p x[p + t - 1][ci] dy[p][co] and
-// db[co] = sum_p dy[p][co] over the tiles of planes of one scale.  Each block
-// walks tiles with a grid stride and writes one partial [9*32*32 + 32].
-// Pixels are the reduction axis: A[m = ci][k = pixel], B[k = pixel][n = co].
-// Weight gradients of one layer over a range of planes: for every tap t,
-// dW[t][ci][co] = sum_p x[p + offset(t)][ci] dy[p][co] (implicit GEMM with the
-// pixels on the reduction axis; operands transposed to channel-major tiles in
-// LDS) and dbias[co] = sum_p dy[p][co].  MB x NB selects the 16 x 16 blocks of
-// (ci, co) that can be nonzero: layer 1 has 2 input channels (MB = 1), layer 3
-// one output channel (NB = 1).  Only the channel quarters that those blocks
-// read are loaded (XQ, DQ quarters of 8 channels).  A wave takes one tap row
-// dy and one (mb, nb) block and computes its three taps dx = 0, 1, 2 together:
-// the x rows are padded to 16-byte alignment, each lane reads 16 pixels with
-// two aligned 16-byte loads and forms the three shifted operands in registers,
-// and the dy operand is shared.  Each block writes its partial sums;
-// k_reduce_partials adds them in a fixed order.
-constexpr int kWgRow = 48;   // padded halo row (>= TW + 2 + 14, multiple of 8)
-template <int MB, int NB>
+// Sum of n block partials in a fixed order: one block, a strided sum per
+// thread, then a tree (one thread walking 1024 partials took 65 us).
 __global__ void __launch_bounds__(256)
-k_conv_wgrad(const uint16_t *__restrict__ x, const uint16_t *__restrict__ dy, int H, int W,
-             int plane0, int nplanes, float *__restrict__ partial) {
-  constexpr int XQ = 2 * MB, DQ = 2 * NB;            // channel quarters of x and dy
-  constexpr int NTRIP = 3 * MB * NB;                  // (tap row, mb, nb) units
-  constexpr int TPW = (NTRIP + 3) / 4;                // per wave (4 waves)
-  __shared__ __attribute__((aligned(16))) uint16_t xs[8 * XQ][HH * kWgRow];
-  __shared__ __attribute__((aligned(16))) uint16_t ds[8 * DQ][TH * TW];
-  __shared__ float bsum[256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
-  const size_t HWn = (size_t)H * W;
-  f32x4 acc[TPW][3];
-#pragma unroll
-  for (int s = 0; s < TPW; ++s)
-#pragma unroll
-    for (int d = 0; d < 3; ++d) acc[s][d] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float dbias = 0.f;     // channel threadIdx.x % 32, pixels threadIdx.x / 32 + 8 i
-  const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + TH - 1) / TH;
-  const int ntiles = nplanes * tiles_x * tiles_y;
-  for (int q = blockIdx.x; q < ntiles; q += gridDim.x) {
-    const int p = plane0 + q / (tiles_x * tiles_y);
-    const int rem = q % (tiles_x * tiles_y);
-    const int ty0 = (rem / tiles_x) * TH, tx0 = (rem % tiles_x) * TW;
-    __syncthreads();
-    // halo tile of x and output tile of dy, 8 channels (16 bytes) per load,
-    // transposed to [channel][pixel]
-    for (int k = threadIdx.x; k < HH * HW2 * XQ; k += 256) {
-      const int pix = k / XQ, qu = k % XQ;
-      const int r = pix / HW2, c = pix % HW2;
-      const int yy = ty0 + r - 1, xx = tx0 + c - 1;
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-        v = ((const uint4 *)(x + ((size_t)p * HWn + (size_t)yy * W + xx) * CH))[qu];
-      const uint16_t *h = (const uint16_t *)&v;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) xs[8 * qu + e][r * kWgRow + c] = h[e];
-    }
-    for (int k = threadIdx.x; k < TH * TW * DQ; k += 256) {
-      const int pix = k / DQ, qu = k % DQ;
-      const int yy = ty0 + pix / TW, xx = tx0 + pix % TW;
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (yy < H && xx < W)
-        v = ((const uint4 *)(dy + ((size_t)p * HWn + (size_t)yy * W + xx) * CH))[qu];
-      const uint16_t *h = (const uint16_t *)&v;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) ds[8 * qu + e][pix] = h[e];
-    }
-    __syncthreads();
-    if ((threadIdx.x & 31) < 8 * DQ) {
-      const int c = threadIdx.x & 31;
-#pragma unroll
-      for (int k = threadIdx.x >> 5; k < TH * TW; k += 8) dbias += bf2f(ds[c][k]);
-    }
-#pragma unroll
-    for (int s = 0; s < TPW; ++s) {
-      const int trip = wave + 4 * s;
-      if (trip < NTRIP) {
-        const int dyy = trip / (MB * NB), mb = (trip / NB) % MB, nb = trip % NB;
-        const int ci = 16 * mb + (lane & 15), co = 16 * nb + (lane & 15);
-        for (int r = 0; r < TH; ++r) {
-          const uint4 u0 = *(const uint4 *)&xs[ci][(r + dyy) * kWgRow + 8 * g];
-          const uint4 u1 = *(const uint4 *)&xs[ci][(r + dyy) * kWgRow + 8 * g + 8];
-          const bf16x8 bb = *(const bf16x8 *)&ds[co][r * TW + 8 * g];
-          // pixels 8 g + dx .. 8 g + dx + 7 of the halo row for dx = 0, 1, 2
-          const uint4 a1 = make_uint4(__builtin_amdgcn_alignbit(u0.y, u0.x, 16),
-                                      __builtin_amdgcn_alignbit(u0.z, u0.y, 16),
-                                      __builtin_amdgcn_alignbit(u0.w, u0.z, 16),
-                                      __builtin_amdgcn_alignbit(u1.x, u0.w, 16));
-          const uint4 a2 = make_uint4(u0.y, u0.z, u0.w, u1.x);
-          acc[s][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8 *)&u0, bb, acc[s][0], 0, 0, 0);
-          acc[s][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8 *)&a1, bb, acc[s][1], 0, 0, 0);
-          acc[s][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8 *)&a2, bb, acc[s][2], 0, 0, 0);
-        }
-      }
-    }
-  }
-  // D[m = ci][n = co]: lane holds ci = 16 mb + 4 (lane / 16) + e, co = 16 nb + lane % 16;
-  // blocks outside MB x NB are zero
-  float *dst = partial + (size_t)blockIdx.x * (9 * CH * CH + CH);
-  for (int k = threadIdx.x; k < 9 * CH * CH; k += 256) {
-    const int ci = (k / CH) % CH, co = k % CH;
-    if (ci >= 16 * MB || co >= 16 * NB) dst[k] = 0.f;
-  }
-#pragma unroll
-  for (int s = 0; s < TPW; ++s) {
-    const int trip = wave + 4 * s;
-    if (trip < NTRIP) {
-      const int dyy = trip / (MB * NB), mb = (trip / NB) % MB, nb = trip % NB;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int t = 3 * dyy + d;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ci = 16 * mb + 4 * g + e, co = 16 * nb + (lane & 15);
-          dst[(t * CH + ci) * CH + co] = acc[s][d][e];
-        }
-      }
-    }
-  }
-  bsum[threadIdx.x] = dbias;
-  __syncthreads();
-  if (threadIdx.x < CH) {
-    float sum = 0.f;
-#pragma unroll
-    for (int g2 = 0; g2 < 8; ++g2) sum += bsum[g2 * 32 + threadIdx.x];
-    dst[9 * CH * CH + threadIdx.x] = sum;
-  }
-}
-
-// Sum block partials in a fixed order (deterministic).
-__global__ void k_reduce_partials(const float *__restrict__ partial, int nparts, int len,
-                                  float *__restrict__ outv) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= len) return;
+k_sum_partials(const float *__restrict__ partial, int n, float *__restrict__ outv) {
+  __shared__ float red[256];
   float s = 0.f;
-  for (int q = 0; q < nparts; ++q) s += partial[(size_t)q * len + k];
-  outv[k] = s;
+  for (int q = threadIdx.x; q < n; q += 256) s += partial[q];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) outv[0] = red[0];
 }
 
 // Pack the conv B operands of every scale from the FP32 parameter blobs,
@@ -732,18 +564,15 @@ hipError_t cnn_x0(const float *coef, const CnnPlanes &pl, int P, int H, int W, u
 
 hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float *bias,
                     int bias_stride, const CnnPlanes &pl, int P, int H, int W, int mode,
-                    uint16_t *out, const uint16_t *mask, const float *coef, float *coef_out,
-                    float *gain, hipStream_t st) {
+                    uint16_t *out, const float *coef, float *coef_out, float *gain,
+                    hipStream_t st) {
   dim3 grid((W + TW - 1) / TW, (H + TH - 1) / TH, P);
   if (mode == CONV_RELU && NB == 2)
     hipLaunchKernelGGL((k_conv3x3<2, CONV_RELU>), grid, dim3(256), 0, st, in, Wp, bias,
-                       bias_stride, pl, H, W, out, mask, coef, coef_out, gain);
-  else if (mode == CONV_MASKED && NB == 2)
-    hipLaunchKernelGGL((k_conv3x3<2, CONV_MASKED>), grid, dim3(256), 0, st, in, Wp, bias,
-                       bias_stride, pl, H, W, out, mask, coef, coef_out, gain);
+                       bias_stride, pl, H, W, out, coef, coef_out, gain);
   else if (mode == CONV_GAIN && NB == 1)
     hipLaunchKernelGGL((k_conv3x3<1, CONV_GAIN>), grid, dim3(256), 0, st, in, Wp, bias,
-                       bias_stride, pl, H, W, out, mask, coef, coef_out, gain);
+                       bias_stride, pl, H, W, out, coef, coef_out, gain);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -759,34 +588,6 @@ hipError_t cnn_fused(const float *coef, const CnnPlanes &pl, int P, int H, int W
   if (grid < 1) return hipSuccess;
   hipLaunchKernelGGL(k_cnn_fused, dim3(grid), dim3(kFusedThreads), 0, st, coef, pl, H, W, ntiles,
                      W1k, W2p, W3m, params, coef_out, gain);
-  return hipGetLastError();
-}
-
-hipError_t cnn_dz(const float *dcoef, const float *coef, const float *gain, const CnnPlanes &pl,
-                  int P, int H, int W, uint16_t *dz, float *dzf, hipStream_t st) {
-  const int HWn = H * W;
-  hipLaunchKernelGGL(k_cnn_dz, dim3((HWn + 255) / 256, P), dim3(256), 0, st, dcoef, coef, gain,
-                     pl, HWn, dz, dzf);
-  return hipGetLastError();
-}
-
-hipError_t cnn_wgrad(const uint16_t *x, const uint16_t *dy, int H, int W, int plane0,
-                     int nplanes, int nblocks, float *partial, float *outv, int in_blocks,
-                     int out_blocks, hipStream_t st) {
-  if (in_blocks == 2 && out_blocks == 2)
-    hipLaunchKernelGGL((k_conv_wgrad<2, 2>), dim3(nblocks), dim3(256), 0, st, x, dy, H, W, plane0,
-                       nplanes, partial);
-  else if (in_blocks == 1 && out_blocks == 2)
-    hipLaunchKernelGGL((k_conv_wgrad<1, 2>), dim3(nblocks), dim3(256), 0, st, x, dy, H, W, plane0,
-                       nplanes, partial);
-  else if (in_blocks == 2 && out_blocks == 1)
-    hipLaunchKernelGGL((k_conv_wgrad<2, 1>), dim3(nblocks), dim3(256), 0, st, x, dy, H, W, plane0,
-                       nplanes, partial);
-  else
-    return hipErrorInvalidValue;
-  const int len = 9 * CH * CH + CH;
-  hipLaunchKernelGGL(k_reduce_partials, dim3((len + 255) / 256), dim3(256), 0, st, partial,
-                     nblocks, len, outv);
   return hipGetLastError();
 }
 
@@ -819,7 +620,7 @@ __global__ void k_sqerr(const float *__restrict__ a, const float *__restrict__ b
 hipError_t sq_error_grad(const float *a, const float *b, size_t n, float scale, float *out,
                          float *partial, int nblocks, float *loss, hipStream_t st) {
   hipLaunchKernelGGL(k_sqerr, dim3(nblocks), dim3(256), 0, st, a, b, n, scale, out, partial);
-  hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(256), 0, st, partial, nblocks, 1, loss);
+  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, partial, nblocks, loss);
   return hipGetLastError();
 }
 
@@ -827,41 +628,6 @@ hipError_t cnn_copy_lowpass(const float *coef, float *coef_out, int B, int R, in
                             hipStream_t st) {
   hipLaunchKernelGGL(k_copy_lowpass, dim3((HWn + 255) / 256, B), dim3(256), 0, st, coef, coef_out,
                      R, HWn);
-  return hipGetLastError();
-}
-
-// Scatter the full [9][32][32] + [32] weight gradients of the three layers
-// into the parameter-blob layout of scale j (grads [J][kCnnParams]).
-// dW1 comes from x = x0 (ci < 2), dW3 from dy = dz (co = 0).
-__global__ void k_grad_assemble(const float *__restrict__ g1, const float *__restrict__ g2,
-                                const float *__restrict__ g3, int j, float *__restrict__ grads) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= kCnnParams) return;
-  constexpr int L = 9 * CH * CH;   // bias sums follow the weights
-  float v;
-  if (k < kOffB1) {            // W1[co][ci][t], ci < 2: full[t][ci][co] of layer 1
-    const int co = k / 18, ci = (k / 9) % 2, t = k % 9;
-    v = g1[(t * CH + ci) * CH + co];
-  } else if (k < kOffW2) {
-    v = g1[L + (k - kOffB1)];
-  } else if (k < kOffB2) {
-    const int q = k - kOffW2, co = q / 288, ci = (q / 9) % 32, t = q % 9;
-    v = g2[(t * CH + ci) * CH + co];
-  } else if (k < kOffW3) {
-    v = g2[L + (k - kOffB2)];
-  } else if (k < kOffB3) {     // W3[0][ci][t]
-    const int q = k - kOffW3, ci = q / 9, t = q % 9;
-    v = g3[(t * CH + ci) * CH + 0];
-  } else {
-    v = g3[L + 0];
-  }
-  grads[(size_t)j * kCnnParams + k] = v;
-}
-
-hipError_t cnn_grad_assemble(const float *dW1, const float *dW2, const float *dW3, int j,
-                             float *grads, hipStream_t st) {
-  hipLaunchKernelGGL(k_grad_assemble, dim3((kCnnParams + 255) / 256), dim3(256), 0, st, dW1, dW2,
-                     dW3, j, grads);
   return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@ namespace sl {
 constexpr int kOffW1 = 0, kOffB1 = 576, kOffW2 = 608, kOffB2 = 9824, kOffW3 = 9856,
               kOffB3 = 10144, kCnnParams = 10145;
 
-enum { CONV_RELU = 0, CONV_MASKED = 1, CONV_GAIN = 2 };
+enum { CONV_RELU = 0, CONV_GAIN = 1 };
 
 // Detail planes processed by a launch, grouped by scale: global plane g of
 // scale j (start[j] <= g < start[j+1]) is image (g - start[j]) / nsub[j] and
@@ -42,21 +42,26 @@ hipError_t cnn_x0(const float *coef, const CnnPlanes &pl, int P, int H, int W, u
                   hipStream_t st);
 hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float *bias,
                     int bias_stride, const CnnPlanes &pl, int P, int H, int W, int mode,
-                    uint16_t *out, const uint16_t *mask, const float *coef, float *coef_out,
-                    float *gain, hipStream_t st);
+                    uint16_t *out, const float *coef, float *coef_out, float *gain,
+                    hipStream_t st);
 // fused inference over P planes; a persistent grid (one or two blocks per
 // compute unit, by LDS size; nblocks = compute units) walks the output tiles
 hipError_t cnn_fused(const float *coef, const CnnPlanes &pl, int P, int H, int W,
                      const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W3m,
                      const float *params, float *coef_out, float *gain, int nblocks,
                      hipStream_t st);
-hipError_t cnn_dz(const float *dcoef, const float *coef, const float *gain, const CnnPlanes &pl,
-                  int P, int H, int W, uint16_t *dz, float *dzf, hipStream_t st);
-// weight gradient over planes [plane0, plane0 + nplanes) (local indices)
-// in_blocks / out_blocks: 16-channel blocks of x / dy that can be nonzero (1 or 2)
-hipError_t cnn_wgrad(const uint16_t *x, const uint16_t *dy, int H, int W, int plane0,
-                     int nplanes, int nblocks, float *partial, float *outv, int in_blocks,
-                     int out_blocks, hipStream_t st);
+// Blocks of the fused backward kernel: scale j owns blocks
+// [first[j], first[j + 1]); cnn_bwd_blocks fills bk and returns their number
+// (one partial gradient of kCnnParams floats each).
+struct CnnBwdBlocks {
+  int first[kMaxScales + 1];
+};
+int cnn_bwd_blocks(const CnnPlanes &pl, int H, int W, int num_cu, CnnBwdBlocks &bk);
+// weight gradients grads [J][kCnnParams] from coefficients and dL/d(coef_out)
+hipError_t cnn_bwd(const float *coef, const float *dcoef, const CnnPlanes &pl, int H, int W,
+                   const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W2tp,
+                   const float *params, int num_cu, float *partial, float *grads,
+                   hipStream_t st);
 hipError_t cnn_pack(const float *params, int J, int layer, int mode, uint16_t *Wp, int NB,
                     hipStream_t st);
 hipError_t cnn_adam(float *p, const float *g, float *m, float *v, int n, float lr, double b1,
@@ -65,7 +70,5 @@ hipError_t cnn_copy_lowpass(const float *coef, float *coef_out, int B, int R, in
                             hipStream_t st);
 hipError_t sq_error_grad(const float *a, const float *b, size_t n, float scale, float *out,
                          float *partial, int nblocks, float *loss, hipStream_t st);
-hipError_t cnn_grad_assemble(const float *dW1, const float *dW2, const float *dW3, int j,
-                             float *grads, hipStream_t st);
 
 }  // namespace sl

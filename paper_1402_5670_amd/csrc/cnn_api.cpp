@@ -24,8 +24,6 @@ constexpr size_t kPackLayer2 = 9 * 2 * 512;   // u16 per scale, two output block
 constexpr size_t kPackLayer1 = 9 * 1 * 512;   // one output block
 constexpr size_t kPackK1 = 2 * 512;             // layer 1, taps packed into K
 constexpr size_t kPackTaps3 = 512;              // layer 3, taps on the M axis
-constexpr int kWgradLen = 9 * 32 * 32 + 32;
-constexpr int kWgradBlocks = 512;
 constexpr int kErrBlocks = SL_SQERR_SCRATCH - 1;
 
 size_t al(size_t v) { return (v + 255) / 256 * 256; }
@@ -142,13 +140,12 @@ int sl_cnn_pack(const float *params_dev, int J, void *packed_dev, void *stream) 
 
 int sl_cnn_workspace_size(const sl_system *s, int batch, int training, size_t *bytes_out) {
   if (!s || !bytes_out || batch < 1) return sl::set_error(SL_EINVAL, "bad arguments");
-  const int P = batch * (s->R - 1);
   if (!training) {
     *bytes_out = layerwise() ? 2 * act_bytes(s, apply_chunk(s, batch)) : 256;
   } else {
-    const int J = s->cfg.J;
-    *bytes_out = 5 * act_bytes(s, P) + al((size_t)batch * s->R * s->cfg.npix() * 4) +
-                 al((size_t)kWgradBlocks * kWgradLen * 4) + al((size_t)3 * J * kWgradLen * 4);
+    // one partial gradient per block of the backward kernel, which runs at
+    // most one block per compute unit and one more per scale
+    *bytes_out = al((size_t)(s->num_cu + s->cfg.J) * kCnnParams * sizeof(float));
   }
   return SL_OK;
 }
@@ -186,11 +183,11 @@ int sl_cnn_apply(const sl_system *s, const float *params_dev, const void *packed
     pl.p0 = p0;
     CK(sl::cnn_x0(coeffs_dev, pl, n, H, W, A, st));
     CK(sl::cnn_conv(A, pk.w1, 2, params_dev + sl::kOffB1, kCnnParams, pl, n, H, W, sl::CONV_RELU,
-                    Bf, nullptr, nullptr, nullptr, nullptr, st));
+                    Bf, nullptr, nullptr, nullptr, st));
     CK(sl::cnn_conv(Bf, pk.w2, 2, params_dev + sl::kOffB2, kCnnParams, pl, n, H, W, sl::CONV_RELU,
-                    A, nullptr, nullptr, nullptr, nullptr, st));
+                    A, nullptr, nullptr, nullptr, st));
     CK(sl::cnn_conv(A, pk.w3, 1, params_dev + sl::kOffB3, kCnnParams, pl, n, H, W, sl::CONV_GAIN,
-                    nullptr, nullptr, coeffs_dev, coeffs_out_dev, gains_dev, st));
+                    nullptr, coeffs_dev, coeffs_out_dev, gains_dev, st));
   }
   return SL_OK;
 }
@@ -210,51 +207,12 @@ int sl_cnn_backward(const sl_system *s, const float *params_dev, const void *pac
   hipStream_t st = (hipStream_t)stream;
   int H, W;
   plane_hw(s, H, W);
-  const int J = s->cfg.J, P = batch * (s->R - 1);
-  Packed pk = packed_view(packed_dev, J);
-  char *w = (char *)workspace_dev;
-  const size_t ab = act_bytes(s, P);
-  uint16_t *X0 = (uint16_t *)w;
-  uint16_t *H1 = (uint16_t *)(w + ab);
-  uint16_t *H2 = (uint16_t *)(w + 2 * ab);
-  uint16_t *DZ = (uint16_t *)(w + 3 * ab);
-  uint16_t *DA2 = (uint16_t *)(w + 4 * ab);
-  float *G = (float *)(w + 5 * ab);
-  float *part = (float *)(w + 5 * ab + al((size_t)batch * s->R * s->cfg.npix() * 4));
-  float *dW = (float *)((char *)part + al((size_t)kWgradBlocks * kWgradLen * 4));
+  Packed pk = packed_view(packed_dev, s->cfg.J);
   sl::CnnPlanes pl = planes(s, batch, sigma_dev);
-  // forward recompute
-  CK(sl::cnn_x0(coeffs_dev, pl, P, H, W, X0, st));
-  CK(sl::cnn_conv(X0, pk.w1, 2, params_dev + sl::kOffB1, kCnnParams, pl, P, H, W, sl::CONV_RELU,
-                  H1, nullptr, nullptr, nullptr, nullptr, st));
-  CK(sl::cnn_conv(H1, pk.w2, 2, params_dev + sl::kOffB2, kCnnParams, pl, P, H, W, sl::CONV_RELU,
-                  H2, nullptr, nullptr, nullptr, nullptr, st));
-  CK(sl::cnn_conv(H2, pk.w3, 1, params_dev + sl::kOffB3, kCnnParams, pl, P, H, W, sl::CONV_GAIN,
-                  nullptr, nullptr, coeffs_dev, nullptr, G, st));
-  // backward
-  CK(sl::cnn_dz(dcoeffs_dev, coeffs_dev, G, pl, P, H, W, DZ, nullptr, st));
-  CK(sl::cnn_conv(DZ, pk.w3t, 2, nullptr, 0, pl, P, H, W, sl::CONV_MASKED, DA2, H2, nullptr,
-                  nullptr, nullptr, st));
-  const int tiles_per_plane = ((W + 31) / 32) * ((H + 7) / 8);
-  for (int j = 0; j < J; ++j)
+  for (int j = 0; j < s->cfg.J; ++j)
     if (pl.start[j + 1] == pl.start[j]) return sl::set_error(SL_EINVAL, "a scale without planes");
-  for (int j = 0; j < J; ++j) {
-    const int a = pl.start[j], n = pl.start[j + 1] - pl.start[j];
-    const int nb = std::min(kWgradBlocks, n * tiles_per_plane);
-    CK(sl::cnn_wgrad(H2, DZ, H, W, a, n, nb, part, dW + (size_t)(3 * j + 2) * kWgradLen, 2, 1, st));
-    CK(sl::cnn_wgrad(H1, DA2, H, W, a, n, nb, part, dW + (size_t)(3 * j + 1) * kWgradLen, 2, 2, st));
-  }
-  uint16_t *DA1 = DZ;
-  CK(sl::cnn_conv(DA2, pk.w2t, 2, nullptr, 0, pl, P, H, W, sl::CONV_MASKED, DA1, H1, nullptr,
-                  nullptr, nullptr, st));
-  for (int j = 0; j < J; ++j) {
-    const int a = pl.start[j], n = pl.start[j + 1] - pl.start[j];
-    float *g1 = dW + (size_t)(3 * j) * kWgradLen;
-    const int nb = std::min(kWgradBlocks, n * tiles_per_plane);
-    CK(sl::cnn_wgrad(X0, DA1, H, W, a, n, nb, part, g1, 1, 2, st));
-    CK(sl::cnn_grad_assemble(g1, dW + (size_t)(3 * j + 1) * kWgradLen,
-                             dW + (size_t)(3 * j + 2) * kWgradLen, j, grads_dev, st));
-  }
+  CK(sl::cnn_bwd(coeffs_dev, dcoeffs_dev, pl, H, W, pk.w1k, pk.w2, pk.w2t, params_dev, s->num_cu,
+                 (float *)workspace_dev, grads_dev, st));
   return SL_OK;
 }
 

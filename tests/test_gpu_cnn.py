@@ -160,6 +160,50 @@ def test_cnn_backward_matches_oracle():
                 assert rel(got[k], ref[j][k]) < 1e-3, (j, k, rel(got[k], ref[j][k]))
 
 
+@pytest.mark.parametrize("dims,Bn", [((8, 16), 1), ((16, 32), 1), ((24, 48), 2), ((32, 12), 1),
+                                     ((64, 96), 3)])
+def test_cnn_backward_tiles_match_oracle(dims, Bn):
+    """Gradients where the 16 x 32 tiles of the backward kernel begin and end:
+    planes smaller than a tile, exactly one tile, ragged in both directions,
+    narrower than a strip, and enough tiles that blocks walk several.
+
+    Tolerance as for the 64 x 64 case above: relative L2 <= 1e-3 per weight
+    tensor (occasional bfloat16 roundings that flip between float32 and
+    float64 accumulation), biases against the sum of their terms' magnitudes."""
+    print(f"case: cnn backward {dims} J=2 B={Bn}", flush=True)
+    sysg, sig, c, params, pg = _setup(dims=dims, Bn=Bn, seed=21)
+    net = B.Shrinkage(sysg, pg)
+    dc = np.random.default_rng(8).standard_normal(tuple(c.shape)).astype(np.float32)
+    gg = net.backward(c, _gpu(sig), _gpu(dc)).cpu().numpy()
+    again = net.backward(c, _gpu(sig), _gpu(dc)).cpu().numpy()
+    assert np.array_equal(gg, again)              # fixed summation order
+    cn = c.cpu().numpy().astype(np.float64)
+    l2 = np.array([s[4] for s in sysg.subbands], dtype=np.float32)
+    for j in range(sysg.n_scales):
+        ref = {k: np.zeros_like(v) for k, v in params[j].items()}
+        mag = {k: np.zeros_like(params[j][k]) for k in ("b1", "b2", "b3")}
+        for b in range(Bn):
+            for i in range(1, sysg.R):
+                if sysg.subbands[i][1] != j:
+                    continue
+                g, cache = OC.forward(params[j], cn[b, i], float(sig[b]), float(l2[i]), bf16=True)
+                dg = dc[b, i].astype(np.float64) * cn[b, i]
+                gr = OC.backward(cache, dg)
+                for k in gr:
+                    ref[k] += gr[k]
+                dz = OC.bf16_round(dg * g * (1 - g))[None]
+                da2 = OC.conv3x3_backward(cache["h2"], cache["W3"], dz)[0] * (cache["a2"] > 0)
+                da1 = OC.conv3x3_backward(cache["h1"], cache["W2"], OC.bf16_round(da2))[0] * (cache["a1"] > 0)
+                for k, d in (("b1", da1), ("b2", da2), ("b3", dz)):
+                    mag[k] += np.abs(d).sum(axis=(1, 2))
+        got = unblob(gg[j])
+        for k in ref:
+            if k in mag:
+                assert np.all(np.abs(got[k] - ref[k]) < 1e-3 * mag[k] + 1e-12), (dims, j, k)
+            else:
+                assert rel(got[k], ref[k]) < 1e-3, (dims, j, k, rel(got[k], ref[k]))
+
+
 def test_training_reduces_loss():
     # a few Adam steps on one batch: the image-domain loss must go down
     print("case: cnn training smoke 64x64", flush=True)
