@@ -59,9 +59,8 @@ struct CnnBwdBlocks {
 int cnn_bwd_blocks(const CnnPlanes &pl, int H, int W, int num_cu, CnnBwdBlocks &bk);
 // weight gradients grads [J][kCnnParams] from coefficients and dL/d(coef_out)
 hipError_t cnn_bwd(const float *coef, const float *dcoef, const CnnPlanes &pl, int H, int W,
-                   const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W2tp,
-                   const float *params, int num_cu, float *partial, float *grads,
-                   hipStream_t st);
+                   const uint16_t *W2p, const uint16_t *W2tp, const float *params, int num_cu,
+                   float *partial, float *grads, hipStream_t st);
 hipError_t cnn_pack(const float *params, int J, int layer, int mode, uint16_t *Wp, int NB,
                     hipStream_t st);
 hipError_t cnn_adam(float *p, const float *g, float *m, float *v, int n, float lr, double b1,

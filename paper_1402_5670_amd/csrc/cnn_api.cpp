@@ -211,7 +211,7 @@ int sl_cnn_backward(const sl_system *s, const float *params_dev, const void *pac
   sl::CnnPlanes pl = planes(s, batch, sigma_dev);
   for (int j = 0; j < s->cfg.J; ++j)
     if (pl.start[j + 1] == pl.start[j]) return sl::set_error(SL_EINVAL, "a scale without planes");
-  CK(sl::cnn_bwd(coeffs_dev, dcoeffs_dev, pl, H, W, pk.w1k, pk.w2, pk.w2t, params_dev, s->num_cu,
+  CK(sl::cnn_bwd(coeffs_dev, dcoeffs_dev, pl, H, W, pk.w2, pk.w2t, params_dev, s->num_cu,
                  (float *)workspace_dev, grads_dev, st));
   return SL_OK;
 }

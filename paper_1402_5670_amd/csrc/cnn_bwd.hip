@@ -19,11 +19,13 @@
 // v_mfma_f32_16x16x32_bf16 (64 lanes, n = lane % 16, g = lane / 16):
 //   A[m][k]: m = n, k = 8 g + j;  B[k][n]: k = 8 g + j;  D[m][n]: m = 4 g + e.
 // Activations are pixel-major in LDS, 32 channels in 64 bytes; the 16-byte
-// chunk c of the pixel in column x sits at chunk c ^ ((x / 4) % 4), which
-// spreads 16 consecutive pixels of a row over all banks.  Convolutions read
+// chunk c of the pixel in column x sits at chunk c ^ s, s the bits of
+// (x / 4) % 4 swapped.  Convolutions read
 // 8 channels of one pixel per lane; the weight gradients, whose reduction
 // axis is the pixels, read 4 pixels of one channel per lane with the
-// transposing LDS read (ds_read_b64_tr_b16).  Their 32 K slots are two
+// transposing LDS read (ds_read_b64_tr_b16).  The chunk permutation serves
+// both: 16 consecutive pixels at one chunk, and 8 consecutive pixels at one
+// half of their chunks, touch every bank once.  Their 32 K slots are two
 // vertically adjacent 16-pixel blocks: slot 8 g + j is pixel 4 g + j % 4 of
 // row j / 4.
 //
@@ -45,7 +47,15 @@ namespace sl {
 
 namespace {
 
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+};
+
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int BH = 16, BW = 32;                    // owned tile
@@ -60,7 +70,8 @@ constexpr int kOH2 = kOH1 + AH * AW * kPix;
 constexpr int kODA = kOH2 + EH * EW * kPix;        // da2; before it, layer-3 partial sums
 constexpr int kOX0 = kODA + DH * DW * kPix;
 constexpr int kODZ = kOX0 + XH * XW * 4;
-constexpr int kLdsBwd = kODZ + ZH * ZW * 2;
+constexpr int kOZero = kODZ + ZH * ZW * 4;         // four zero words
+constexpr int kLdsBwd = kOZero + 16;
 constexpr int NE = EH * EW;                        // pixels of the h2 region
 static_assert(9 * NE * 4 <= DH * DW * kPix, "layer-3 partial sums share the da2 region");
 static_assert(kLdsBwd <= 160 * 1024, "LDS of a compute unit");
@@ -70,17 +81,26 @@ constexpr int kXPer = (XH * XW + kBwdThreads - 1) / kBwdThreads;
 constexpr int kZPer = (ZH * ZW + kBwdThreads - 1) / kBwdThreads;
 
 // byte offset of 16-byte chunk c of column x within its pixel
-__device__ __forceinline__ int swz(int x, int c) { return (c ^ ((x >> 2) & 3)) << 4; }
+__device__ __forceinline__ int swz(int x, int c) {
+  return (c << 4) ^ (((x << 3) & 32) | ((x << 1) & 16));
+}
 
-// relu of 4 values, rounded to bfloat16, ANDed with the in-image mask
+// 4 values rounded to bfloat16 (round to nearest even)
+__device__ __forceinline__ uint2 pack4(f32x4 d) {
+  const bf16x2 a = __builtin_convertvector((f32x2){d[0], d[1]}, bf16x2);
+  const bf16x2 b = __builtin_convertvector((f32x2){d[2], d[3]}, bf16x2);
+  return make_uint2(*(const uint32_t *)&a, *(const uint32_t *)&b);
+}
+
+// relu of 4 values, rounded to bfloat16, ANDed with the in-image mask (a
+// maximum with 0 of the 16-bit patterns as signed integers: negative values
+// have the sign bit set)
 __device__ __forceinline__ uint2 relu_pack(f32x4 d, uint32_t in) {
-  bf16x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = (__bf16)fmaxf(d[e], 0.f);
-  uint2 u = *(const uint2 *)&o;
-  u.x &= in;
-  u.y &= in;
-  return u;
+  uint2 u = pack4(d);
+  const s16x2 z = {0, 0};
+  const s16x2 a = __builtin_elementwise_max(*(const s16x2 *)&u.x, z);
+  const s16x2 b = __builtin_elementwise_max(*(const s16x2 *)&u.y, z);
+  return make_uint2(*(const uint32_t *)&a & in, *(const uint32_t *)&b & in);
 }
 
 // 16-bit halves of v kept where the halves of h (bfloat16) are not zero
@@ -94,6 +114,15 @@ __device__ __forceinline__ bf16x8 frag(uint2 a, uint2 b) {
   return *(const bf16x8 *)&u;
 }
 
+// The value of x, computed anew: addresses derived from it stay inside their
+// phase of the tile loop instead of being kept in registers across it (the
+// operands and accumulators that live through the loop leave no room: hoisted
+// addresses spilled 79 registers and doubled the time of a tile).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -102,16 +131,17 @@ __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
 
 __global__ void __launch_bounds__(kBwdThreads)
 k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPlanes pl,
-          CnnBwdBlocks bk, int H, int W, const uint16_t *__restrict__ W1k,
-          const uint16_t *__restrict__ W2p, const uint16_t *__restrict__ W2tp,
+          CnnBwdBlocks bk, int H, int W, const uint16_t *__restrict__ W2p,
+          const uint16_t *__restrict__ W2tp,
           const float *__restrict__ params, float *__restrict__ partial) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsBwd];
-  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int lane = threadIdx.x & 63, n0 = lane & 15, g0 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = wave & 1, strip = (wave >> 1) & 1, half = wave >> 2;
   const size_t HWn = (size_t)H * W;
   uint32_t *x0s = (uint32_t *)(smem + kOX0);
-  uint16_t *dzs = (uint16_t *)(smem + kODZ);
+  // dz as pairs of bfloat16: element k holds dz[k] and dz[k + 1]
+  uint32_t *dzs = (uint32_t *)(smem + kODZ);
   float *d3 = (float *)(smem + kODA);
 
   // this block's scale, its planes and tiles
@@ -122,19 +152,28 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
   const int step = bk.first[j + 1] - bk.first[j];
   const float *P = params + (size_t)j * kCnnParams;
 
+  const int n = n0, g = g0;
   // ---- operands held for the whole kernel ----
   bf16x8 w1[2], w2[9], w2t[9], w3f, w3t[2];
   f32x4 bias1[2], bias2;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    w1[b] = *(const bf16x8 *)(W1k + (((size_t)j * 2 + b) * 64 + lane) * 8);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bias1[b][e] = P[kOffB1 + 16 * b + 4 * g + e];
-    // transposed layer 3, taps on K: channel 16 b + n, k = tap
+    // layer 1, taps and channels on K: lane group g < 3 holds tap row g,
+    // element 2 dx + c tap column dx of input channel c
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int t = 8 * g + e;
-      const uint16_t h = t < 9 ? f2bf(P[kOffW3 + (16 * b + n) * 9 + (t < 9 ? t : 0)]) : (uint16_t)0;
+      const bool used = g < 3 && e < 6;
+      const uint16_t h = used ? f2bf(P[kOffW1 + ((16 * b + n) * 2 + (e & 1)) * 9 + (used ? 3 * g + (e >> 1) : 0)]) : (uint16_t)0;
+      w1[b][e] = *(const __bf16 *)&h;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias1[b][e] = P[kOffB1 + 16 * b + 4 * g + e];
+    // transposed layer 3, taps on K: channel 16 b + n; lane group g < 3 holds
+    // the taps of row 2 - g, element e < 3 that of column 2 - e
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool used = g < 3 && e < 3;
+      const uint16_t h = used ? f2bf(P[kOffW3 + (16 * b + n) * 9 + (used ? 8 - 3 * g - e : 0)]) : (uint16_t)0;
       w3t[b][e] = *(const __bf16 *)&h;
     }
   }
@@ -181,53 +220,47 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
   float xr[kXPer], pc[kZPer], pd[kZPer];
   auto fetch = [&](const Tile &t) {
     const size_t o = ((size_t)t.b * pl.R + t.i) * HWn;
+    const float *cb = coef + o, *db = dcoef + o;
+    const int tid = fresh(threadIdx.x);
 #pragma unroll
     for (int u = 0; u < kXPer; ++u) {
-      const int q = threadIdx.x + u * kBwdThreads;
-      const int yy = t.ty0 - 5 + q / XW, xx = t.tx0 - 5 + q % XW;
-      xr[u] = (q < XH * XW && yy >= 0 && yy < H && xx >= 0 && xx < W) ? coef[o + (size_t)yy * W + xx] : 0.f;
+      const int q = tid + u * kBwdThreads;
+      const int r = (q * 1561) >> 16;                        // q / 42
+      const int yy = t.ty0 - 5 + r, xx = t.tx0 - 5 + q - r * XW;
+      const bool in = q < XH * XW && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
+      xr[u] = in ? cb[yy * W + xx] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kZPer; ++u) {
-      const int q = threadIdx.x + u * kBwdThreads;
-      const int yy = t.ty0 - 2 + q / ZW, xx = t.tx0 - 2 + q % ZW;
-      const bool in = q < ZH * ZW && yy >= 0 && yy < H && xx >= 0 && xx < W;
-      const size_t k = o + (in ? (size_t)yy * W + xx : 0);
-      pc[u] = in ? coef[k] : 0.f;
-      pd[u] = in ? dcoef[k] : 0.f;
+      const int q = tid + u * kBwdThreads;
+      const int r = (q * 1821) >> 16;                        // q / 36
+      const int yy = t.ty0 - 2 + r, xx = t.tx0 - 2 + q - r * ZW;
+      const bool in = q < ZH * ZW && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
+      pc[u] = in ? cb[yy * W + xx] : 0.f;
+      pd[u] = in ? db[yy * W + xx] : 0.f;
     }
   };
 
-  // layer-1 operand: dword h of a lane's K slice is tap 4 g + h (the slots of
-  // taps >= 9 have zero weights and read tap 0)
-  int toff[4];
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int t = 4 * g + h;
-    toff[h] = t < 9 ? (t / 3) * XW + t % 3 : 0;
-  }
-  // transposed layer-3 operand: element e of lane group 0 is tap e, element 0
-  // of group 1 tap 8, the rest zero
-  const uint32_t zm0 = g == 0 ? 0xFFFFFFFFu : g == 1 ? 0xFFFFu : 0u;
-  const uint32_t zm1 = g == 0 ? 0xFFFFFFFFu : 0u;
-  const int zt0 = g == 1 ? 0 : 2 * ZW + 2;
-
+  if (threadIdx.x < 4) *(uint32_t *)(smem + kOZero + 4 * threadIdx.x) = 0u;
   int q = (int)blockIdx.x - bk.first[j];
   Tile t = tile_at(q < ntiles ? q : 0);
   if (q < ntiles) fetch(t);
   for (; q < ntiles; q += step) {
     const int ty0 = t.ty0, tx0 = t.tx0;
+    const bool interior = ty0 >= 5 && ty0 + BH + 5 <= H && tx0 >= 5 && tx0 + BW + 5 <= W;
     // ---- x0 of this tile ----
     float prod[kZPer];
     {
       const float sg = pl.sigma[t.b], den = sg * pl.l2[t.i];
       const uint32_t ch1 = (uint32_t)f2bf(sg * (255.0f / 50.0f)) << 16;
+      const int tx = fresh(threadIdx.x);
 #pragma unroll
       for (int u = 0; u < kXPer; ++u) {
-        const int k = threadIdx.x + u * kBwdThreads;
+        const int k = tx + u * kBwdThreads;
         if (k >= XH * XW) continue;
-        const int yy = ty0 - 5 + k / XW, xx = tx0 - 5 + k % XW;
-        const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W;
+        const int r = (k * 1561) >> 16;                      // k / 42
+        const int yy = ty0 - 5 + r, xx = tx0 - 5 + k - r * XW;
+        const bool in = (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
         x0s[k] = in ? ((uint32_t)f2bf(fabsf(xr[u]) / den) | ch1) : 0u;
       }
 #pragma unroll
@@ -235,22 +268,43 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
     }
     __syncthreads();
 
-    // ---- layer 1 on T+4 ----
-#pragma unroll 2
-    for (int bl = wave; bl < AH * AW / 16; bl += NWV) {
-      const int p = bl * 16 + n, r = p / AW, c = p % AW;
-      const int base = r * XW + c;
-      uint32_t u[4];
+    // ---- layer 1 on T+4: three rows of 40 pixels per wave ----
+    {
+      const int n = fresh(n0), g = fresh(g0);
+      static_assert(AH == 3 * NWV && AW == 40, "rows per wave");
+      // pixel q of the wave's 120 (the last 8 lanes of block 7 repeat the last
+      // pixel); lane group 3, whose weights are zero, reads zeros
+      auto l1 = [&](int k0, auto count) {
+        constexpr int S = decltype(count)::value;
+        bf16x8 xb[S];
+        int o[S];
+        uint32_t in[S];
 #pragma unroll
-      for (int h = 0; h < 4; ++h) u[h] = x0s[base + toff[h]];
-      const bf16x8 xb = *(const bf16x8 *)u;
-      const int yy = ty0 - 4 + r, xx = tx0 - 4 + c;
-      const uint32_t in = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? 0xFFFFFFFFu : 0u;
+        for (int s = 0; s < S; ++s) {
+          const int q = min(16 * (k0 + s) + n, 3 * AW - 1);
+          const int rl = (q >= AW) + (q >= 2 * AW), c = q - rl * AW;
+          const uint32_t *xp = (const uint32_t *)(smem + (g < 3 ? kOX0 + ((3 * wave + g) * XW + q + 2 * rl) * 4 : kOZero));
+          xb[s] = frag(make_uint2(xp[0], xp[1]), make_uint2(xp[2], 0u));
+          o[s] = kOH1 + (3 * wave * AW + q) * kPix + (swz(c, g >> 1) | (g & 1) * 8);
+          in[s] = 0xFFFFFFFFu;
+          if (!interior) {
+            const int yy = ty0 - 4 + 3 * wave + rl, xx = tx0 - 4 + c;
+            in[s] = ((unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W) ? 0xFFFFFFFFu : 0u;
+          }
+        }
+        f32x4 d[S][2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const f32x4 d = mma(w1[b], xb, bias1[b]);
-        *(uint2 *)(smem + kOH1 + p * kPix + swz(c, 2 * b + (g >> 1)) + (g & 1) * 8) = relu_pack(d, in);
-      }
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) d[s][b] = mma(w1[b], xb[s], bias1[b]);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          *(uint2 *)(smem + o[s]) = relu_pack(d[s][0], in[s]);
+          *(uint2 *)(smem + (o[s] ^ 32)) = relu_pack(d[s][1], in[s]);
+        }
+      };
+      l1(0, IntC<4>{});
+      l1(4, IntC<4>{});
     }
     __syncthreads();
 
@@ -259,13 +313,14 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
     {
       constexpr int RH = EH / 2;
       static_assert(EH % 2 == 0 && EW - 32 == 6, "strip geometry");
+      const int n = fresh(n0), g = fresh(g0);
       const int r0 = RH * half, c = 16 * strip + n;
       int ad[3];
 #pragma unroll
       for (int dx = 0; dx < 3; ++dx)
         ad[dx] = kOH1 + (r0 * AW + c + dx) * kPix + swz(c + dx, g);
       const int st = kOH2 + (r0 * EW + c) * kPix + swz(c, 2 * nb + (g >> 1)) + (g & 1) * 8;
-      const bool cin = tx0 - 3 + c >= 0 && tx0 - 3 + c < W;
+      const bool cin = (unsigned)(tx0 - 3 + c) < (unsigned)W;
       f32x4 acc[3];
       bf16x8 fr[2][3];
 #pragma unroll
@@ -289,95 +344,143 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
         __builtin_amdgcn_s_setprio(0);
         if (y >= 2) {
           const int yy = ty0 - 3 + r0 + y - 2;
-          const uint32_t in = (cin && yy >= 0 && yy < H) ? 0xFFFFFFFFu : 0u;
+          const uint32_t in = (cin && (unsigned)yy < (unsigned)H) ? 0xFFFFFFFFu : 0u;
           *(uint2 *)(smem + st + (y - 2) * EW * kPix) = relu_pack(acc[(y - 2) % 3], in);
         }
       }
+      // (22 rows of 6 pixels: blocks wave / 2, + 4 and, for the first pair of
+      // waves, + 8)
       constexpr int NL = EH * 6;
-#pragma unroll 1
-      for (int bl = wave >> 1; bl < (NL + 15) / 16; bl += NWV / 2) {
-        const int l = bl * 16 + n, lc = l < NL ? l : NL - 1;
-        const int r = lc / 6, cl = 32 + lc % 6;
-        f32x4 a = bias2;
-        bf16x8 f[9];
+      static_assert((NL + 15) / 16 == 9, "blocks of the remaining columns");
+      auto rest = [&](int b0, auto count) {
+        constexpr int S = decltype(count)::value;
+        f32x4 a[S];
+        int o[S][3], so[S];
+        uint32_t in[S];
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-          const int o = kOH1 + (r * AW + cl + dx) * kPix + swz(cl + dx, g);
+        for (int s = 0; s < S; ++s) {
+          // (lanes past the last pixel repeat it)
+          const int l = min((b0 + 4 * s) * 16 + n, NL - 1);
+          const int r = (l * 10923) >> 16, cl = 32 + l - 6 * r;   // l / 6
+          in[s] = 0xFFFFFFFFu;
+          if (!interior) {
+            const int yy = ty0 - 3 + r, xx = tx0 - 3 + cl;
+            in[s] = ((unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W) ? 0xFFFFFFFFu : 0u;
+          }
 #pragma unroll
-          for (int dy = 0; dy < 3; ++dy) f[3 * dy + dx] = *(const bf16x8 *)(smem + o + dy * AW * kPix);
+          for (int dx = 0; dx < 3; ++dx) o[s][dx] = kOH1 + (r * AW + cl + dx) * kPix + swz(cl + dx, g);
+          so[s] = kOH2 + (r * EW + cl) * kPix + swz(cl, 2 * nb + (g >> 1)) + (g & 1) * 8;
+          a[s] = bias2;
         }
 #pragma unroll
-        for (int k = 0; k < 9; ++k) a = mma(w2[k], f[k], a);
-        const int yy = ty0 - 3 + r, xx = tx0 - 3 + cl;
-        const uint32_t in = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? 0xFFFFFFFFu : 0u;
-        if (l < NL)
-          *(uint2 *)(smem + kOH2 + (r * EW + cl) * kPix + swz(cl, 2 * nb + (g >> 1)) + (g & 1) * 8) = relu_pack(a, in);
-      }
+        for (int k = 0; k < 9; ++k)
+#pragma unroll
+          for (int s = 0; s < S; ++s)
+            a[s] = mma(w2[k], *(const bf16x8 *)(smem + o[s][k % 3] + (k / 3) * AW * kPix), a[s]);
+#pragma unroll
+        for (int s = 0; s < S; ++s) *(uint2 *)(smem + so[s]) = relu_pack(a[s], in[s]);
+      };
+      rest(wave >> 1, IntC<2>{});
+      if (wave < 2) rest(8, IntC<1>{});
     }
     __syncthreads();
 
     // ---- layer 3: D[tap][p] = sum_ci W3[ci][tap] h2[p][ci] on T+3 ----
-#pragma unroll 2
-    for (int bl = wave; bl < (NE + 15) / 16; bl += NWV) {
-      const int p = bl * 16 + n, pc_ = p < NE ? p : NE - 1;
-      const bf16x8 hb = *(const bf16x8 *)(smem + kOH2 + pc_ * kPix + swz(pc_ % EW, g));
-      const f32x4 d = mma(w3f, hb, zero4);
-      if (p < NE && g < 3) {
-        d3[(4 * g) * NE + p] = d[0];
-        if (g < 2) {
+    // (rows wave, wave + 8, wave + 16 in blocks of 16, 16 and 6 pixels)
+    {
+      const int n = fresh(n0), g = fresh(g0);
+      const int cl = min(32 + n, EW - 1);
+      const int hc[3] = {n * kPix + swz(n, g), (16 + n) * kPix + swz(16 + n, g), cl * kPix + swz(cl, g)};
+      const int dc[3] = {n, 16 + n, cl};
+      f32x4 d[3][3];
 #pragma unroll
-          for (int e = 1; e < 4; ++e) d3[(4 * g + e) * NE + p] = d[e];
-        }
+      for (int rr = 0; rr < 3; ++rr) {
+        const int r = min(wave + NWV * rr, EH - 1);
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          d[rr][k] = mma(w3f, *(const bf16x8 *)(smem + kOH2 + r * EW * kPix + hc[k]), zero4);
+      }
+      // lane group g holds taps 4 g ..: 4, 4 and 1 of them are used
+      if (g < 3) {
+#pragma unroll
+        for (int rr = 0; rr < 3; ++rr)
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+            d3[4 * g * NE + min(wave + NWV * rr, EH - 1) * EW + dc[k]] = d[rr][k][0];
+      }
+      if (g < 2) {
+#pragma unroll
+        for (int rr = 0; rr < 3; ++rr)
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int e = 1; e < 4; ++e)
+              d3[(4 * g + e) * NE + min(wave + NWV * rr, EH - 1) * EW + dc[k]] = d[rr][k][e];
       }
     }
     __syncthreads();
 
     // ---- gain and dz = dL/dc' c g (1 - g) on T+2 ----
+    {
+      const int tid = fresh(threadIdx.x);
 #pragma unroll
-    for (int u = 0; u < kZPer; ++u) {
-      const int k = threadIdx.x + u * kBwdThreads;
-      if (k < ZH * ZW) {
-        const int r = k / ZW, c = k % ZW;
-        float z = b3;
+      for (int u = 0; u < kZPer; ++u) {
+        const int k = tid + u * kBwdThreads;
+        if (k < ZH * ZW) {
+          const int r = (k * 1821) >> 16, c = k - r * ZW;   // k / 36
+          float z = b3;
 #pragma unroll
-        for (int e = 0; e < 9; ++e) z += d3[e * NE + (r + e / 3) * EW + c + e % 3];
-        const float gv = 1.0f / (1.0f + __expf(-z));
-        const int yy = ty0 - 2 + r, xx = tx0 - 2 + c;
-        const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W;
-        const uint16_t v = in ? f2bf(prod[u] * gv * (1.f - gv)) : (uint16_t)0;
-        dzs[k] = v;
-        if (r >= 2 && r < 2 + BH && c >= 2 && c < 2 + BW) gb3 += bf2f(v);
+          for (int e = 0; e < 9; ++e) z += d3[k + 2 * r + e * NE + (e / 3) * EW + e % 3];
+          const float gv = 1.0f / (1.0f + __expf(-z));
+          const int yy = ty0 - 2 + r, xx = tx0 - 2 + c;
+          const bool in = (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
+          const uint16_t v = in ? f2bf(prod[u] * gv * (1.f - gv)) : (uint16_t)0;
+          ((uint16_t *)dzs)[2 * k] = v;
+          if (k > 0) ((uint16_t *)dzs)[2 * k - 1] = v;
+          if (r >= 2 && r < 2 + BH && c >= 2 && c < 2 + BW) gb3 += bf2f(v);
+        }
       }
     }
     __syncthreads();
 
     // ---- da2 = [h2 > 0] (W3 transposed) dz on T+1, taps on K ----
-    // element e of pixel (r, c): dz of tap e at (r + 2 - dy, c + 2 - dx) of T+2
-#pragma unroll 2
-    for (int bl = wave; bl < (DH * DW + 15) / 16; bl += NWV) {
-      const int p = bl * 16 + n, pq = p < DH * DW ? p : DH * DW - 1;
-      const int r = pq / DW, c = pq % DW;
-      const uint16_t *zp = dzs + r * ZW + c;
-      uint32_t v[8];
-      v[0] = zp[zt0];
+    // lane group g < 3 reads the three dz of row r + g of T+2 (columns c ..);
+    // lanes past the last pixel repeat it
+    {
+      const int n = fresh(n0), g = fresh(g0);
+      auto l3t = [&](int b0, auto count) {
+        constexpr int S = decltype(count)::value;
+        bf16x8 zb[S];
+        uint2 h[S][2];
+        int o[S];
 #pragma unroll
-      for (int e = 1; e < 8; ++e) v[e] = zp[2 * ZW + 2 - (e / 3) * ZW - e % 3];
-      const uint2 lo = make_uint2((v[0] | v[1] << 16) & zm0, (v[2] | v[3] << 16) & zm1);
-      const uint2 hi = make_uint2((v[4] | v[5] << 16) & zm1, (v[6] | v[7] << 16) & zm1);
-      const bf16x8 zb = frag(lo, hi);
+        for (int s = 0; s < S; ++s) {
+          const int p = min((b0 + NWV * s) * 16 + n, DH * DW - 1);
+          const int r = (p * 1928) >> 16, c = p - DW * r;     // p / 34
+          const uint32_t *zp = (const uint32_t *)(smem + (g < 3 ? kODZ + (p + 2 * r + g * ZW) * 4 : kOZero));
+          zb[s] = frag(make_uint2(zp[0], zp[2] & 0xFFFFu), make_uint2(0u, 0u));
+          const int ho = kOH2 + (p + 4 * r + 2 * EW + 2) * kPix + (swz(c + 2, g >> 1) | (g & 1) * 8);
+          h[s][0] = *(const uint2 *)(smem + ho);
+          h[s][1] = *(const uint2 *)(smem + (ho ^ 32));
+          o[s] = kODA + p * kPix + (swz(c, g >> 1) | (g & 1) * 8);
+        }
+        f32x4 d[S][2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const f32x4 d = mma(w3t[b], zb, zero4);
-        const uint2 h = *(const uint2 *)(smem + kOH2 + ((r + 2) * EW + c + 2) * kPix +
-                                         swz(c + 2, 2 * b + (g >> 1)) + (g & 1) * 8);
-        bf16x4 o;
+        for (int s = 0; s < S; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (__bf16)d[e];
-        const uint2 w = *(const uint2 *)&o;
-        if (p < DH * DW)
-          *(uint2 *)(smem + kODA + p * kPix + swz(c, 2 * b + (g >> 1)) + (g & 1) * 8) =
-              make_uint2(keep_nonzero(w.x, h.x), keep_nonzero(w.y, h.y));
-      }
+          for (int b = 0; b < 2; ++b) d[s][b] = mma(w3t[b], zb[s], zero4);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const uint2 w = pack4(d[s][b]);
+            *(uint2 *)(smem + (b ? o[s] ^ 32 : o[s])) =
+                make_uint2(keep_nonzero(w.x, h[s][b].x), keep_nonzero(w.y, h[s][b].y));
+          }
+      };
+      static_assert((DH * DW + 15) / 16 <= 5 * NWV, "blocks of da2");
+      l3t(wave, IntC<3>{});
+      l3t(wave + 3 * NWV, IntC<2>{});
     }
     // the next tile's coefficients land during the gradient products below
     const Tile tn = tile_at(q + step < ntiles ? q + step : q);
@@ -389,6 +492,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
     // 16 nb + n: two rows make the pixel operand of dW1 in registers ----
     {
       constexpr int RH = BH / 2;
+      const int n = fresh(n0), g = fresh(g0);
       const int r0 = RH * half, c = 16 * strip + n;
       int ad[3];
 #pragma unroll
@@ -422,13 +526,13 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
         __builtin_amdgcn_s_setprio(0);
         if (y >= 2) {
           const int r = y - 2;
-          bf16x4 o;
+          f32x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const uint16_t h = *(const uint16_t *)(smem + hm + (r * AW + e) * kPix);
-            o[e] = (__bf16)(h != 0 ? acc[r % 3][e] : 0.f);
+            o[e] = h != 0 ? acc[r % 3][e] : 0.f;
           }
-          const uint2 cur = *(const uint2 *)&o;
+          const uint2 cur = pack4(o);
           if (r & 1) {
             const bf16x8 db = frag(prev, cur);
             uint2 c0[2], c1[2];
@@ -454,6 +558,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
     // ---- dW2 of channels (16 half .., 16 nb ..) over the strip; dW3 of
     // channels 16 half .. (waves with nb = 1) ----
     {
+      const int n = fresh(n0), g = fresh(g0);
       // lane i of a 16-lane group reads pixel 4 g + i / 4, channels 4 (i % 4) ..
       const int px = 16 * strip + 4 * g + (n >> 2), ch = n & 3;
       int ah[3];
@@ -465,7 +570,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
       const int ab = kODA + (DW + px + 1) * kPix + swz(px + 1, 2 * nb + (ch >> 1)) + (ch & 1) * 8;
       const int ae = kOH2 + (3 * EW + px + 3) * kPix + swz(px + 3, 2 * half + (ch >> 1)) + (ch & 1) * 8;
       const int tap = n < 9 ? n : 8;
-      const uint16_t *zp = dzs + (3 - tap / 3) * ZW + 16 * strip + 4 * g + 3 - tap % 3;
+      const uint32_t *zp = dzs + (3 - tap / 3) * ZW + 16 * strip + 4 * g + 3 - tap % 3;
       auto tr = [&](int off) -> uint2 {
         const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(smem + off));
         return *(const uint2 *)&v;
@@ -492,12 +597,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
         if (nb == 1) {
           uint2 z[2];
 #pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            uint32_t v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = zp[(r + k) * ZW + e];
-            z[k] = make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
-          }
+          for (int k = 0; k < 2; ++k) z[k] = make_uint2(zp[(r + k) * ZW], zp[(r + k) * ZW + 2]);
           g3 = mma(frag(tr(ae + r * EW * kPix), tr(ae + (r + 1) * EW * kPix)), frag(z[0], z[1]), g3);
         }
       }
@@ -579,13 +679,12 @@ int cnn_bwd_blocks(const CnnPlanes &pl, int H, int W, int num_cu, CnnBwdBlocks &
 }
 
 hipError_t cnn_bwd(const float *coef, const float *dcoef, const CnnPlanes &pl, int H, int W,
-                   const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W2tp,
-                   const float *params, int num_cu, float *partial, float *grads,
-                   hipStream_t st) {
+                   const uint16_t *W2p, const uint16_t *W2tp, const float *params, int num_cu,
+                   float *partial, float *grads, hipStream_t st) {
   CnnBwdBlocks bk{};
   const int nblk = cnn_bwd_blocks(pl, H, W, num_cu, bk);
   hipLaunchKernelGGL(k_cnn_bwd, dim3(nblk), dim3(kBwdThreads), 0, st, coef, dcoef, pl, bk, H, W,
-                     W1k, W2p, W2tp, params, partial);
+                     W2p, W2tp, params, partial);
   hipLaunchKernelGGL(k_cnn_bwd_sum, dim3((kCnnParams + 255) / 256, pl.J), dim3(256), 0, st,
                      partial, bk, grads);
   return hipGetLastError();
