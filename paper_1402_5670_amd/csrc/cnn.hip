@@ -142,63 +142,40 @@ k_conv3x3(const uint16_t *__restrict__ in, const uint16_t *__restrict__ Wp,
 }
 
 // ---------------------------------------------------------------------------
-// fused inference: the three layers of 16 x 32 output tiles in LDS
+// fused inference: the three layers of 12 x 32 output tiles in LDS
 // ---------------------------------------------------------------------------
-// Regions (rows x cols): x0 22 x 38, h1 20 x 36, h2 18 x 34, output 16 x 32.
+// Regions (rows x cols): x0 18 x 38, h1 16 x 36, h2 14 x 34, output 12 x 32.
 // Activations outside the image are zero (the "same" zero padding of every
-// layer).  The weights are the A operand and the activations the B operand,
-// so each lane receives 4 consecutive output channels of one pixel
-// (D[m = channel][n = pixel]) and stores them with one 8-byte LDS write.
-// Layer 1 packs its 9 taps x 2 input channels into one K = 32 operand
-// (k = 2 t + c, k >= 18 zero); layer 2 is the per-tap implicit GEMM.  Layer 3
-// has one output channel: an MFMA with the 9 taps on the M axis yields
-// D[t][p] = sum_ci W3[ci][t] h2[p][ci] for every h2 pixel p, and the output is
-// b3 + sum_t D[t][p + offset(t)].  D needs h2 at p only, so it is computed
-// from the layer-2 accumulators in registers and h2 never reaches LDS.
-// h1 pixels are padded to 48 channels (96 bytes, 16-byte aligned).  Measured
-// per 32 images: 40 channels 17.7 ms, 48 channels 17.3 ms, 56 channels
-// 17.9 ms, 64 channels (128-byte stride) 24.0 ms.
-// Output tile FTH x 32 (SL_CNN_FTH = 16 or 8), one thread per output pixel;
-// pixel stride of h1 SL_CNN_CHP bfloat16 values (>= 32, a multiple of 8).
-#ifndef SL_CNN_FTH
-#define SL_CNN_FTH 16
-#endif
-#ifndef SL_CNN_CHP
-#define SL_CNN_CHP 48
-#endif
-constexpr int FTH = SL_CNN_FTH, FTW = 32;
+// layer).  Layer 1 packs its 9 taps x 2 input channels into one K = 32
+// operand (k = 2 t + c, k >= 18 zero); layer 2 is the per-tap implicit GEMM.
+// Layer 3 has one output channel: a product with the 9 taps on the M axis
+// yields D[t][p] = sum_ci W3[ci][t] h2[p][ci], and the output is
+// b3 + sum_t D[t][p + offset(t)]; h2 never reaches LDS.
+//
+// A wave computes 16 of the 32 channels of layer 2 (nb = wave % 2), so its
+// operands take 36 registers instead of 72 and two blocks of 8 waves run per
+// compute unit (128 registers, 74 KiB of LDS): one block's matrix products
+// overlap the other's element work and barriers.  Layer 2 streams down two
+// 16-pixel strips (three shifted operands of an input row feed three output
+// rows, a third of the LDS reads of nine operands per row); the two columns
+// left over go in two blocks.  Each half of the channels leaves its own layer-3
+// sums D in LDS (adding them there with LDS atomics took 13 ms per 8 images);
+// 12 rows keep both within two blocks' share.
+// One 512-thread block per CU holding all 72 operand registers per wave, nine
+// LDS operands per 16 pixels and 48-channel pixel strides: 16.4 ms per
+// 32 x 512^2 images; this form 12.9 ms (8 images: 4.1 -> 3.2 ms).
+constexpr int FTH = 12, FTW = 32;
 constexpr int X0H = FTH + 6, X0W = FTW + 6;
 constexpr int H1H = FTH + 4, H1W = FTW + 4;
 constexpr int H2H = FTH + 2, H2W = FTW + 2;
 constexpr int NX0 = X0H * X0W, NH1 = H1H * H1W, NH2 = H2H * H2W;
-constexpr int CHP = SL_CNN_CHP;
-constexpr int kFusedThreads = FTH * FTW;
-static_assert(NH1 % 16 == 0 && CHP % 8 == 0 && CHP >= 32, "tile geometry");
+constexpr int kFusedThreads = 512, kFusedWaves = kFusedThreads / 64;
+static_assert(NH1 % 16 == 0 && H2W == 34, "tile geometry");
 constexpr int kX0PerThread = (NX0 + kFusedThreads - 1) / kFusedThreads;
-// LDS (bytes): h1 | layer-3 partial sums D[16][NH2] | x0 | 2 x raw centre
-// coefficients.  h2 never reaches LDS: layer 3 consumes it from the layer-2
-// accumulators.
-constexpr int kLdsH1 = NH1 * CHP * 2, kLdsD3 = 16 * NH2 * 4, kLdsX0 = ((NX0 * 4 + 15) / 16) * 16,
-              kLdsC = FTH * FTW * 4;
-constexpr int kLdsFused = kLdsH1 + kLdsD3 + kLdsX0 + 2 * kLdsC;
-// blocks of the persistent grid per compute unit (160 KiB of LDS each)
-constexpr int kFusedBlocksPerCU = (2 * kLdsFused <= 160 * 1024) ? 2 : 1;
-
-// relu(d) on 4 channels (the bias is the accumulator's initial value), zero
-// outside the image, rounded to bfloat16 (round to nearest even, as f2bf) by
-// the native conversion
-// (relu as a signed integer maximum of the float bits: negative floats have
-// the sign bit set, so max(bits, 0) maps them to +0 and keeps the others)
-template <bool INTERIOR>
-__device__ __forceinline__ bf16x4 relu_bf16x4(f32x4 d, bool in) {
-  bf16x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float v = __int_as_float(max(__float_as_int(d[e]), 0));
-    o[e] = (__bf16)((INTERIOR || in) ? v : 0.f);
-  }
-  return o;
-}
+// LDS (bytes): h1 | layer-3 sums D[2][9][NH2] | x0
+constexpr int kFOD3 = NH1 * kPix, kFOX0 = kFOD3 + 2 * 9 * NH2 * 4, kLdsFused = kFOX0 + NX0 * 4;
+constexpr int kFusedBlocksPerCU = 2;
+static_assert(kFusedBlocksPerCU * kLdsFused <= 160 * 1024, "LDS of a compute unit");
 
 struct FusedTile {
   int p, ty0, tx0, b, i, j;
@@ -215,266 +192,235 @@ __device__ __forceinline__ FusedTile fused_tile(const CnnPlanes &pl, int tile, i
   return f;
 }
 
-template <int V>
-struct IntC {
-  static constexpr int value = V;
-};
-
-__global__ void __launch_bounds__(kFusedThreads)
+__global__ void __launch_bounds__(kFusedThreads, 4)
 k_cnn_fused(const float *__restrict__ coef, CnnPlanes pl, int H, int W, int ntiles,
             const uint16_t *__restrict__ W1k, const uint16_t *__restrict__ W2p,
-            const uint16_t *__restrict__ W3m, const float *__restrict__ params,
-            float *__restrict__ coef_out, float *__restrict__ gain) {
+            const float *__restrict__ params, float *__restrict__ coef_out,
+            float *__restrict__ gain) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsFused];
-  uint16_t *h1s = (uint16_t *)smem;
-  float *d3 = (float *)(smem + kLdsH1);
-  uint32_t *x0s = (uint32_t *)(smem + kLdsH1 + kLdsD3);
-  float *cs = (float *)(smem + kLdsH1 + kLdsD3 + kLdsX0);   // [2][FTH * FTW]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
-  constexpr int NW = kFusedThreads / 64;
+  float *d3 = (float *)(smem + kFOD3);
+  uint32_t *x0s = (uint32_t *)(smem + kFOX0);
+  const int lane = threadIdx.x & 63, n0 = lane & 15, g0 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = wave & 1, strip = (wave >> 1) & 1, half = wave >> 2;
   const int tiles_x = (W + FTW - 1) / FTW;
   const int tiles_per_plane = tiles_x * ((H + FTH - 1) / FTH);
   const size_t HWn = (size_t)H * W;
 
-  // x0 staging: thread positions in the x0 region do not depend on the tile
-  int xq_r[kX0PerThread], xq_c[kX0PerThread], xq_cs[kX0PerThread];
-#pragma unroll
-  for (int u = 0; u < kX0PerThread; ++u) {
-    const int q = threadIdx.x + u * kFusedThreads;
-    xq_r[u] = q < NX0 ? q / X0W : -1000;
-    xq_c[u] = q % X0W;
-    const int r = xq_r[u], c = xq_c[u];
-    xq_cs[u] = (r >= 3 && r < 3 + FTH && c >= 3 && c < 3 + FTW) ? (r - 3) * FTW + c - 3 : -1;
-  }
-  float xr[kX0PerThread];
+  // coefficients of the x0 region and of the thread's output pixel
+  float xr[kX0PerThread], cen;
   auto fetch = [&](const FusedTile &f) {
     const float *cpl = coef + ((size_t)f.b * pl.R + f.i) * HWn;
+    const int tid = fresh(threadIdx.x);
 #pragma unroll
     for (int u = 0; u < kX0PerThread; ++u) {
-      const int yy = f.ty0 - 3 + xq_r[u], xx = f.tx0 - 3 + xq_c[u];
-      xr[u] = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? cpl[(size_t)yy * W + xx] : 0.f;
+      const int q = tid + u * kFusedThreads, r = (q * 1725) >> 16;       // q / 38
+      const int yy = f.ty0 - 3 + r, xx = f.tx0 - 3 + q - r * X0W;
+      const bool in = q < NX0 && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
+      xr[u] = in ? cpl[yy * W + xx] : 0.f;
     }
+    const int yy = f.ty0 + (tid >> 5), xx = f.tx0 + (tid & 31);
+    cen = (tid < FTH * FTW && yy < H && xx < W) ? cpl[yy * W + xx] : 0.f;
   };
-  auto stage = [&](const FusedTile &f, int buf) {
+  auto stage = [&](const FusedTile &f) {
     const float sg = pl.sigma[f.b];
     const float inv = 1.0f / (sg * pl.l2[f.i]);
     const uint32_t ch1 = (uint32_t)f2bf(sg * (255.0f / 50.0f)) << 16;
+    const int tid = fresh(threadIdx.x);
 #pragma unroll
     for (int u = 0; u < kX0PerThread; ++u) {
-      if (xq_r[u] < 0) continue;
-      const int q = threadIdx.x + u * kFusedThreads;
+      const int q = tid + u * kFusedThreads, r = (q * 1725) >> 16;
       // out-of-image positions were fetched as 0; their x0 must be 0 in both channels
-      const int yy = f.ty0 - 3 + xq_r[u], xx = f.tx0 - 3 + xq_c[u];
-      const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W;
-      x0s[q] = in ? ((uint32_t)f2bf(fabsf(xr[u]) * inv) | ch1) : 0u;
-      if (xq_cs[u] >= 0) cs[buf * FTH * FTW + xq_cs[u]] = xr[u];
+      const int yy = f.ty0 - 3 + r, xx = f.tx0 - 3 + q - r * X0W;
+      const bool in = (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W;
+      if (q < NX0) x0s[q] = in ? ((uint32_t)f2bf(fabsf(xr[u]) * inv) | ch1) : 0u;
     }
   };
 
-  // layer-1 operand: dword h of a lane's K slice is the (channel 0, channel 1)
-  // pair of tap t = 4 g + h (k = 8 g + 2 h + channel).  Slots of taps >= 9
-  // have zero weights; they read tap 0 (a staged, finite value) instead.
-  int toff[4];
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int t = 4 * g + h;
-    toff[h] = t < 9 ? (t / 3) * X0W + t % 3 : 0;
-  }
-
-  // weights of the current scale (reloaded when the scale changes); the
-  // biases become the accumulators' initial values
-  bf16x8 w1[2], w2[9][2], w3;
-  f32x4 bias1[2], bias2[2];
+  // operands of the current scale (reloaded when the scale changes); the
+  // biases are the accumulators' initial values
+  bf16x8 w1[2], w2[9];
+  s16x4 w3;
+  f32x4 bias1[2], bias2;
   float b3 = 0.f;
-  int cur_j = -1;
   auto load_weights = [&](int j) {
     const float *P = params + (size_t)j * kCnnParams;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      w1[nb] = *(const bf16x8 *)(W1k + (((size_t)j * 2 + nb) * 64 + lane) * 8);
+    for (int b = 0; b < 2; ++b) {
+      w1[b] = *(const bf16x8 *)(W1k + (((size_t)j * 2 + b) * 64 + lane) * 8);
 #pragma unroll
-      for (int t = 0; t < 9; ++t)
-        w2[t][nb] = *(const bf16x8 *)(W2p + ((((size_t)j * 9 + t) * 2 + nb) * 64 + lane) * 8);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int ch = 16 * nb + 4 * g + q;
-        bias1[nb][q] = P[kOffB1 + ch];
-        bias2[nb][q] = P[kOffB2 + ch];
-      }
+      for (int e = 0; e < 4; ++e) bias1[b][e] = P[kOffB1 + 16 * b + 4 * g0 + e];
     }
-    w3 = *(const bf16x8 *)(W3m + ((size_t)j * 64 + lane) * 8);
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+      w2[t] = *(const bf16x8 *)(W2p + ((((size_t)j * 9 + t) * 2 + nb) * 64 + lane) * 8);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      bias2[e] = P[kOffB2 + 16 * nb + 4 * g0 + e];
+      // layer 3, taps on M, this wave's 16 channels on K: row n, k = 4 g + e
+      w3[e] = n0 < 9 ? (short)f2bf(P[kOffW3 + (16 * nb + 4 * g0 + e) * 9 + n0]) : (short)0;
+    }
     b3 = P[kOffB3];
   };
-
-  // the three layers and the output of tile f; INTERIOR: the x0 region lies
-  // inside the image, so no activation needs the zero padding mask
-  auto layers = [&](const FusedTile &f, int buf, auto interior) {
-    constexpr bool INTERIOR = decltype(interior)::value != 0;
-    // ---- layer 1: NH1 pixels in blocks of 16; wave w takes blocks w, w + NW,
-    // ..., three at a time (independent products and operand reads; 16.6 ->
-    // 16.4 ms per 32 images against two at a time)
-    auto l1 = [&](int bA, auto count) {
-      constexpr int S = decltype(count)::value;
-      bf16x8 xb[S];
-      int qq[S];
+  // relu and layer 3 of 16 pixels at d3 index q of lane n
+  auto layer3 = [&](f32x4 a, uint32_t in, int q, int g) {
+    const uint2 h = relu_pack(a, in);
+    const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w3, *(const s16x4 *)&h,
+                                                              f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    float *dp = d3 + (9 * nb + 4 * g) * NH2 + q;
+    if (g < 3) dp[0] = d[0];
+    if (g < 2) {
 #pragma unroll
-      for (int s2 = 0; s2 < S; ++s2) {
-        const int q = (bA + NW * s2) * 16 + (lane & 15);
-        qq[s2] = q;
-        const int base = (q / H1W) * X0W + q % H1W;
-        uint32_t u[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) u[h] = x0s[base + toff[h]];
-        xb[s2] = *(const bf16x8 *)u;
-      }
-      __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-      for (int s2 = 0; s2 < S; ++s2) {
-        const int q = qq[s2];
-        bool in = true;
-        if constexpr (!INTERIOR) {
-          const int r = q / H1W, c = q % H1W;
-          const int yy = f.ty0 - 2 + r, xx = f.tx0 - 2 + c;
-          in = yy >= 0 && yy < H && xx >= 0 && xx < W;
-        }
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[nb], xb[s2], bias1[nb], 0, 0, 0);
-          *(bf16x4 *)(h1s + q * CHP + 16 * nb + 4 * g) = relu_bf16x4<INTERIOR>(d, in);
-        }
-      }
-      __builtin_amdgcn_s_setprio(0);
-    };
-    constexpr int NB1 = NH1 / 16;
-    for (int bA = wave; bA < NB1; bA += 3 * NW) {
-      if (bA + 2 * NW < NB1) l1(bA, IntC<3>{});
-      else if (bA + NW < NB1) l1(bA, IntC<2>{});
-      else l1(bA, IntC<1>{});
-    }
-    __syncthreads();
-    // ---- layer 2: NH2 pixels in NB2 blocks of 16 (the last may be partial).
-    // Wave w of NW takes blocks w, w + NW, w + 2 NW, ..., three at a time (six
-    // independent accumulators, the next tap's operands in flight; 240 VGPRs,
-    // still two waves per SIMD; 16.7 -> 16.5 ms per 32 images against two at
-    // a time)
-    constexpr int NB2 = (NH2 + 15) / 16;
-    auto l2 = [&](int bA, auto count) {
-      constexpr int S = decltype(count)::value;
-      int qq[S], base[S];
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int q = (bA + NW * s) * 16 + (lane & 15);
-        qq[s] = q;
-        const int qc = q < NH2 ? q : NH2 - 1;   // duplicate a valid pixel; not stored
-        base[s] = (qc / H2W) * H1W + qc % H2W;
-      }
-      f32x4 acc[S][2];
-#pragma unroll
-      for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[s][nb] = bias2[nb];
-      const uint16_t *hp = h1s + 8 * g;
-      bf16x8 xa[S];
-#pragma unroll
-      for (int s = 0; s < S; ++s) xa[s] = *(const bf16x8 *)(hp + base[s] * CHP);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        bf16x8 xn[S];
-        if (t < 8) {
-          const int off = ((t + 1) / 3) * H1W + (t + 1) % 3;
-#pragma unroll
-          for (int s = 0; s < S; ++s) xn[s] = *(const bf16x8 *)(hp + (base[s] + off) * CHP);
-        }
-        // a wave raises its issue priority while it issues its products, which
-        // keeps the matrix pipe fed while the other wave of the SIMD issues its
-        // LDS reads in the gaps (layers 1 and 2: 17.2 -> 16.8 ms per 32
-        // images, bitwise-equal outputs)
-        __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[s][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[t][nb], xa[s], acc[s][nb], 0, 0, 0);
-        __builtin_amdgcn_s_setprio(0);
-        if (t < 8) {
-#pragma unroll
-          for (int s = 0; s < S; ++s) xa[s] = xn[s];
-        }
-      }
-      // layer 3 on the h2 values of these pixels: lane group g holds channels
-      // 4 g .. 4 g + 3 and 16 + 4 g .. 16 + 4 g + 3 of its pixel, the K order
-      // of the packed layer-3 weights; D[t][q] for the 16 taps (9 used)
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int q = qq[s];
-        bool in = true;
-        if constexpr (!INTERIOR) {
-          const int qc = q < NH2 ? q : NH2 - 1;
-          const int r = qc / H2W, c = qc % H2W;
-          const int yy = f.ty0 - 1 + r, xx = f.tx0 - 1 + c;
-          in = yy >= 0 && yy < H && xx >= 0 && xx < W;
-        }
-        const bf16x4 lo = relu_bf16x4<INTERIOR>(acc[s][0], in);
-        const bf16x4 hi = relu_bf16x4<INTERIOR>(acc[s][1], in);
-        const bf16x8 hb = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3, hb, f32x4{0.f, 0.f, 0.f, 0.f},
-                                                                0, 0, 0);
-        if (q < NH2) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) d3[(4 * g + e) * NH2 + q] = d[e];
-        }
-      }
-    };
-    for (int bA = wave; bA < NB2; bA += 3 * NW) {
-      if (bA + 2 * NW < NB2) l2(bA, IntC<3>{});
-      else if (bA + NW < NB2) l2(bA, IntC<2>{});
-      else l2(bA, IntC<1>{});
-    }
-    __syncthreads();
-    // ---- output: one pixel per thread
-    const int r = threadIdx.x / FTW, c = threadIdx.x % FTW;
-    float z = b3;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) z += d3[t * NH2 + (r + t / 3) * H2W + c + t % 3];
-    const int yy = f.ty0 + r, xx = f.tx0 + c;
-    if (INTERIOR || (yy < H && xx < W)) {
-      const float gv = 1.0f / (1.0f + __expf(-z));
-      const size_t co = ((size_t)f.b * pl.R + f.i) * HWn + (size_t)yy * W + xx;
-      if (gain) gain[co] = gv;
-      coef_out[co] = gv * cs[buf * FTH * FTW + threadIdx.x];
+      for (int e = 1; e < 4; ++e) dp[e * NH2] = d[e];
     }
   };
 
   int tile = blockIdx.x;
   if (tile >= ntiles) return;
+  int cur_j = -1;
   FusedTile f = fused_tile(pl, tile, tiles_x, tiles_per_plane);
   fetch(f);
-  stage(f, 0);
-  int buf = 0;
-  __syncthreads();
+  stage(f);
+  float cc = cen;
   for (;;) {
     if (f.j != cur_j) {
       load_weights(f.j);
       cur_j = f.j;
     }
-    // prefetch the next tile's coefficients; they land during the layers
+    const bool interior = f.ty0 >= 3 && f.ty0 + FTH + 3 <= H && f.tx0 >= 3 && f.tx0 + FTW + 3 <= W;
+    __syncthreads();
+    // ---- layer 1 (36 blocks of 16 pixels, three and two at a time; waves
+    // without a fifth block repeat block 35) ----
+    {
+      const int n = fresh(n0), g = fresh(g0);
+      // dword h of a lane's K slice is the (channel 0, channel 1) pair of tap
+      // 4 g + h; the slots of taps >= 9 have zero weights and read tap 0
+      int toff[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const int t = 4 * g + h, dy = (t * 11) >> 5;               // t / 3
+        toff[h] = t < 9 ? dy * X0W + t - 3 * dy : 0;
+      }
+      auto l1 = [&](int b0, auto count) {
+        constexpr int S = decltype(count)::value;
+        bf16x8 xb[S];
+        int o[S];
+        uint32_t in[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int q = min(b0 + kFusedWaves * s, NH1 / 16 - 1) * 16 + n;
+          const int r = (q * 1821) >> 16, c = q - r * H1W;         // q / 36
+          const int base = q + 2 * r;                              // r X0W + c
+          uint32_t u[4];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) u[h] = x0s[base + toff[h]];
+          xb[s] = *(const bf16x8 *)u;
+          o[s] = q * kPix + (swz(c, g >> 1) | (g & 1) * 8);
+          in[s] = 0xFFFFFFFFu;
+          if (!interior) {
+            const int yy = f.ty0 - 2 + r, xx = f.tx0 - 2 + c;
+            in[s] = ((unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W) ? 0xFFFFFFFFu : 0u;
+          }
+        }
+        f32x4 d[S][2];
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) d[s][b] = mma(w1[b], xb[s], bias1[b]);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          *(uint2 *)(smem + o[s]) = relu_pack(d[s][0], in[s]);
+          *(uint2 *)(smem + (o[s] ^ 32)) = relu_pack(d[s][1], in[s]);
+        }
+      };
+      static_assert((NH1 / 16 + kFusedWaves - 1) / kFusedWaves == 5, "layer-1 blocks per wave");
+      l1(wave, IntC<3>{});
+      l1(wave + 3 * kFusedWaves, IntC<2>{});
+    }
+    // the next tile's coefficients land during layer 2
     const int next = tile + gridDim.x;
     FusedTile fn = f;
     if (next < ntiles) {
       fn = fused_tile(pl, next, tiles_x, tiles_per_plane);
       fetch(fn);
     }
-    const bool interior = f.ty0 >= 3 && f.ty0 + FTH + 3 <= H && f.tx0 >= 3 && f.tx0 + FTW + 3 <= W;
-    if (interior) layers(f, buf, IntC<1>{});
-    else layers(f, buf, IntC<0>{});
+    __syncthreads();
+    // ---- layers 2 and 3: columns 0..31 in two strips of two halves of 7
+    // rows; columns 32, 33 in two blocks of 16 (8 rows) ----
+    {
+      constexpr int RH = H2H / 2;
+      const int n = fresh(n0), g = fresh(g0);
+      const int r0 = RH * half, c = 16 * strip + n;
+      int ad[3];
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) ad[dx] = (r0 * H1W + c + dx) * kPix + swz(c + dx, g);
+      const bool cin = (unsigned)(f.tx0 - 1 + c) < (unsigned)W;
+      f32x4 acc[3];
+      bf16x8 fr[2][3];
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) fr[0][dx] = *(const bf16x8 *)(smem + ad[dx]);
+#pragma unroll
+      for (int y = 0; y < RH + 2; ++y) {
+        if (y + 1 < RH + 2) {
+#pragma unroll
+          for (int dx = 0; dx < 3; ++dx)
+            fr[(y + 1) & 1][dx] = *(const bf16x8 *)(smem + ad[dx] + (y + 1) * H1W * kPix);
+        }
+        if (y < RH) acc[y % 3] = bias2;
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+          for (int dy = 2; dy >= 0; --dy) {
+            const int r = y - dy;
+            if (r >= 0 && r < RH) acc[r % 3] = mma(w2[3 * dy + dx], fr[y & 1][dx], acc[r % 3]);
+          }
+        __builtin_amdgcn_s_setprio(0);
+        if (y >= 2) {
+          const int yy = f.ty0 - 1 + r0 + y - 2;
+          const uint32_t in = (cin && (unsigned)yy < (unsigned)H) ? 0xFFFFFFFFu : 0u;
+          layer3(acc[(y - 2) % 3], in, (r0 + y - 2) * H2W + c, g);
+        }
+      }
+      if (wave < 4) {
+        const int lc = min((wave >> 1) * 16 + n, 2 * H2H - 1);
+        const int r = lc >> 1, cl = 32 + (lc & 1);
+        f32x4 a = bias2;
+        int o[3];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) o[dx] = (r * H1W + cl + dx) * kPix + swz(cl + dx, g);
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+          a = mma(w2[k], *(const bf16x8 *)(smem + o[k % 3] + (k / 3) * H1W * kPix), a);
+        const int yy = f.ty0 - 1 + r, xx = f.tx0 - 1 + cl;
+        const uint32_t in = ((unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W) ? 0xFFFFFFFFu : 0u;
+        // (lanes past the last pixel repeat it)
+        layer3(a, in, r * H2W + cl, g);
+      }
+    }
+    __syncthreads();
+    // ---- output: one pixel per thread; then the next tile's x0 ----
+    {
+      const int tid = fresh(threadIdx.x), r = tid >> 5, c = tid & 31;
+      const int yy = f.ty0 + r, xx = f.tx0 + c;
+      if (r < FTH && yy < H && xx < W) {
+        float z = b3;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const float *dp = d3 + t * NH2 + (r + t / 3) * H2W + c + t % 3;
+          z += dp[0] + dp[9 * NH2];
+        }
+        const float gv = 1.0f / (1.0f + __expf(-z));
+        const size_t co = ((size_t)f.b * pl.R + f.i) * HWn + (size_t)yy * W + xx;
+        if (gain) gain[co] = gv;
+        coef_out[co] = gv * cc;
+      }
+    }
     if (next >= ntiles) break;
-    // x0 was last read by layer 1 and the other centre buffer by the previous
-    // tile's output: stage the next tile
-    buf ^= 1;
-    stage(fn, buf);
+    stage(fn);
+    cc = cen;
     tile = next;
     f = fn;
-    __syncthreads();
   }
 }
 
@@ -579,15 +525,14 @@ hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float 
 }
 
 hipError_t cnn_fused(const float *coef, const CnnPlanes &pl, int P, int H, int W,
-                     const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W3m,
-                     const float *params, float *coef_out, float *gain, int nblocks,
-                     hipStream_t st) {
+                     const uint16_t *W1k, const uint16_t *W2p, const float *params,
+                     float *coef_out, float *gain, int nblocks, hipStream_t st) {
   const int ntiles = P * ((W + FTW - 1) / FTW) * ((H + FTH - 1) / FTH);
   nblocks *= kFusedBlocksPerCU;
   const int grid = nblocks < ntiles ? nblocks : ntiles;
   if (grid < 1) return hipSuccess;
   hipLaunchKernelGGL(k_cnn_fused, dim3(grid), dim3(kFusedThreads), 0, st, coef, pl, H, W, ntiles,
-                     W1k, W2p, W3m, params, coef_out, gain);
+                     W1k, W2p, params, coef_out, gain);
   return hipGetLastError();
 }
 

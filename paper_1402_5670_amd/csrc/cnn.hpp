@@ -44,12 +44,11 @@ hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float 
                     int bias_stride, const CnnPlanes &pl, int P, int H, int W, int mode,
                     uint16_t *out, const float *coef, float *coef_out, float *gain,
                     hipStream_t st);
-// fused inference over P planes; a persistent grid (one or two blocks per
-// compute unit, by LDS size; nblocks = compute units) walks the output tiles
+// fused inference over P planes; a persistent grid (two blocks per
+// compute unit; nblocks = compute units) walks the output tiles
 hipError_t cnn_fused(const float *coef, const CnnPlanes &pl, int P, int H, int W,
-                     const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W3m,
-                     const float *params, float *coef_out, float *gain, int nblocks,
-                     hipStream_t st);
+                     const uint16_t *W1k, const uint16_t *W2p, const float *params,
+                     float *coef_out, float *gain, int nblocks, hipStream_t st);
 // Blocks of the fused backward kernel: scale j owns blocks
 // [first[j], first[j + 1]); cnn_bwd_blocks fills bk and returns their number
 // (one partial gradient of kCnnParams floats each).

@@ -170,7 +170,7 @@ int sl_cnn_apply(const sl_system *s, const float *params_dev, const void *packed
   sl::CnnPlanes pl0 = planes(s, batch, sigma_dev);
   if (!layerwise()) {
     CK(sl::cnn_copy_lowpass(coeffs_dev, coeffs_out_dev, batch, s->R, (int)s->cfg.npix(), st));
-    CK(sl::cnn_fused(coeffs_dev, pl0, P, H, W, pk.w1k, pk.w2, pk.w3m, params_dev, coeffs_out_dev,
+    CK(sl::cnn_fused(coeffs_dev, pl0, P, H, W, pk.w1k, pk.w2, params_dev, coeffs_out_dev,
                      gains_dev, s->num_cu, st));
     return SL_OK;
   }

@@ -18,14 +18,10 @@
 //
 // v_mfma_f32_16x16x32_bf16 (64 lanes, n = lane % 16, g = lane / 16):
 //   A[m][k]: m = n, k = 8 g + j;  B[k][n]: k = 8 g + j;  D[m][n]: m = 4 g + e.
-// Activations are pixel-major in LDS, 32 channels in 64 bytes; the 16-byte
-// chunk c of the pixel in column x sits at chunk c ^ s, s the bits of
-// (x / 4) % 4 swapped.  Convolutions read
+// Activations are pixel-major in LDS (cnn_device.hpp).  Convolutions read
 // 8 channels of one pixel per lane; the weight gradients, whose reduction
 // axis is the pixels, read 4 pixels of one channel per lane with the
-// transposing LDS read (ds_read_b64_tr_b16).  The chunk permutation serves
-// both: 16 consecutive pixels at one chunk, and 8 consecutive pixels at one
-// half of their chunks, touch every bank once.  Their 32 K slots are two
+// transposing LDS read (ds_read_b64_tr_b16).  Their 32 K slots are two
 // vertically adjacent 16-pixel blocks: slot 8 g + j is pixel 4 g + j % 4 of
 // row j / 4.
 //
@@ -47,15 +43,6 @@ namespace sl {
 
 namespace {
 
-template <int V>
-struct IntC {
-  static constexpr int value = V;
-};
-
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int BH = 16, BW = 32;                    // owned tile
@@ -64,7 +51,6 @@ constexpr int AH = BH + 8, AW = BW + 8;            // h1
 constexpr int EH = BH + 6, EW = BW + 6;            // h2
 constexpr int ZH = BH + 4, ZW = BW + 4;            // dz
 constexpr int DH = BH + 2, DW = BW + 2;            // da2
-constexpr int kPix = 64;                           // bytes per pixel (32 bf16)
 constexpr int kOH1 = 0;
 constexpr int kOH2 = kOH1 + AH * AW * kPix;
 constexpr int kODA = kOH2 + EH * EW * kPix;        // da2; before it, layer-3 partial sums
@@ -80,51 +66,10 @@ constexpr int kBwdThreads = 512, NWV = kBwdThreads / 64;
 constexpr int kXPer = (XH * XW + kBwdThreads - 1) / kBwdThreads;
 constexpr int kZPer = (ZH * ZW + kBwdThreads - 1) / kBwdThreads;
 
-// byte offset of 16-byte chunk c of column x within its pixel
-__device__ __forceinline__ int swz(int x, int c) {
-  return (c << 4) ^ (((x << 3) & 32) | ((x << 1) & 16));
-}
-
-// 4 values rounded to bfloat16 (round to nearest even)
-__device__ __forceinline__ uint2 pack4(f32x4 d) {
-  const bf16x2 a = __builtin_convertvector((f32x2){d[0], d[1]}, bf16x2);
-  const bf16x2 b = __builtin_convertvector((f32x2){d[2], d[3]}, bf16x2);
-  return make_uint2(*(const uint32_t *)&a, *(const uint32_t *)&b);
-}
-
-// relu of 4 values, rounded to bfloat16, ANDed with the in-image mask (a
-// maximum with 0 of the 16-bit patterns as signed integers: negative values
-// have the sign bit set)
-__device__ __forceinline__ uint2 relu_pack(f32x4 d, uint32_t in) {
-  uint2 u = pack4(d);
-  const s16x2 z = {0, 0};
-  const s16x2 a = __builtin_elementwise_max(*(const s16x2 *)&u.x, z);
-  const s16x2 b = __builtin_elementwise_max(*(const s16x2 *)&u.y, z);
-  return make_uint2(*(const uint32_t *)&a & in, *(const uint32_t *)&b & in);
-}
-
 // 16-bit halves of v kept where the halves of h (bfloat16) are not zero
 __device__ __forceinline__ uint32_t keep_nonzero(uint32_t v, uint32_t h) {
   const uint32_t m = ((h & 0x7FFF7FFFu) + 0x7FFF7FFFu) & 0x80008000u;
   return v & ((m - (m >> 15)) | m);
-}
-
-__device__ __forceinline__ bf16x8 frag(uint2 a, uint2 b) {
-  const uint4 u = make_uint4(a.x, a.y, b.x, b.y);
-  return *(const bf16x8 *)&u;
-}
-
-// The value of x, computed anew: addresses derived from it stay inside their
-// phase of the tile loop instead of being kept in registers across it (the
-// operands and accumulators that live through the loop leave no room: hoisted
-// addresses spilled 79 registers and doubled the time of a tile).
-__device__ __forceinline__ int fresh(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
-
-__device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 }  // namespace
