@@ -474,7 +474,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
           f32x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const uint16_t h = *(const uint16_t *)(smem + hm + (r * AW + e) * kPix);
+            const uint16_t h = *(const uint16_t *)(smem + (e < 2 ? hm : hm ^ 16) + (r * AW + e) * kPix);
             o[e] = h != 0 ? acc[r % 3][e] : 0.f;
           }
           const uint2 cur = pack4(o);

@@ -25,14 +25,13 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // Activations in LDS: 32 channels of a pixel in 64 bytes, 16-byte chunk c of
-// the pixel in column x at chunk c ^ s, s the bits of (x / 4) % 4 swapped.  16
-// consecutive pixels at one chunk, and 8 consecutive pixels at one half of
-// their chunks, then touch every bank once.
+// the pixel in column x at chunk c ^ ((x / 2) % 4).  By the bank-conflict
+// counter, 16-byte reads of 16 consecutive pixels and the transposing reads of
+// 8-byte pieces are then free of conflicts (without the permutation, or with
+// (x / 4) % 4, the former take twice the cycles).
 constexpr int kPix = 64;
 // byte offset of 16-byte chunk c of column x within its pixel
-__device__ __forceinline__ int swz(int x, int c) {
-  return (c << 4) ^ (((x << 3) & 32) | ((x << 1) & 16));
-}
+__device__ __forceinline__ int swz(int x, int c) { return (c << 4) ^ ((x << 3) & 48); }
 
 // 4 values rounded to bfloat16 (round to nearest even)
 __device__ __forceinline__ uint2 pack4(f32x4 d) {
