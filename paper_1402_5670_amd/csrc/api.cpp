@@ -215,12 +215,16 @@ enum Pass {
   P_ROWS_THR,
   P_XCD_FWD,
   P_XCD_INV,
+  P_PLANE_FWD,
+  P_PLANE_INV,
+  P_PLANE_THR,
   P_COUNT
 };
 const char *kPassNames[P_COUNT] = {"rows_real_fft",   "cols_fft",      "cols_filter_ifft",
                                    "rows_coef",       "rows_coef_fft", "cols_fft_acc",
                                    "rows_real_ifft",  "aux",           "rows_thr",
-                                   "xcd_fwd",         "xcd_inv"};
+                                   "xcd_fwd",         "xcd_inv",       "plane_fwd",
+                                   "plane_inv",       "plane_thr"};
 
 struct Timing {
   bool on = false;
@@ -378,6 +382,12 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
     return SL_OK;
   }
   const sl::Sys2D v = view2d(s);
+  if (sl::plane2_supported(v.H, v.W)) {
+    const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
+    SL_LAUNCH(P_PLANE_THR, st,
+              sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, T, G, batch, st));
+    return SL_OK;
+  }
   const int G = inv_groups(s, batch);
   float2 *part = (float2 *)(ws + L.off_part);
   if (mix)
@@ -1048,6 +1058,11 @@ static int forward_impl(const sl_system *s, const float *x_dev, int batch, void 
                                  s->xcd_err_dev, batch, s->xcd_spin, st));
     return SL_OK;
   }
+  if (sl::plane2_supported(v.H, v.W)) {
+    SL_LAUNCH(P_PLANE_FWD, st,
+              sl::launch_plane2_fwd(v, x_dev, coeffs_dev, scales_dev, batch, dual, st));
+    return SL_OK;
+  }
   if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_zero_u32(xmax, batch, st));
   SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(v, x_dev, F, scaled ? xmax : nullptr, batch, st));
   SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(v, F, F, batch, false, st));
@@ -1109,6 +1124,13 @@ int sl_inverse(const sl_system *s, const void *coeffs_dev, const float *scales_d
   }
   int nb, np;
   chunk_plan(s, batch, nb, np);
+  if (sl::plane2_supported(v.H, v.W)) {
+    // partial sums take the chunk's pair planes
+    const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
+    SL_LAUNCH(P_PLANE_INV, st,
+              sl::launch_plane2_inv(v, coeffs_dev, scales_dev, thr, x_dev, U, G, batch, st));
+    return SL_OK;
+  }
   const int P = (s->R + 1) / 2;
   const int G = inv_groups(s, batch);
   float2 *part = (float2 *)(ws + L.off_part);

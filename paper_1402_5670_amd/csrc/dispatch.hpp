@@ -98,6 +98,32 @@ hipError_t launch_cols_acc_finish(const Sys2D &s, float2 *ACC, const float2 *par
 // ACC -> x (row inverse DFT, real part, 1/(HW))
 hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, float *x, int B, hipStream_t st);
 
+// ---- whole-plane passes of small images (plane2d.hip) -------------------------
+struct Plane2Args {
+  int R;
+  bool dual;               // forward with the dual filters psi_hat / Psi_hat
+  const float *filt, *psi, *l1;
+  const float2 *twH, *twW;
+  float inv_hw;
+  float *out;              // [B][H][W]
+  float2 *part;            // partial sums [B][G][H][W] (G > 1 groups)
+};
+bool plane2_supported(int H, int W);
+// pair groups of the inverse and the denoiser, with part_planes planes of
+// scratch for their partial sums (1 = none needed)
+int plane2_inv_groups(const Sys2D &s, int B, size_t part_planes);
+// x -> coefficients and, for F16 / BF16 storage, scales
+hipError_t launch_plane2_fwd(const Sys2D &s, const float *x, void *coef, float *scales, int B,
+                             bool dual, hipStream_t st);
+// coefficients (hard threshold on load if thr.sigma) -> x
+hipError_t launch_plane2_inv(const Sys2D &s, const void *coef, const float *scales,
+                             const ThrArgs &thr, float *x, float2 *part, int G, int B,
+                             hipStream_t st);
+// x (or the inpainting input of mix) -> denoised out, without coefficients
+hipError_t launch_plane2_thr(const Sys2D &s, const float *x, const MixArgs *mix,
+                             const ThrArgs &thr, float *out, float2 *part, int G, int B,
+                             hipStream_t st);
+
 // ---- multi-class coefficient row passes (uneven batches) ---------------------
 // One launch runs the coefficient row pass of several size classes: the
 // forward's row IDFT and coefficient store (T -> coef, as launch_rows_coef)

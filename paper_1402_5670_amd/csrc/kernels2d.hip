@@ -16,12 +16,11 @@
 // Each block owns M lines of one image; the FFT of a line runs in registers
 // with LDS exchanges between radix stages (fft_core.hpp).  Row passes read
 // and write whole rows; column passes move M adjacent columns per row.
-#include <hip/hip_bf16.h>
-#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
 #include "dispatch.hpp"
 #include "fft_core.hpp"
+#include "tiles.hpp"
 
 namespace sl {
 
@@ -29,9 +28,6 @@ namespace sl {
 // with SL_COL_EMUL > 1 each thread of a column pass owns SL_COL_EMUL times
 // more values, halving the threads per column and doubling the columns per
 // block (wider coalesced segments) for lengths 256..512.
-#ifndef SL_COL_EMUL
-#define SL_COL_EMUL 1
-#endif
 // EM (line plan): each thread holds EM times the plan's values, so a line
 // takes EM times fewer threads (EM = 2 makes a 1024-point row one wavefront,
 // whose radix exchanges need no block barrier); the coefficient row passes
@@ -55,75 +51,6 @@ __device__ __forceinline__ void row_fft(float2 (&v)[(Tile<N, EM>::E)], int t, co
 // line plans with EM = 2 exist for these lengths
 template <int N>
 constexpr bool em2_length() { return N == 1024; }
-template <int N>
-struct CTile {
-  static constexpr int EM = (N >= 256 && N <= 512) ? SL_COL_EMUL : 1;
-  using PL = Plan<N, EM>;
-  static constexpr int NT = PL::NT;
-  static constexpr int E = PL::E;
-  static constexpr int M = (NT * 16 <= 1024 ? 16 : 8) * (EM > 1 ? 2 : 1);
-  static constexpr int THREADS = M * NT;
-};
-
-// ---------------------------------------------------------------------------
-// storage encode / decode
-// ---------------------------------------------------------------------------
-template <int DT>
-struct Store;
-// T is the element type of the coefficient tensor; Raw its bit pattern as a
-// plain scalar (kernels load and store Raw values, so that all loads of a row
-// can be issued before the first conversion).
-template <>
-struct Store<0> {
-  using T = float;
-  using Raw = float;
-  __device__ static T enc(float v) { return v; }
-  __device__ static float dec(T v) { return v; }
-  __device__ static Raw enc_raw(float v) { return v; }
-  __device__ static float dec_raw(Raw v) { return v; }
-};
-template <>
-struct Store<1> {
-  using T = __half;
-  using Raw = unsigned short;
-  __device__ static T enc(float v) { return __float2half_rn(v); }
-  __device__ static float dec(T v) { return __half2float(v); }
-  __device__ static Raw enc_raw(float v) { return __half_as_ushort(__float2half_rn(v)); }
-  __device__ static float dec_raw(Raw v) { return __half2float(__ushort_as_half(v)); }
-};
-template <>
-struct Store<2> {
-  using T = __hip_bfloat16;
-  using Raw = unsigned short;
-  __device__ static T enc(float v) { return __float2bfloat16(v); }
-  __device__ static float dec(T v) { return __bfloat162float(v); }
-  __device__ static Raw enc_raw(float v) { return __bfloat16_as_ushort(__float2bfloat16(v)); }
-  __device__ static float dec_raw(Raw v) { return __uint_as_float((unsigned)v << 16); }
-};
-
-// Coefficient planes are streamed once per call; with SL_NT_COEF the float32
-// coefficient stores and loads carry the non-temporal hint so that they do
-// not displace the pass intermediates from the caches.
-#ifndef SL_NT_COEF
-#define SL_NT_COEF 0
-#endif
-template <class T>
-__device__ __forceinline__ void coef_store(T *p, T v) {
-  if constexpr (SL_NT_COEF && sizeof(T) == 4) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-template <class T>
-__device__ __forceinline__ T coef_load(const T *p) {
-  if constexpr (SL_NT_COEF && sizeof(T) == 4) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------

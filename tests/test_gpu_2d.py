@@ -345,3 +345,47 @@ def test_error_paths():
         B.check(B.lib().sl_forward(f16._h, B._ptr(x), 2, B._ptr(c), None,
                                    B._ptr(f16.workspace(2, DEV)), f16.workspace_bytes(2), None))
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("dims,J,levels,Bn,dtype", [
+    ((32, 32), 2, [1, 1], 1, "f32"), ((64, 48), 2, [1, 1], 5, "f16"), ((48, 64), 3, [0, 1, 1], 2, "bf16"),
+    ((64, 64), 3, [1, 1, 2], 3, "f32"), ((32, 32), 2, [1, 1], 1000, "f32")])
+def test_whole_plane_passes(dims, J, levels, Bn, dtype):
+    """Planes that one block transforms in LDS: one pair per block up to all
+    pairs of an image in one block (the batch of 1000, which also finishes
+    without partial sums).  Coefficients, reconstruction, thresholded
+    reconstruction on an exact mask and the fused denoiser; tolerances of the
+    precision policy (1e-5, 2e-3 for 16-bit storage, whose reconstruction of
+    the stored values is float32 arithmetic again)."""
+    print(f"case: whole planes {dims} B={Bn} {dtype}", flush=True)
+    o = S.build_2d(dims, J, levels)
+    sysg = B.System(dims, J, levels, dtype=dtype)
+    rng = np.random.default_rng(11)
+    x = rng.random((Bn, *dims)).astype(np.float32)
+    sg = np.full(Bn, 0.1, dtype=np.float32)
+    K = [2.0] * J
+    xg = _gpu(x)
+    c, sc = sysg.forward(xg)
+    xr = sysg.inverse(c, sc)
+    xt = sysg.inverse(c, sc, sigma=_gpu(sg), K=K)
+    xd = sysg.denoise_fused(xg, _gpu(sg), K)
+    torch.cuda.synchronize()
+    tol = 1e-5 if dtype == "f32" else 2e-3
+    for b in sorted({0, Bn // 2, Bn - 1}):
+        cg = _decode(c[b:b + 1], sc[b:b + 1] if dtype != "f32" else None)[0]
+        assert rel(cg, T.forward(x[b].astype(np.float64), o.filters)) < tol
+        assert rel(xr[b].cpu().numpy(), T.inverse(cg, o.filters, o.dual_weight)) < 1e-5
+        l2 = np.array([s[4] for s in sysg.subbands], dtype=np.float32)
+        ct = cg.copy()
+        for i in range(1, sysg.R):
+            d = np.float32(np.float32(K[sysg.subbands[i][1]]) * sg[b]) * l2[i]
+            ct[i] *= np.abs(cg[i].astype(np.float32)) >= d
+        want = T.inverse(ct, o.filters, o.dual_weight)
+        assert rel(xt[b].cpu().numpy(), want) < 1e-5
+        if dtype == "f32":      # the denoiser thresholds the same float32 coefficients
+            assert rel(xd[b].cpu().numpy(), want) < 1e-5
+    if dtype == "f32":
+        r = rng.standard_normal((Bn, *dims))
+        a = sysg.inverse_adjoint(_gpu(r)).cpu().numpy()
+        R0 = np.fft.fft2(r[0].astype(np.float32)) / o.dual_weight
+        assert rel(a[0], np.fft.ifft2(R0 * o.filters).real) < 1e-5
