@@ -338,6 +338,23 @@ int inverse3d(const sl_system *s, const void *coef, const float *scales, int bat
 }
 
 
+// Whether the 2D passes take a plane whole in LDS (small images).
+bool whole_planes(const sl_system *s) {
+  return s->cfg.ndim == 2 && sl::plane2_supported((int)s->cfg.dims[0], (int)s->cfg.dims[1]);
+}
+
+// Inverse of small images; partial sums take the chunk's pair planes.
+int inverse_whole_planes(const sl_system *s, const void *coef, const float *scales,
+                         const sl::ThrArgs &thr, int batch, float *x, char *ws, hipStream_t st) {
+  const sl::Sys2D v = view2d(s);
+  int nb, np;
+  chunk_plan(s, batch, nb, np);
+  const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
+  float2 *part = (float2 *)(ws + layout(s, batch).off_chunk);
+  SL_LAUNCH(P_PLANE_INV, st, sl::launch_plane2_inv(v, coef, scales, thr, x, part, G, batch, st));
+  return SL_OK;
+}
+
 // Forward transform, hard threshold and inverse transform without
 // materialising the coefficients (the body of sl_denoise_fused and of every
 // inpainting iteration).  Arguments are validated by the callers.
@@ -382,7 +399,7 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
     return SL_OK;
   }
   const sl::Sys2D v = view2d(s);
-  if (sl::plane2_supported(v.H, v.W)) {
+  if (whole_planes(s)) {
     const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
     SL_LAUNCH(P_PLANE_THR, st,
               sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, T, G, batch, st));
@@ -532,6 +549,17 @@ sl::ThrArgs unit_thresholds(const sl_system *s, const float *sigma) {
   return thr;
 }
 
+// hard thresholds of one class of an uneven batch (none without sigma)
+sl::ThrArgs multi_thresholds(const sl::MultiClass2D &c, const float *K) {
+  sl::ThrArgs thr{};
+  thr.sigma = c.sigma;
+  thr.l2 = c.s->d_l2;
+  thr.jof = c.s->d_jof;
+  if (c.sigma)
+    for (int j = 0; j < c.s->cfg.J; ++j) thr.K[j] = K[j];
+  return thr;
+}
+
 uint64_t bits_of(double v) {
   uint64_t b;
   std::memcpy(&b, &v, sizeof(b));
@@ -558,6 +586,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
     const MultiClass2D &c = cls[i];
     int rc = check_call(c.s, c.B, c.x ? (const void *)c.x : c.coef, c.coef, c.ws, c.ws_bytes);
     if (rc) return rc;
+    if (whole_planes(c.s)) continue;   // one pass per direction, no chunks
     int nb, np;
     chunk_plan(c.s, c.B, nb, np);
     const int P = (c.s->R + 1) / 2;
@@ -578,6 +607,11 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
       const sl::Sys2D v = view2d(c.s);
       const bool scaled = dtype != SL_F32;
       if (scaled && !c.scales) return fail(SL_EINVAL, "scales are required for F16/BF16 storage");
+      if (whole_planes(c.s)) {
+        SL_LAUNCH(P_PLANE_FWD, st,
+                  sl::launch_plane2_fwd(v, c.x, c.coef, c.scales, c.B, false, st));
+        continue;
+      }
       if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_zero_u32(xmax, c.B, st));
       SL_LAUNCH(P_ROWS_REAL_FFT, st,
                 sl::launch_rows_real_fft(v, c.x, F, scaled ? xmax : nullptr, c.B, st));
@@ -600,12 +634,24 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
         mc.coef = c.coef;
         mc.scales = c.scales;
       }
-      SL_LAUNCH(P_ROWS_COEF, st, sl::launch_rows_multi(mr, dtype, true, st));
+      if (mr.n) SL_LAUNCH(P_ROWS_COEF, st, sl::launch_rows_multi(mr, dtype, true, st));
     }
   }
   if (what & 2) {
+    for (int i = 0; i < n; ++i) {
+      if (!cls[i].sigma) continue;
+      if (!K) return fail(SL_EINVAL, "K is required with sigma");
+      if (cls[i].s->cfg.J > sl::kMaxScales) return fail(SL_EUNSUPPORTED, "too many scales");
+    }
     std::vector<int> groups(n);
     for (int i = 0; i < n; ++i) groups[i] = inv_groups(cls[i].s, cls[i].B);
+    for (int i = 0; i < n; ++i) {
+      const MultiClass2D &c = cls[i];
+      if (!whole_planes(c.s)) continue;
+      int rc = inverse_whole_planes(c.s, c.coef, c.scales, multi_thresholds(c, K), c.B, c.out,
+                                    (char *)c.ws, st);
+      if (rc) return rc;
+    }
     for (size_t k = 0; k < steps; ++k) {
       sl::MultiRows mr{};
       for (int i = 0; i < n; ++i) {
@@ -618,16 +664,9 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
         mc.U = (float2 *)((char *)c.ws + L.off_chunk);
         mc.coef = c.coef;
         mc.scales = c.scales;
-        mc.thr.sigma = c.sigma;
-        mc.thr.l2 = c.s->d_l2;
-        mc.thr.jof = c.s->d_jof;
-        if (c.sigma) {
-          if (!K) return fail(SL_EINVAL, "K is required with sigma");
-          if (c.s->cfg.J > sl::kMaxScales) return fail(SL_EUNSUPPORTED, "too many scales");
-          for (int j = 0; j < c.s->cfg.J; ++j) mc.thr.K[j] = K[j];
-        }
+        mc.thr = multi_thresholds(c, K);
       }
-      SL_LAUNCH(P_ROWS_COEF_FFT, st, sl::launch_rows_multi(mr, dtype, false, st));
+      if (mr.n) SL_LAUNCH(P_ROWS_COEF_FFT, st, sl::launch_rows_multi(mr, dtype, false, st));
       for (int i = 0; i < n; ++i) {
         if (k >= chunks[i].size()) continue;
         const MultiClass2D &c = cls[i];
@@ -644,6 +683,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
     }
     for (int i = 0; i < n; ++i) {
       const MultiClass2D &c = cls[i];
+      if (whole_planes(c.s)) continue;
       const Layout L = layout(c.s, c.B);
       char *ws = (char *)c.ws;
       const sl::Sys2D v = view2d(c.s);
@@ -1058,7 +1098,7 @@ static int forward_impl(const sl_system *s, const float *x_dev, int batch, void 
                                  s->xcd_err_dev, batch, s->xcd_spin, st));
     return SL_OK;
   }
-  if (sl::plane2_supported(v.H, v.W)) {
+  if (whole_planes(s)) {
     SL_LAUNCH(P_PLANE_FWD, st,
               sl::launch_plane2_fwd(v, x_dev, coeffs_dev, scales_dev, batch, dual, st));
     return SL_OK;
@@ -1124,13 +1164,8 @@ int sl_inverse(const sl_system *s, const void *coeffs_dev, const float *scales_d
   }
   int nb, np;
   chunk_plan(s, batch, nb, np);
-  if (sl::plane2_supported(v.H, v.W)) {
-    // partial sums take the chunk's pair planes
-    const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
-    SL_LAUNCH(P_PLANE_INV, st,
-              sl::launch_plane2_inv(v, coeffs_dev, scales_dev, thr, x_dev, U, G, batch, st));
-    return SL_OK;
-  }
+  if (whole_planes(s))
+    return inverse_whole_planes(s, coeffs_dev, scales_dev, thr, batch, x_dev, ws, st);
   const int P = (s->R + 1) / 2;
   const int G = inv_groups(s, batch);
   float2 *part = (float2 *)(ws + L.off_part);
