@@ -18,6 +18,8 @@
 // and write whole rows; column passes move M adjacent columns per row.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "dispatch.hpp"
 #include "fft_core.hpp"
 #include "tiles.hpp"
@@ -1687,6 +1689,41 @@ static int pair_groups(const Sys2D &s, int blocks, int np, int per_cu, int cap) 
   return (np + per - 1) / per;
 }
 
+// Blocks of a kernel resident on the device at once (0 if unknown); slot caches
+// the occupancy of the kernel instance.
+template <class Kernel>
+static long resident_blocks(Kernel k, int threads, int num_cu, std::atomic<int> &slot) {
+  int per = slot.load(std::memory_order_relaxed);
+  if (per < 0) {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, 0) != hipSuccess || n < 1) n = 1;
+    per = n;
+    slot.store(per, std::memory_order_relaxed);
+  }
+  return (long)per * num_cu;
+}
+
+// Parts to split a column pass's pair loop into when its grid has at least a
+// block per compute unit: blocks run their whole loop in one round, so a grid
+// that is not a multiple of the resident blocks leaves a partly idle last
+// round (6 x 1024^2: 384 blocks on 256, two rounds for one and a half).  The
+// split with the fewest rounds per unit of work wins; a further part has to
+// save 5%, since each re-reads its tile of the spectrum.
+static int round_split(long blocks, long resident, int np, int cap) {
+  int best = 1;
+  double best_cost = 1e30;
+  for (int sp = 1; sp <= cap && sp <= np; ++sp) {
+    const long per = (np + sp - 1) / sp;
+    if ((np + per - 1) / per != sp) continue;              // no empty part
+    const double cost = (double)((blocks * sp + resident - 1) / resident) * (double)per / np;
+    if (cost < 0.95 * best_cost) {
+      best_cost = cost;
+      best = sp;
+    }
+  }
+  return best;
+}
+
 // images per block of the inverse accumulation: the system's choice, else
 // two (one for a single image, which does not fill a two-image block)
 static int inv_bt(const Sys2D &s, int nb) {
@@ -1726,9 +1763,15 @@ static void launch_fwd3(const Sys2D &s, const float2 *F, float2 *T, Chunk c, hip
   // barriers (24 x 1024^2, R = 33: 1.71 -> 1.44 ms per forward column pass)
   constexpr int BT = (N == 1024 && MW == kFwdWide) ? 2 : kFwdBT;
   const int tiles = (s.W + FT::M - 1) / FT::M, ny = (c.nb + BT - 1) / BT;
-  hipLaunchKernelGGL((k_cols_filter_ifft3<N, BT, MW, EM>),
-                     dim3(tiles, ny, pair_groups(s, tiles * ny, c.np, 4, 32)), dim3(FT::THREADS),
-                     0, st, F, s.filt, T, s.W, s.R, c.b0, c.nb, c.p0, c.np, s.twH);
+  int groups = pair_groups(s, tiles * ny, c.np, 4, 32);
+  if (s.split_pairs && tiles * ny >= s.num_cu) {
+    static std::atomic<int> occ{-1};
+    groups = round_split((long)tiles * ny,
+                         resident_blocks(k_cols_filter_ifft3<N, BT, MW, EM>, FT::THREADS, s.num_cu, occ),
+                         c.np, 8);
+  }
+  hipLaunchKernelGGL((k_cols_filter_ifft3<N, BT, MW, EM>), dim3(tiles, ny, groups),
+                     dim3(FT::THREADS), 0, st, F, s.filt, T, s.W, s.R, c.b0, c.nb, c.p0, c.np, s.twH);
 }
 
 hipError_t launch_cols_filter_ifft(const Sys2D &s, const float2 *F, float2 *T, Chunk c,
