@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libshearlet.so")
 
-SOURCES = ["api.cpp", "host_filters.cpp", "kernels2d.hip", "plane2d.hip",
+SOURCES = ["api.cpp", "host_filters.cpp", "kernels2d.hip", "acc2d.hip", "plane2d.hip",
            "kernels3d.hip", "cnn.hip", "cnn_bwd.hip",
            "cnn_api.cpp", "render.hip", "multi_api.cpp", "inpaint.hip", "noalloc.hip",
            "xcd2d.hip"]

@@ -93,6 +93,11 @@ hipError_t launch_rows_thr(const Sys2D &s, float2 *T, float inv_n, Chunk c, cons
 int inv_pair_groups(const Sys2D &s, int nb, int np);
 hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
                                int Btot, Chunk c, bool first, bool last, hipStream_t st);
+// The same with tiles streamed to LDS, columns of 256, 512 or 1024 points
+// (acc2d.hip); launch_cols_fft_acc chooses.
+bool cols_acc_stream_supported(int H, int W);
+hipError_t launch_cols_acc_stream(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
+                               int Btot, Chunk c, int bt, bool first, bool last, hipStream_t st);
 hipError_t launch_cols_acc_finish(const Sys2D &s, float2 *ACC, const float2 *part, int G, int B,
                                   hipStream_t st);
 // ACC -> x (row inverse DFT, real part, 1/(HW))

@@ -1740,6 +1740,25 @@ static int inv_tile_m(const Sys2D &s, int nb) {
   return nb == 1 ? ITile<N, kInvNarrow>::M : ITile<N, kInvWide>::M;
 }
 
+// Whether the inverse accumulation takes the tile-streaming kernel (acc2d.hip),
+// and its blocks before the pair loop is split.  It wins where few blocks
+// leave the pass waiting for its loads (512 points: 1, 2, 4, 8 images 78.6 ->
+// 69.3, 127 -> 110, 201 -> 184, 326 -> 315 us per thresholded inverse; one
+// 1024^2 image denoised 356 -> 305 us; 4 and 16 images of 256^2 5% and 7%),
+// and not where the device is full (32 x 512^2 470 -> 490 us for the pass, its
+// row segments come at 4.3 TB/s even without the transforms; 6 x 1024^2 537 ->
+// 620 us; 16 of 256 x 512 2% slower) or a 256-point image is alone (2%).
+static int acc_stream_blocks(const Sys2D &s, int nb) {
+  const int bt = inv_bt(s, nb);
+  return s.W / (s.H == 1024 ? 8 : 16) * ((nb + bt - 1) / bt);
+}
+static bool acc_stream(const Sys2D &s, int nb) {
+  if (!cols_acc_stream_supported(s.H, s.W)) return false;
+  const int blocks = acc_stream_blocks(s, nb);
+  if (s.H == 256) return blocks >= 32 && blocks < s.num_cu;
+  return blocks < (s.H == 1024 ? s.num_cu / 2 + 1 : s.num_cu);
+}
+
 int inv_pair_groups(const Sys2D &s, int nb, int np) {
   if (SL_COL_V3_INV || !lines_supported(s.H)) return 1;
   int M = 0;
@@ -1751,6 +1770,8 @@ int inv_pair_groups(const Sys2D &s, int nb, int np) {
     SL_FOR_EACH_N(X)
 #undef X
   }
+  // (the streaming kernel runs one block per compute unit, two at 256 points)
+  if (acc_stream(s, nb)) return pair_groups(s, acc_stream_blocks(s, nb), np, s.H > 256 ? 1 : 2, 16);
   const int bt = inv_bt(s, nb);
   return pair_groups(s, ((s.W + M - 1) / M) * ((nb + bt - 1) / bt), np, 2, 16);
 }
@@ -1981,6 +2002,8 @@ static dim3 acc_grid(int W, int M, int groups, int G) {
 hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part,
                                int G, int Btot, Chunk c, bool first, bool last, hipStream_t st) {
   if (G < 1 || (G > 1 && (!part || SL_COL_V3_INV))) return hipErrorInvalidValue;
+  if (acc_stream(s, c.nb))
+    return launch_cols_acc_stream(s, U, ACC, part, G, Btot, c, inv_bt(s, c.nb), first, last, st);
   switch (s.H) {
 #define X(N)                                                                                    \
   case N:                                                                                       \

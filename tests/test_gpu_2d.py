@@ -389,3 +389,25 @@ def test_whole_plane_passes(dims, J, levels, Bn, dtype):
         a = sysg.inverse_adjoint(_gpu(r)).cpu().numpy()
         R0 = np.fft.fft2(r[0].astype(np.float32)) / o.dual_weight
         assert rel(a[0], np.fft.ifft2(R0 * o.filters).real) < 1e-5
+
+
+@pytest.mark.parametrize("dims,J,levels,Bn,chunk_mb", [
+    ((512, 16), 2, [1, 1], 1, None), ((512, 48), 2, [1, 1], 3, None), ((512, 64), 2, [1, 1], 2, 1),
+    ((1024, 8), 2, [1, 1], 1, None), ((1024, 24), 2, [1, 1], 3, None), ((256, 128), 2, [1, 1], 9, None),
+    ((256, 256), 2, [1, 1], 4, 8)])
+def test_streamed_accumulation(monkeypatch, dims, J, levels, Bn, chunk_mb):
+    """Inverse accumulation with tiles streamed to LDS: one tile, tile counts
+    off the multiple of 8 that groups them, an odd last image, and several
+    chunks (accumulators re-read).  Reconstruction of random coefficients
+    against the oracle, float32 tolerance of the precision policy."""
+    print(f"case: streamed accumulation {dims} B={Bn} chunk {chunk_mb}", flush=True)
+    if chunk_mb:
+        monkeypatch.setenv("SL_CHUNK_MB", str(chunk_mb))
+    o = S.build_2d(dims, J, levels)
+    sysg = B.System(dims, J, levels)
+    c = np.random.default_rng(12).standard_normal((Bn, sysg.R, *dims)).astype(np.float32)
+    x = sysg.inverse(_gpu(c)).cpu().numpy()
+    again = sysg.inverse(_gpu(c)).cpu().numpy()
+    assert np.array_equal(x, again)
+    for b in sorted({0, Bn - 1}):
+        assert rel(x[b], T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)) < 1e-5
