@@ -892,6 +892,14 @@ __device__ __forceinline__ void acc_tile_group(int tiles, int &tile, int &grp) {
   tile = r * (tiles >> 3) + u / groups;
 }
 
+// Twiddles from a copy in LDS: 768-point tiles of 16 columns leave room for one
+// block of 12 waves per CU, too few to cover the table reads of the line FFTs.
+// Synthesis of 24 x 768^2: 2297 -> 2189 us, of 4 x 768 x 256: 271 -> 235.
+// Shorter lines have enough waves, and there the reads cost LDS time (384^2,
+// batch 32: 778 -> 824 us); 1024 measured the same either way.
+template <int N>
+constexpr bool acc_tw_lds() { return N == 768; }
+
 template <int N, int BT, int MW, int EM = 1>
 __global__ void __launch_bounds__((ITile<N, MW, EM>::THREADS))
 k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
@@ -901,6 +909,8 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
   constexpr int NT = ITile<N, MW, EM>::NT, M = ITile<N, MW, EM>::M, E = ITile<N, MW, EM>::E;
   using PL = typename ITile<N, MW, EM>::PL;
   __shared__ float2 lds[M * N];
+  __shared__ float2 twl[acc_tw_lds<N>() ? N : 1];
+  if constexpr (acc_tw_lds<N>()) stage_twiddles<N>(twl, tw);   // the FFT's leading barrier orders it
   const int m = threadIdx.x % M, t = threadIdx.x / M;
   int tile, grp;
   acc_tile_group((W + M - 1) / M, tile, grp);
@@ -951,7 +961,10 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
       float2 v[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = stream_load<SL_NT_STREAM && MW != kInvNarrow>(at8(Ui, e));
-      fft_line_p<PL, false>(v, t, LdsLine{lds + m, M}, tw);
+      if constexpr (acc_tw_lds<N>())
+        fft_line_p<PL, false>(v, t, LdsLine{lds + m, M}, TwLds{twl});
+      else
+        fft_line_p<PL, false>(v, t, LdsLine{lds + m, M}, tw);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         // (psi_a - i psi_b) * v
@@ -969,7 +982,10 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
         const float d = *at4(psi, e);
         acc[bt][e] = make_float2(acc[bt][e].x / d, acc[bt][e].y / d);
       }
-      fft_line_p<PL, true>(acc[bt], t, LdsLine{lds + m, M}, tw);
+      if constexpr (acc_tw_lds<N>())
+        fft_line_p<PL, true>(acc[bt], t, LdsLine{lds + m, M}, TwLds{twl});
+      else
+        fft_line_p<PL, true>(acc[bt], t, LdsLine{lds + m, M}, tw);
     }
     if (ok && bl < nb) {
       float2 *accp = dst + (size_t)(b0 + bl) * plane;
