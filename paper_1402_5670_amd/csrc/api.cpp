@@ -95,11 +95,12 @@ void chunk_plan(const sl_system *s, int B, int &nb, int &np) {
 
 // Workspace: spectrum F (also the inverse's accumulator) [B] complex planes,
 // a second accumulator [B] used by sl_denoise_fused (F must survive every
-// chunk there), the chunk of pair planes, per-image max |x|.
+// chunk there; a forward with 16-bit storage keeps its maxima of |x| in it), the
+// chunk of pair planes.
 // Partial sums of the 2D inverse accumulation when its pair loop is split
 // into groups (small batches): [groups - 1][B] complex planes.
 struct Layout {
-  size_t off_F, off_acc, off_chunk, off_xmax, off_part, total;
+  size_t off_F, off_acc, off_chunk, off_part, total;
 };
 
 int inv_groups(const sl_system *s, int B);
@@ -112,8 +113,7 @@ Layout layout(const sl_system *s, int B) {
   L.off_F = 0;
   L.off_acc = align_up(plane * B);
   L.off_chunk = align_up(L.off_acc + plane * B);
-  L.off_xmax = align_up(L.off_chunk + plane * (size_t)nb * np);
-  L.off_part = align_up(L.off_xmax + 4ull * B);
+  L.off_part = align_up(L.off_chunk + plane * (size_t)nb * np);
   L.total = align_up(L.off_part + plane * B * (size_t)(inv_groups(s, B) - 1));
   return L;
 }
@@ -149,7 +149,7 @@ sl::Sys2D view2d(const sl_system *s) {
 // workspace can hold their scratch planes.
 bool use_xcd(const sl_system *s, int B, const Layout &L) {
   if (!s->xcd || s->cfg.ndim != 2 || !s->xcd_err_dev) return false;
-  if (L.off_xmax - L.off_chunk < sl::xcd_scratch_bytes()) return false;
+  if (L.off_part - L.off_chunk < sl::xcd_scratch_bytes()) return false;
   return sl::xcd_supported(view2d(s), B);
 }
 
@@ -266,8 +266,14 @@ hipError_t timed(int pass, hipStream_t st, F &&launch) {
 
 #define SL_LAUNCH(pass, st, expr) SL_TRY(timed(pass, st, [&]() { return (expr); }))
 
+// Storage scales of a forward: rows is the row view of the images, each
+// `slices` planes of the column pass.
+sl::ScaleArgs scale_args(const sl::Sys2D &rows, const float *bmax, float *scales, int slices) {
+  return {bmax, rows.l1, scales, sl::rows_real_blocks(rows), rows.R, slices};
+}
+
 int forward3d(const sl_system *s, const float *x, int batch, void *coef, float *scales,
-              float2 *F, float2 *T, unsigned *xmax, bool dual, hipStream_t st) {
+              float2 *F, float2 *T, float *bmax, bool dual, hipStream_t st) {
   const int D = (int)s->cfg.dims[0], H = (int)s->cfg.dims[1], W = (int)s->cfg.dims[2];
   const bool scaled = s->cfg.dtype != SL_F32;
   const sl::Sys2D vr = view2d(s, D * H, W, 0, W);       // x lines
@@ -278,15 +284,15 @@ int forward3d(const sl_system *s, const float *x, int batch, void *coef, float *
   const bool half = s->plane3d && !plane && sl::half_plane_supported(H, W);
   const float inv_vol = 1.0f / ((float)(D * H) * (float)W);
   const sl::Sys3D v3 = view3d(s);
-  if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_zero_u32(xmax, batch, st));
-  SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(vr, x, F, scaled ? xmax : nullptr, batch, st));
-  SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(vy, F, F, batch * D, false, st));
+  SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(vr, x, F, scaled ? bmax : nullptr, batch, st));
+  SL_LAUNCH(P_COLS_FFT, st,
+            sl::launch_cols_fft(vy, F, F, batch * D, false, st, false,
+                                scale_args(vr, bmax, scaled ? scales : nullptr, D)));
   // the z pass takes the DFT along z itself, unless F must be divided by
   // Psi_hat first (the adjoint)
   const bool zdft = !dual;
   if (!zdft) SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(vz, F, F, batch, false, st));
   if (dual) SL_LAUNCH(P_AUX, st, sl::launch_div_psi(F, s->d_psi, (size_t)s->cfg.npix(), batch, st));
-  if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_scales(vr, xmax, scales, batch, st));
   int nb, np;
   chunk_plan(s, batch, nb, np);
   const int P = (s->R + 1) / 2;
@@ -603,7 +609,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
       const Layout L = layout(c.s, c.B);
       char *ws = (char *)c.ws;
       float2 *F = (float2 *)(ws + L.off_F);
-      unsigned *xmax = (unsigned *)(ws + L.off_xmax);
+      float *bmax = (float *)(ws + L.off_acc);
       const sl::Sys2D v = view2d(c.s);
       const bool scaled = dtype != SL_F32;
       if (scaled && !c.scales) return fail(SL_EINVAL, "scales are required for F16/BF16 storage");
@@ -612,11 +618,11 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
                   sl::launch_plane2_fwd(v, c.x, c.coef, c.scales, c.B, false, st));
         continue;
       }
-      if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_zero_u32(xmax, c.B, st));
       SL_LAUNCH(P_ROWS_REAL_FFT, st,
-                sl::launch_rows_real_fft(v, c.x, F, scaled ? xmax : nullptr, c.B, st));
-      SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(v, F, F, c.B, false, st));
-      if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_scales(v, xmax, c.scales, c.B, st));
+                sl::launch_rows_real_fft(v, c.x, F, scaled ? bmax : nullptr, c.B, st));
+      SL_LAUNCH(P_COLS_FFT, st,
+                sl::launch_cols_fft(v, F, F, c.B, false, st, false,
+                                    scale_args(v, bmax, scaled ? c.scales : nullptr, 1)));
     }
     for (size_t k = 0; k < steps; ++k) {
       sl::MultiRows mr{};
@@ -1088,9 +1094,9 @@ static int forward_impl(const sl_system *s, const float *x_dev, int batch, void 
   char *ws = (char *)workspace_dev;
   float2 *F = (float2 *)(ws + L.off_F);
   float2 *T = (float2 *)(ws + L.off_chunk);
-  unsigned *xmax = (unsigned *)(ws + L.off_xmax);
+  float *bmax = (float *)(ws + L.off_acc);
   if (s->cfg.ndim == 3)
-    return forward3d(s, x_dev, batch, coeffs_dev, scales_dev, F, T, xmax, dual, st);
+    return forward3d(s, x_dev, batch, coeffs_dev, scales_dev, F, T, bmax, dual, st);
   const sl::Sys2D v = view2d(s);
   if (!dual && use_xcd(s, batch, L)) {
     SL_LAUNCH(P_XCD_FWD, st,
@@ -1103,11 +1109,11 @@ static int forward_impl(const sl_system *s, const float *x_dev, int batch, void 
               sl::launch_plane2_fwd(v, x_dev, coeffs_dev, scales_dev, batch, dual, st));
     return SL_OK;
   }
-  if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_zero_u32(xmax, batch, st));
-  SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(v, x_dev, F, scaled ? xmax : nullptr, batch, st));
-  SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(v, F, F, batch, false, st));
+  SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(v, x_dev, F, scaled ? bmax : nullptr, batch, st));
+  SL_LAUNCH(P_COLS_FFT, st,
+            sl::launch_cols_fft(v, F, F, batch, false, st, false,
+                                scale_args(v, bmax, scaled ? scales_dev : nullptr, 1)));
   if (dual) SL_LAUNCH(P_AUX, st, sl::launch_div_psi(F, s->d_psi, (size_t)s->cfg.npix(), batch, st));
-  if (scaled) SL_LAUNCH(P_AUX, st, sl::launch_scales(v, xmax, scales_dev, batch, st));
   int nb, np;
   chunk_plan(s, batch, nb, np);
   const int P = (s->R + 1) / 2;

@@ -41,9 +41,11 @@ struct Chunk {
 bool lines_supported(int n);
 
 // Forward passes --------------------------------------------------------------
-// x [B][H][W] real -> A [B][H][W] complex (row DFT); xmax[b] = max |x_b| bits
-hipError_t launch_rows_real_fft(const Sys2D &s, const float *x, float2 *A, unsigned *xmax, int B,
+// x [B][H][W] real -> A [B][H][W] complex (row DFT); bmax (or NULL):
+// [B][rows_real_blocks] maxima of |x|
+hipError_t launch_rows_real_fft(const Sys2D &s, const float *x, float2 *A, float *bmax, int B,
                                 hipStream_t st);
+int rows_real_blocks(const Sys2D &s);
 // Inpainting input of one iteration (Algorithm 3), formed while the rows are
 // loaded: x = fm where mask != 0, else f (0 when first: the iteration starts
 // from f = 0 and f is not read).  The launch also writes the iteration's
@@ -60,20 +62,26 @@ struct MixArgs {
 // launch_rows_real_fft with x formed by MixArgs (no max-|x|)
 hipError_t launch_rows_real_fft_mix(const Sys2D &s, const MixArgs &mix, float2 *A, int B,
                                     hipStream_t st);
+// Storage scales written by launch_cols_fft: scales [B][R] from n maxima per
+// image and the subbands' l1 norms; an image is `slices` planes of the call.
+struct ScaleArgs {
+  const float *bmax;
+  const float *l1;
+  float *scales;    // NULL: none
+  int n, R, slices;
+};
 // A -> F (column DFT, or inverse DFT without scaling when inverse is set);
 // stream marks A and F as pair-plane streams read or written once (accessed
 // with the non-temporal hint)
 hipError_t launch_cols_fft(const Sys2D &s, const float2 *A, float2 *F, int B, bool inverse,
-                           hipStream_t st, bool stream = false);
+                           hipStream_t st, bool stream = false,
+                           const ScaleArgs &sc = ScaleArgs{nullptr, nullptr, nullptr, 0, 0, 1});
 // F, filters -> T[chunk] (filter pair multiply + column inverse DFT)
 hipError_t launch_cols_filter_ifft(const Sys2D &s, const float2 *F, float2 *T, Chunk c,
                                    hipStream_t st);
 // T[chunk] -> coefficients (row inverse DFT, pair split, storage encode)
 hipError_t launch_rows_coef(const Sys2D &s, const float2 *T, void *coef, const float *scales,
                             Chunk c, hipStream_t st);
-// scales[b][i] from xmax and l1 norms (F16 / BF16 storage)
-hipError_t launch_scales(const Sys2D &s, const unsigned *xmax, float *scales, int B,
-                         hipStream_t st);
 hipError_t launch_zero_u32(unsigned *p, int n, hipStream_t st);
 hipError_t launch_div_psi(float2 *F, const float *psi, size_t npix, int B, hipStream_t st);
 

@@ -82,4 +82,19 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Maximum over a block of THREADS threads, through lds (a wave's value each,
+// or a thread's where the last wave is partial), which must not be in use and
+// is free again only after the caller's next barrier.
+template <int THREADS>
+__device__ __forceinline__ float block_max(float v, float *lds) {
+  constexpr bool FULL = THREADS % 64 == 0;
+  constexpr int n = FULL ? THREADS / 64 : THREADS;
+  if constexpr (FULL) v = wave_max(v);
+  if (!FULL || (threadIdx.x & 63) == 0) lds[FULL ? threadIdx.x >> 6 : threadIdx.x] = v;
+  __syncthreads();
+  float mm = lds[0];
+  for (int i = 1; i < n; ++i) mm = fmaxf(mm, lds[i]);
+  return mm;
+}
+
 }  // namespace sl

@@ -411,3 +411,39 @@ def test_streamed_accumulation(monkeypatch, dims, J, levels, Bn, chunk_mb):
     assert np.array_equal(x, again)
     for b in sorted({0, Bn - 1}):
         assert rel(x[b], T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)) < 1e-5
+
+
+@pytest.mark.parametrize("dims,J,levels", [
+    ((12, 24), 1, [1]), ((96, 16), 1, [1]), ((8, 48), 1, [1]), ((384, 48), 2, [1, 1]),
+    ((1024, 12), 1, [1]), ((96, 768), 2, [1, 1]), ((12, 16, 24), 1, [1]), ((24, 12, 96), 1, [1])])
+def test_storage_scales(dims, J, levels):
+    """Scales of 16-bit storage from the row blocks' maxima: partial wavefronts,
+    one and many blocks per image, volumes; an extreme value in the first and
+    the last row, an image of zeros.  The scales are powers of two given by
+    max|x| and the subband's l1 norm, so they are compared exactly."""
+    print(f"case: storage scales {dims}", flush=True)
+    sysg = B.System(dims, J, levels, dtype="f16")
+    x = np.random.default_rng(5).standard_normal((4, *dims)).astype(np.float32)
+    x[0].flat[-1] = -311.5
+    x[1].flat[0] = 77.25
+    x[2] = 0
+    l1 = np.array([s[5] for s in sysg.subbands], np.float32)
+    bound = np.abs(x).reshape(4, -1).max(1)[:, None] * l1[None]
+    want = np.where(bound > 0, np.exp2(np.ceil(np.log2(np.maximum(bound, 1e-30))) - 15), 1)
+    for _ in range(2):
+        _, s = sysg.forward(_gpu(x))
+        assert np.array_equal(s.cpu().numpy().reshape(want.shape), want.astype(np.float32))
+
+
+@pytest.mark.parametrize("dims,Bn", [((768, 24), 1), ((768, 48), 3), ((768, 256), 2)])
+def test_768_point_columns(dims, Bn):
+    """Inverse accumulation of 768-point columns (twiddles staged in LDS): a
+    partial tile, an odd last image, float32 tolerance of the precision
+    policy."""
+    print(f"case: 768-point columns {dims} B={Bn}", flush=True)
+    o = S.build_2d(dims, 2, [1, 1])
+    sysg = B.System(dims, 2, [1, 1])
+    c = np.random.default_rng(13).standard_normal((Bn, sysg.R, *dims)).astype(np.float32)
+    x = sysg.inverse(_gpu(c)).cpu().numpy()
+    for b in range(Bn):
+        assert rel(x[b], T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)) < 1e-5
