@@ -349,14 +349,14 @@ bool whole_planes(const sl_system *s) {
   return s->cfg.ndim == 2 && sl::plane2_supported((int)s->cfg.dims[0], (int)s->cfg.dims[1]);
 }
 
-// Inverse of small images; partial sums take the chunk's pair planes.
+// Inverse of small images; the groups' shares take the chunk's pair planes.
 int inverse_whole_planes(const sl_system *s, const void *coef, const float *scales,
                          const sl::ThrArgs &thr, int batch, float *x, char *ws, hipStream_t st) {
   const sl::Sys2D v = view2d(s);
   int nb, np;
   chunk_plan(s, batch, nb, np);
   const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
-  float2 *part = (float2 *)(ws + layout(s, batch).off_chunk);
+  float *part = (float *)(ws + layout(s, batch).off_chunk);
   SL_LAUNCH(P_PLANE_INV, st, sl::launch_plane2_inv(v, coef, scales, thr, x, part, G, batch, st));
   return SL_OK;
 }
@@ -408,7 +408,7 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
   if (whole_planes(s)) {
     const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
     SL_LAUNCH(P_PLANE_THR, st,
-              sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, T, G, batch, st));
+              sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, (float *)T, G, batch, st));
     return SL_OK;
   }
   const int G = inv_groups(s, batch);

@@ -119,22 +119,22 @@ struct Plane2Args {
   const float2 *twH, *twW;
   float inv_hw;
   float *out;              // [B][H][W]
-  float2 *part;            // partial sums [B][G][H][W] (G > 1 groups)
+  float *part;             // shares of out [B][G][H][W] (G > 1 groups)
 };
 bool plane2_supported(int H, int W);
-// pair groups of the inverse and the denoiser, with part_planes planes of
-// scratch for their partial sums (1 = none needed)
+// pair groups of the inverse and the denoiser, with part_planes complex
+// planes of scratch for their shares of the result (1 = none needed)
 int plane2_inv_groups(const Sys2D &s, int B, size_t part_planes);
 // x -> coefficients and, for F16 / BF16 storage, scales
 hipError_t launch_plane2_fwd(const Sys2D &s, const float *x, void *coef, float *scales, int B,
                              bool dual, hipStream_t st);
 // coefficients (hard threshold on load if thr.sigma) -> x
 hipError_t launch_plane2_inv(const Sys2D &s, const void *coef, const float *scales,
-                             const ThrArgs &thr, float *x, float2 *part, int G, int B,
+                             const ThrArgs &thr, float *x, float *part, int G, int B,
                              hipStream_t st);
 // x (or the inpainting input of mix) -> denoised out, without coefficients
 hipError_t launch_plane2_thr(const Sys2D &s, const float *x, const MixArgs *mix,
-                             const ThrArgs &thr, float *out, float2 *part, int G, int B,
+                             const ThrArgs &thr, float *out, float *part, int G, int B,
                              hipStream_t st);
 
 // ---- multi-class coefficient row passes (uneven batches) ---------------------

@@ -9,13 +9,13 @@
 //             IDFT, coefficient store.  The image's DFT is repeated per group,
 //             half of one pair's work each.
 //   inverse   block (group, image): per pair coefficient load, threshold, row
-//             and column DFT, filter product, sum in registers; one group
-//             finishes in place, several leave partial sums that
-//             k_plane2_finish adds in group order.
+//             and column DFT, filter product, sum in registers, inverse
+//             DFT of the sum: x, or with several groups a share of it that
+//             k_plane2_sum adds in group order.
 //   denoise   both around the threshold, without coefficients.
 // Measured on MI355X against the line passes, forward + inverse: one 64 x 64
-// image 38 -> 23 us, 64 of them (R = 33) 75 -> 43 us, one 32 x 32 39 -> 18 us;
-// denoise of 64 x 64 x 64 62 -> 34 us.  The line ends at 64 x 64: from 96 x 64
+// image 38 -> 17 us, 64 of them (R = 33) 76 -> 41 us; denoise of 8 such images
+// 31 -> 14 us.  The line ends at 64 x 64: from 96 x 64
 // on the work of one plane outweighs the launches saved (128 x 128, R = 49:
 // one image 38 us in line passes, 103 us here; 30 images 142 against 195 us).
 //
@@ -213,9 +213,16 @@ __device__ __forceinline__ void p2_acc_cols(Plane2Lds<H, W> &s, ColVals<H, W> &a
   }
 }
 
-// x = Re IDFT(acc / Psi_hat)
+// Re IDFT(acc / Psi_hat) of the block's column sums: x for the only group of an
+// image, else its share of x, real plane (b, g) of part.
+//
+// The transform is linear, so a group may finish its own share.  Shares are half
+// the bytes of partial spectra and are added by as many blocks as there are
+// samples for; adding the spectra of an image in the one block that transforms
+// them took 11.3 us for a 64 x 64 image with 17 groups, against 2.5 us here for
+// the transform and 2.7 us for the sum.
 template <int H, int W>
-__device__ __forceinline__ void p2_finish(Plane2Lds<H, W> &s, ColVals<H, W> &acc,
+__device__ __forceinline__ void p2_result(Plane2Lds<H, W> &s, ColVals<H, W> &acc,
                                           const Plane2Args &a, int b) {
   using PT = Plane2<H, W>;
   float2 *pl = s.pl;
@@ -235,7 +242,8 @@ __device__ __forceinline__ void p2_finish(Plane2Lds<H, W> &s, ColVals<H, W> &acc
   }
   __syncthreads();
   const int t = threadIdx.x % PT::NTR, m = threadIdx.x / PT::NTR;
-  float *xo = a.out + (size_t)b * H * W;
+  float *xo = gridDim.x == 1 ? a.out + (size_t)b * H * W
+                             : a.part + ((size_t)b * gridDim.x + blockIdx.x) * H * W;
 #pragma unroll
   for (int ri = 0; ri < PT::NRI; ++ri) {
     const int y = ri * PT::MR + m;
@@ -247,24 +255,6 @@ __device__ __forceinline__ void p2_finish(Plane2Lds<H, W> &s, ColVals<H, W> &acc
 #pragma unroll
     for (int e = 0; e < PT::ER; ++e) xo[y * W + t + e * PT::NTR] = v[e].x * a.inv_hw;
   }
-}
-
-// the block's column sums: finished to x, or left as partial plane (g, b)
-template <int H, int W>
-__device__ __forceinline__ void p2_result(Plane2Lds<H, W> &s, ColVals<H, W> &acc, const Plane2Args &a,
-                                          int b) {
-  using PT = Plane2<H, W>;
-  if (gridDim.x == 1) {
-    p2_finish<H, W>(s, acc, a, b);
-    return;
-  }
-  const int mc = threadIdx.x % PT::MC, tc = threadIdx.x / PT::MC;
-  float2 *dst = a.part + ((size_t)b * gridDim.x + blockIdx.x) * H * W;
-#pragma unroll
-  for (int ci = 0; ci < PT::NCI; ++ci)
-#pragma unroll
-    for (int e = 0; e < PT::EC; ++e)
-      dst[(tc + e * PT::NTC) * W + ci * PT::MC + mc] = acc[ci][e];
 }
 
 // hard thresholds of a pair (0 = keep everything)
@@ -326,7 +316,7 @@ k_plane2_fwd(Plane2Args a, const float *__restrict__ x, typename Store<DT>::T *_
       p2_filters<H, W>(a.filt, p + gridDim.x, a.R, 0, (tid / PT::MC) * W + tid % PT::MC, fa, fb);
     float sa = a.inv_hw, sb = a.inv_hw;
     if constexpr (DT != 0) {
-      // the storage scales of k_scales
+      // the storage scales, as k_cols_fft
       const float ba = amax * a.l1[ia], bb = ib < a.R ? amax * a.l1[ib] : 0.f;
       const float ca = ba > 0.f ? exp2f(ceilf(log2f(ba)) - 15.f) : 1.f;
       const float cb = bb > 0.f ? exp2f(ceilf(log2f(bb)) - 15.f) : 1.f;
@@ -474,29 +464,23 @@ k_plane2_thr(Plane2Args a, const float *__restrict__ x, ThrArgs thr, MixArgs mix
   p2_result<H, W>(s, acc, a, b);
 }
 
-// x[b] from the partial sums of G groups, added in group order
-template <int H, int W>
-__global__ void __launch_bounds__((Plane2<H, W>::THREADS), (Plane2<H, W>::WPE))
-k_plane2_finish(Plane2Args a, int G) {
-  using PT = Plane2<H, W>;
-  __shared__ Plane2Lds<H, W> s;
-  s.stage(a.twH, a.twW);
-  const int b = blockIdx.x;
-  const int mc = threadIdx.x % PT::MC, tc = threadIdx.x / PT::MC;
-  ColVals<H, W> acc;
-#pragma unroll
-  for (int ci = 0; ci < PT::NCI; ++ci)
-#pragma unroll
-    for (int e = 0; e < PT::EC; ++e) acc[ci][e] = make_float2(0.f, 0.f);
-  const float2 *src = a.part + (size_t)b * G * H * W + tc * W + mc;
-#pragma unroll 2
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int ci = 0; ci < PT::NCI; ++ci)
-#pragma unroll
-      for (int e = 0; e < PT::EC; ++e)
-        acc[ci][e] = cadd(acc[ci][e], src[(size_t)g * H * W + e * PT::NTC * W + ci * PT::MC]);
-  p2_finish<H, W>(s, acc, a, b);
+// x = the shares of G groups, added in group order; n samples per image (grid
+// (blocks, B)).  Blocks of one wave, a sample per lane: an image has few, and x
+// may be aligned to 4 bytes only.
+__global__ void __launch_bounds__(64)
+k_plane2_sum(const float *__restrict__ part, float *__restrict__ x, int G, int n) {
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (i >= n) return;
+  const float *src = part + (size_t)blockIdx.y * G * n + i;
+  float v = src[0];
+#pragma unroll 8
+  for (int g = 1; g < G; ++g) v += src[(size_t)g * n];
+  x[(size_t)blockIdx.y * n + i] = v;
+}
+
+static hipError_t launch_plane2_sum(const Plane2Args &a, int n, int G, int B, hipStream_t st) {
+  hipLaunchKernelGGL(k_plane2_sum, dim3((n + 63) / 64, B), dim3(64), 0, st, a.part, a.out, G, n);
+  return hipGetLastError();
 }
 
 // ---- launchers ------------------------------------------------------------------
@@ -527,7 +511,7 @@ int plane2_inv_groups(const Sys2D &s, int B, size_t part_planes) {
   if (s.H == h && s.W == w) G = plane2_groups(s, B, sizeof(Plane2Lds<h, w>), Plane2<h, w>::WPE * 256 / Plane2<h, w>::THREADS);
   SL_FOR_EACH_PLANE2(X)
 #undef X
-  if (!s.split_pairs || (size_t)G * B > part_planes) G = 1;
+  if (!s.split_pairs || (size_t)G * B > 2 * part_planes) G = 1;
   return G;
 }
 
@@ -568,7 +552,7 @@ hipError_t launch_plane2_fwd(const Sys2D &s, const float *x, void *coef, float *
 }
 
 hipError_t launch_plane2_inv(const Sys2D &s, const void *coef, const float *scales,
-                             const ThrArgs &thr, float *x, float2 *part, int G, int B,
+                             const ThrArgs &thr, float *x, float *part, int G, int B,
                              hipStream_t st) {
   Plane2Args a = plane2_args(s);
   a.out = x;
@@ -585,9 +569,8 @@ hipError_t launch_plane2_inv(const Sys2D &s, const void *coef, const float *scal
     else                                                                                         \
       hipLaunchKernelGGL((k_plane2_inv<h, w, 0>), grid, block, 0, st, a, (const float *)coef,    \
                          scales, thr);                                                           \
-    if (G > 1)                                                                                   \
-      hipLaunchKernelGGL((k_plane2_finish<h, w>), dim3(B), block, 0, st, a, G);                  \
-    return hipGetLastError();                                                                    \
+    const hipError_t e = hipGetLastError();                                                      \
+    return e != hipSuccess || G == 1 ? e : launch_plane2_sum(a, h * w, G, B, st);                \
   }
   SL_FOR_EACH_PLANE2(X)
 #undef X
@@ -595,7 +578,7 @@ hipError_t launch_plane2_inv(const Sys2D &s, const void *coef, const float *scal
 }
 
 hipError_t launch_plane2_thr(const Sys2D &s, const float *x, const MixArgs *mix,
-                             const ThrArgs &thr, float *out, float2 *part, int G, int B,
+                             const ThrArgs &thr, float *out, float *part, int G, int B,
                              hipStream_t st) {
   Plane2Args a = plane2_args(s);
   a.out = out;
@@ -609,9 +592,8 @@ hipError_t launch_plane2_thr(const Sys2D &s, const float *x, const MixArgs *mix,
       hipLaunchKernelGGL((k_plane2_thr<h, w, 1>), grid, block, 0, st, a, x, thr, *mix);          \
     else                                                                                         \
       hipLaunchKernelGGL((k_plane2_thr<h, w, 2>), grid, block, 0, st, a, x, thr, *mix);          \
-    if (G > 1)                                                                                   \
-      hipLaunchKernelGGL((k_plane2_finish<h, w>), dim3(B), block, 0, st, a, G);                  \
-    return hipGetLastError();                                                                    \
+    const hipError_t e = hipGetLastError();                                                      \
+    return e != hipSuccess || G == 1 ? e : launch_plane2_sum(a, h * w, G, B, st);                \
   }
   SL_FOR_EACH_PLANE2(X)
 #undef X
