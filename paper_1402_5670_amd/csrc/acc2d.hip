@@ -318,11 +318,11 @@ hipError_t launch_cols_acc_stream(const Sys2D &s, const float2 *U, float2 *ACC, 
     const dim3 grid(s.W / DTile<N>::COLS * ((c.nb + bt - 1) / bt), 1, G), block(DTile<N>::THREADS); \
     if (bt == 2)                                                                                 \
       hipLaunchKernelGGL((k_cols_acc_stream<N, 2>), grid, block, 0, st, U, s.filt, s.psi, ACC, part, \
-                         Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first, (int)(last && G == 1), \
+                         Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first, (int)last, \
                          s.twH);                                                                 \
     else                                                                                         \
       hipLaunchKernelGGL((k_cols_acc_stream<N, 1>), grid, block, 0, st, U, s.filt, s.psi, ACC, part, \
-                         Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first, (int)(last && G == 1), \
+                         Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first, (int)last, \
                          s.twH);                                                                 \
     return hipGetLastError();                                                                    \
   }

@@ -339,7 +339,7 @@ int inverse3d(const sl_system *s, const void *coef, const float *scales, int bat
                 sl::launch_z_fft_acc(v3, U, ACC, c, p0 == 0, p0 + c.np == P, st));
     }
   SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(vy, ACC, ACC, batch * D, true, st));
-  SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(vr, ACC, x, batch, st));
+  SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(vr, ACC, nullptr, 1, x, batch, st));
   return SL_OK;
 }
 
@@ -401,7 +401,7 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
                   sl::launch_z_fft_acc(v3, T, ACC, c, p0 == 0, p0 + c.np == P, st));
       }
     SL_LAUNCH(P_COLS_FFT, st, sl::launch_cols_fft(vy, ACC, ACC, batch * D, true, st));
-    SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(vr, ACC, out_dev, batch, st));
+    SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(vr, ACC, nullptr, 1, out_dev, batch, st));
     return SL_OK;
   }
   const sl::Sys2D v = view2d(s);
@@ -426,8 +426,7 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
       SL_LAUNCH(P_COLS_FFT_ACC, st,
                 sl::launch_cols_fft_acc(v, T, ACC, part, G, batch, c, p0 == 0, p0 + c.np == P, st));
     }
-  if (G > 1) SL_LAUNCH(P_COLS_FFT_ACC, st, sl::launch_cols_acc_finish(v, ACC, part, G, batch, st));
-  SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(v, ACC, out_dev, batch, st));
+  SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(v, ACC, part, G, out_dev, batch, st));
   return SL_OK;
 }
 
@@ -694,10 +693,9 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
       char *ws = (char *)c.ws;
       const sl::Sys2D v = view2d(c.s);
       float2 *ACC = (float2 *)(ws + L.off_F);
-      if (groups[i] > 1)
-        SL_LAUNCH(P_COLS_FFT_ACC, st,
-                  sl::launch_cols_acc_finish(v, ACC, (float2 *)(ws + L.off_part), groups[i], c.B, st));
-      SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(v, ACC, c.out, c.B, st));
+      SL_LAUNCH(P_ROWS_REAL_IFFT, st,
+                sl::launch_rows_real_ifft(v, ACC, (float2 *)(ws + L.off_part), groups[i], c.out,
+                                          c.B, st));
     }
   }
   return SL_OK;
@@ -1182,8 +1180,7 @@ int sl_inverse(const sl_system *s, const void *coeffs_dev, const float *scales_d
       SL_LAUNCH(P_COLS_FFT_ACC, st,
                 sl::launch_cols_fft_acc(v, U, ACC, part, G, batch, c, p0 == 0, p0 + c.np == P, st));
     }
-  if (G > 1) SL_LAUNCH(P_COLS_FFT_ACC, st, sl::launch_cols_acc_finish(v, ACC, part, G, batch, st));
-  SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(v, ACC, x_dev, batch, st));
+  SL_LAUNCH(P_ROWS_REAL_IFFT, st, sl::launch_rows_real_ifft(v, ACC, part, G, x_dev, batch, st));
   return SL_OK;
 }
 

@@ -96,8 +96,8 @@ hipError_t launch_rows_thr(const Sys2D &s, float2 *T, float inv_n, Chunk c, cons
 // U[chunk] -> ACC (column DFT, multiply by the filter pair, sum over pairs);
 // the last chunk divides by Psi_hat and applies the column inverse DFT.
 // With G > 1 pair groups (inv_pair_groups) group z sums into part[z - 1]
-// ([G - 1][Btot] planes), and launch_cols_acc_finish completes the sum, the
-// division and the column inverse DFT after the last chunk.
+// ([G - 1][Btot] planes), each finished like ACC; launch_rows_real_ifft adds
+// them.
 int inv_pair_groups(const Sys2D &s, int nb, int np);
 hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
                                int Btot, Chunk c, bool first, bool last, hipStream_t st);
@@ -106,10 +106,9 @@ hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, flo
 bool cols_acc_stream_supported(int H, int W);
 hipError_t launch_cols_acc_stream(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
                                int Btot, Chunk c, int bt, bool first, bool last, hipStream_t st);
-hipError_t launch_cols_acc_finish(const Sys2D &s, float2 *ACC, const float2 *part, int G, int B,
-                                  hipStream_t st);
-// ACC -> x (row inverse DFT, real part, 1/(HW))
-hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, float *x, int B, hipStream_t st);
+// x = Re row IDFT of V + part[0] + ... + part[G - 2] ([B] planes each)
+hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, const float2 *part, int G,
+                                 float *x, int B, hipStream_t st);
 
 // ---- whole-plane passes of small images (plane2d.hip) -------------------------
 struct Plane2Args {

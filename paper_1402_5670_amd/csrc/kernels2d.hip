@@ -930,9 +930,10 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
     return (const float *)((const char *)base + e * sb4 + lo4);
   };
   // pair group z sums pairs [q0, q1) of the chunk into its own partial sum:
-  // ACC for z = 0, part[z - 1] ([Btot] planes each) otherwise; with several
-  // groups k_cols_acc_finish adds the partial sums after the last chunk.  A
-  // group with no pair in this chunk still initialises its partial sum.
+  // ACC for z = 0, part[z - 1] ([Btot] planes each) otherwise, divided and
+  // inverse transformed by itself after the last chunk (both are linear);
+  // k_rows_real_ifft adds the groups.  A group with no pair in this chunk
+  // still initialises its partial sum.
   const int per = (np + (int)gridDim.z - 1) / (int)gridDim.z;
   const int q0 = (int)blockIdx.z * per, q1 = min(np, q0 + per);
   float2 *dst = blockIdx.z == 0 ? ACC : part + (size_t)(blockIdx.z - 1) * Btot * plane;
@@ -995,57 +996,24 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
   }
 }
 
-// ACC += part[0] + ... + part[G-2] over n4 groups of 4 floats (two complex
-// values), summed in group order
-__global__ void __launch_bounds__(256)
-k_acc_sum_parts(float4 *__restrict__ ACC, const float4 *__restrict__ part, int G, size_t n4) {
-  const size_t stride = (size_t)gridDim.x * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
-    float4 v = ACC[i];
-    for (int z = 1; z < G; ++z) {
-      const float4 u = part[(size_t)(z - 1) * n4 + i];
-      v = make_float4(v.x + u.x, v.y + u.y, v.z + u.z, v.w + u.w);
-    }
-    ACC[i] = v;
-  }
-}
-
-// ACC[b] = column IDFT(ACC[b] / Psi_hat), in place: every thread reads its
-// own column samples before the FFT.
+// lines per block of k_rows_real_ifft where it adds partial sums
 template <int N>
-__global__ void __launch_bounds__(CTile<N>::THREADS)
-k_cols_acc_finish(float2 *__restrict__ ACC, const float *__restrict__ psi, int W,
-                  const float2 *__restrict__ tw) {
-  constexpr int NT = CTile<N>::NT, M = CTile<N>::M, E = CTile<N>::E;
-  using PL = typename CTile<N>::PL;
-  __shared__ float2 lds[M * N];
-  const int m = threadIdx.x % M, t = threadIdx.x / M;
-  const int col = col_tile() * M + m;
-  const bool ok = col < W;
-  const int cc = ok ? col : 0;
-  const size_t plane = (size_t)N * W;
-  const int b = blockIdx.y;
-  float2 *accp = ACC + (size_t)b * plane + cc;
-  float2 v[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = accp[(size_t)(t + e * NT) * W];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const float d = psi[(size_t)(t + e * NT) * W + cc];
-    v[e] = make_float2(v[e].x / d, v[e].y / d);
-  }
-  fft_line_p<PL, true>(v, t, LdsLine{lds + m, M}, tw);
-  if (ok) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) accp[(size_t)(t + e * NT) * W] = v[e];
-  }
-}
+constexpr int sum_rows() { return Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT; }
 
-template <int N>
-__global__ void __launch_bounds__(Tile<N>::THREADS)
-k_rows_real_ifft(const float2 *__restrict__ V, float *__restrict__ x, int H, float inv_hw,
+// x = Re row IDFT(V), V the column pass's accumulator and, with G > 1 pair
+// groups, G - 1 partial sums after it (pstride values apart), added in group
+// order while the rows are loaded.  G > 1 has few images: blocks of two waves
+// spread the rows over the compute units (M = sum_rows).  With one launch that
+// adds partial spectra and another that transforms their columns in place of
+// the groups doing so themselves: denoise of one 512^2 image 103.6 us, now
+// 94.6; 16 x 256^2 in bf16, both directions, 281 and 275; 3 x 96 x 384 in fp16
+// 59.2 and 56.1.
+template <int N, int M>
+__global__ void __launch_bounds__(M *Tile<N>::NT)
+k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, int G,
+                 size_t pstride, float *__restrict__ x, int H, float inv_hw,
                  const float2 *__restrict__ tw) {
-  constexpr int NT = Tile<N>::NT, M = Tile<N>::M, E = Tile<N>::E;
+  constexpr int NT = Tile<N>::NT, E = Tile<N>::E;
   __shared__ float2 lds[M * row_lds_len<N>()];
   const int t = threadIdx.x % NT, m = threadIdx.x / NT;
   const int row = blockIdx.x * M + m, b = blockIdx.y;
@@ -1054,6 +1022,12 @@ k_rows_real_ifft(const float2 *__restrict__ V, float *__restrict__ x, int H, flo
   float2 v[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = V[off + t + e * NT];
+#pragma unroll 4
+  for (int z = 1; z < G; ++z) {
+    const float2 *p = part + (size_t)(z - 1) * pstride + off + t;
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = cadd(v[e], p[e * NT]);
+  }
   fft_line<N, true>(v, t, LdsLine{lds + m * row_lds_len<N>(), 0}, tw);
   if (ok) {
 #pragma unroll
@@ -1061,9 +1035,6 @@ k_rows_real_ifft(const float2 *__restrict__ V, float *__restrict__ x, int H, flo
   }
 }
 
-// ---------------------------------------------------------------------------
-// launchers: runtime length -> template instance
-// ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // Plane passes of a volume: the y and x line FFTs of one z-slice of a pair
 // volume in LDS (the slice, rows padded as the row kernels pad them), so the
@@ -2000,12 +1971,12 @@ static bool cols_fft_acc_em2(const Sys2D &s, const float2 *U, float2 *ACC, float
         hipLaunchKernelGGL((k_cols_fft_acc<N, 2, kInvNarrow, 2>),
                            dim3((s.W + IT::M - 1) / IT::M, (c.nb + 1) / 2, G), dim3(IT::THREADS), 0,
                            st, U, s.filt, s.psi, ACC, part, Btot, s.W, s.R, c.b0, c.nb, c.p0,
-                           c.np, (int)first, (int)(last && G == 1), s.twH);
+                           c.np, (int)first, (int)last, s.twH);
       else
         hipLaunchKernelGGL((k_cols_fft_acc<N, 1, kInvNarrow, 2>),
                            dim3((s.W + IT::M - 1) / IT::M, c.nb, G), dim3(IT::THREADS), 0, st, U,
                            s.filt, s.psi, ACC, part, Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np,
-                           (int)first, (int)(last && G == 1), s.twH);
+                           (int)first, (int)last, s.twH);
       return true;
     }
   }
@@ -2039,19 +2010,19 @@ hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, flo
                          dim3((s.W + ITile<N, kInvNarrow>::M - 1) / ITile<N, kInvNarrow>::M, 1, G), \
                          dim3(ITile<N, kInvNarrow>::THREADS), 0, st, U, s.filt, s.psi, ACC, part, \
                          Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first,                    \
-                         (int)(last && G == 1), s.twH);                                         \
+                         (int)last, s.twH);                                         \
     else if (inv_bt(s, c.nb) == 1)                                                              \
       hipLaunchKernelGGL((k_cols_fft_acc<N, 1, kInvWide>),                                      \
                          dim3((s.W + ITile<N, kInvWide>::M - 1) / ITile<N, kInvWide>::M, c.nb, G), \
                          dim3(ITile<N, kInvWide>::THREADS), 0, st, U, s.filt, s.psi, ACC, part, \
                          Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first,                    \
-                         (int)(last && G == 1), s.twH);                                         \
+                         (int)last, s.twH);                                         \
     else                                                                                        \
       hipLaunchKernelGGL((k_cols_fft_acc<N, kInvBT, kInvWide>),                                 \
                          acc_grid(s.W, ITile<N, kInvWide>::M, (c.nb + kInvBT - 1) / kInvBT, G), \
                          dim3(ITile<N, kInvWide>::THREADS), 0, st, U, s.filt, s.psi, ACC, part, \
                          Btot, s.W, s.R, c.b0, c.nb, c.p0, c.np, (int)first,                    \
-                         (int)(last && G == 1), s.twH);                                         \
+                         (int)last, s.twH);                                         \
     break;
     SL_FOR_EACH_N(X)
 #undef X
@@ -2061,36 +2032,24 @@ hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, flo
   return hipGetLastError();
 }
 
-hipError_t launch_cols_acc_finish(const Sys2D &s, float2 *ACC, const float2 *part, int G, int B,
-                                  hipStream_t st) {
-  // partial sums first, at full-device parallelism (a plane holds an even
-  // number of complex values: two per float4)
-  const size_t n4 = (size_t)B * s.H * s.W / 2;
-  const size_t want = (n4 + 255) / 256;
-  hipLaunchKernelGGL(k_acc_sum_parts, dim3((unsigned)(want < 8192 ? want : 8192)), dim3(256), 0,
-                     st, (float4 *)ACC, (const float4 *)part, G, n4);
-  switch (s.H) {
-#define X(N)                                                                                  \
-  case N:                                                                                     \
-    hipLaunchKernelGGL(k_cols_acc_finish<N>, col_grid<N>(s.W, B), dim3(CTile<N>::THREADS), 0, \
-                       st, ACC, s.psi, s.W, s.twH);                                           \
-    break;
-    SL_FOR_EACH_N(X)
-#undef X
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, float *x, int B, hipStream_t st) {
+hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, const float2 *part, int G,
+                                 float *x, int B, hipStream_t st) {
   const float inv_hw = 1.0f / ((float)s.H * (float)s.W);
+  const size_t pstride = (size_t)B * s.H * s.W;
   switch (s.W) {
-#define X(N)                                                                                 \
-  case N:                                                                                    \
-    hipLaunchKernelGGL(k_rows_real_ifft<N>, row_grid<N>(s.H, B), dim3(Tile<N>::THREADS), 0, \
-                       st, V, x, s.H, inv_hw, s.twW);                                        \
-    break;
+#define X(N)                                                                                   \
+  case N: {                                                                                    \
+    constexpr int M = sum_rows<N>(), MT = Tile<N>::M;                                          \
+    if (G > 1)                                                                                 \
+      hipLaunchKernelGGL((k_rows_real_ifft<N, M>), dim3((s.H + M - 1) / M, B),                 \
+                         dim3(M *Tile<N>::NT), 0, st, V, part, G, pstride, x, s.H, inv_hw,     \
+                         s.twW);                                                               \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_rows_real_ifft<N, MT>), row_grid<N>(s.H, B),                       \
+                         dim3(Tile<N>::THREADS), 0, st, V, nullptr, 1, pstride, x, s.H, inv_hw, \
+                         s.twW);                                                               \
+    break;                                                                                     \
+  }
     SL_FOR_EACH_N(X)
 #undef X
     default:

@@ -447,3 +447,23 @@ def test_768_point_columns(dims, Bn):
     x = sysg.inverse(_gpu(c)).cpu().numpy()
     for b in range(Bn):
         assert rel(x[b], T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)) < 1e-5
+
+
+@pytest.mark.parametrize("dims,J,levels,Bn", [
+    ((24, 8), 1, [1], 1), ((12, 24), 1, [1], 3), ((96, 16), 1, [1], 2), ((8, 96), 1, [1], 1),
+    ((48, 1024), 1, [1], 1), ((12, 768), 1, [1], 2), ((384, 128), 2, [1, 1], 3)])
+def test_pair_groups_finish(dims, J, levels, Bn):
+    """Pair groups that finish their own partial sums, added by the row pass:
+    row counts off its smaller blocks, short and long rows, an odd last image.
+    Reconstruction of random coefficients against the oracle, float32 tolerance
+    of the precision policy; the undivided schedule agrees."""
+    print(f"case: pair groups {dims} B={Bn}", flush=True)
+    o = S.build_2d(dims, J, levels)
+    sysg = B.System(dims, J, levels)
+    c = np.random.default_rng(14).standard_normal((Bn, sysg.R, *dims)).astype(np.float32)
+    for split in (1, 0):
+        sysg.set_block_shape(0, split)
+        x = sysg.inverse(_gpu(c)).cpu().numpy()
+        for b in range(Bn):
+            ref = T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)
+            assert rel(x[b], ref) < 1e-5, (split, b)
