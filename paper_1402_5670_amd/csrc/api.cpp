@@ -266,10 +266,11 @@ hipError_t timed(int pass, hipStream_t st, F &&launch) {
 
 #define SL_LAUNCH(pass, st, expr) SL_TRY(timed(pass, st, [&]() { return (expr); }))
 
-// Storage scales of a forward: rows is the row view of the images, each
+// Storage scales of a forward: rows is the row view of the B images, each
 // `slices` planes of the column pass.
-sl::ScaleArgs scale_args(const sl::Sys2D &rows, const float *bmax, float *scales, int slices) {
-  return {bmax, rows.l1, scales, sl::rows_real_blocks(rows), rows.R, slices};
+sl::ScaleArgs scale_args(const sl::Sys2D &rows, int B, const float *bmax, float *scales,
+                         int slices) {
+  return {bmax, rows.l1, scales, sl::rows_real_blocks(rows, B), rows.R, slices};
 }
 
 int forward3d(const sl_system *s, const float *x, int batch, void *coef, float *scales,
@@ -287,7 +288,7 @@ int forward3d(const sl_system *s, const float *x, int batch, void *coef, float *
   SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(vr, x, F, scaled ? bmax : nullptr, batch, st));
   SL_LAUNCH(P_COLS_FFT, st,
             sl::launch_cols_fft(vy, F, F, batch * D, false, st, false,
-                                scale_args(vr, bmax, scaled ? scales : nullptr, D)));
+                                scale_args(vr, batch, bmax, scaled ? scales : nullptr, D)));
   // the z pass takes the DFT along z itself, unless F must be divided by
   // Psi_hat first (the adjoint)
   const bool zdft = !dual;
@@ -621,7 +622,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
                 sl::launch_rows_real_fft(v, c.x, F, scaled ? bmax : nullptr, c.B, st));
       SL_LAUNCH(P_COLS_FFT, st,
                 sl::launch_cols_fft(v, F, F, c.B, false, st, false,
-                                    scale_args(v, bmax, scaled ? c.scales : nullptr, 1)));
+                                    scale_args(v, c.B, bmax, scaled ? c.scales : nullptr, 1)));
     }
     for (size_t k = 0; k < steps; ++k) {
       sl::MultiRows mr{};
@@ -1110,7 +1111,7 @@ static int forward_impl(const sl_system *s, const float *x_dev, int batch, void 
   SL_LAUNCH(P_ROWS_REAL_FFT, st, sl::launch_rows_real_fft(v, x_dev, F, scaled ? bmax : nullptr, batch, st));
   SL_LAUNCH(P_COLS_FFT, st,
             sl::launch_cols_fft(v, F, F, batch, false, st, false,
-                                scale_args(v, bmax, scaled ? scales_dev : nullptr, 1)));
+                                scale_args(v, batch, bmax, scaled ? scales_dev : nullptr, 1)));
   if (dual) SL_LAUNCH(P_AUX, st, sl::launch_div_psi(F, s->d_psi, (size_t)s->cfg.npix(), batch, st));
   int nb, np;
   chunk_plan(s, batch, nb, np);

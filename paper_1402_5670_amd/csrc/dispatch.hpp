@@ -45,7 +45,7 @@ bool lines_supported(int n);
 // [B][rows_real_blocks] maxima of |x|
 hipError_t launch_rows_real_fft(const Sys2D &s, const float *x, float2 *A, float *bmax, int B,
                                 hipStream_t st);
-int rows_real_blocks(const Sys2D &s);
+int rows_real_blocks(const Sys2D &s, int B);
 // Inpainting input of one iteration (Algorithm 3), formed while the rows are
 // loaded: x = fm where mask != 0, else f (0 when first: the iteration starts
 // from f = 0 and f is not read).  The launch also writes the iteration's

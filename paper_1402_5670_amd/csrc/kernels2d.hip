@@ -56,15 +56,24 @@ constexpr bool em2_length() { return N == 1024; }
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
+// Lines per block of the rows of single planes (k_rows_real_fft,
+// k_rows_real_ifft) where tiles of Tile<N>::M lines are fewer than the compute
+// units: blocks of two waves, of a quarter of the lines or fewer.  With
+// narrower column tiles as well (cols_fft): row and column pass of a 512^2 image
+// 6.1 + 6.5 -> 4.7 + 4.8 us, 3 x 96 x 384 in fp16, both directions, 56.1 -> 54.4
+// us, 2 x 192 x 768 97.6 -> 92.9; no difference at 256 blocks and more.
+template <int N>
+constexpr int few_rows() { return Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT; }
+
 // MIX = 0: rows of x; MIX = 1 / 2: rows of the inpainting input (MixArgs),
 // first iteration / later ones.  bmax (16-bit storage): max |x| of each
 // block's rows, [image][block], which the column pass turns into the storage
 // scales; one plain store per block needs no cleared counter and no atomic.
-template <int N, int MIX>
-__global__ void __launch_bounds__(Tile<N>::THREADS)
+template <int N, int MIX, int M>
+__global__ void __launch_bounds__(M *Tile<N>::NT)
 k_rows_real_fft(const float *__restrict__ x, float2 *__restrict__ A, float *__restrict__ bmax,
                 int H, const float2 *__restrict__ tw, MixArgs mix, int B) {
-  constexpr int NT = Tile<N>::NT, M = Tile<N>::M, E = Tile<N>::E;
+  constexpr int NT = Tile<N>::NT, E = Tile<N>::E;
   __shared__ float2 lds[M * row_lds_len<N>()];
   const int t = threadIdx.x % NT, m = threadIdx.x / NT;
   const int row = blockIdx.x * M + m, b = blockIdx.y;
@@ -92,7 +101,7 @@ k_rows_real_fft(const float *__restrict__ x, float2 *__restrict__ A, float *__re
     amax = fmaxf(amax, fabsf(a));
   }
   if (bmax) {
-    const float mm = block_max<Tile<N>::THREADS>(amax, (float *)lds);
+    const float mm = block_max<M * NT>(amax, (float *)lds);
     if (threadIdx.x == 0) bmax[(size_t)b * gridDim.x + blockIdx.x] = mm;
     __syncthreads();
   }
@@ -112,11 +121,11 @@ k_rows_real_fft(const float *__restrict__ x, float2 *__restrict__ A, float *__re
 // transform: two launches (clear, scales) less per forward than with a
 // counter per image (3 x 96 x 384 in fp16, both directions: 62.7 -> 59.2 us;
 // 16 x 256^2 in bf16: 284 -> 281).
-template <int N, bool INV, bool NT_>
-__global__ void __launch_bounds__(CTile<N>::THREADS)
+template <int N, bool INV, bool NT_, int M = CTile<N>::M>
+__global__ void __launch_bounds__(M *CTile<N>::NT)
 k_cols_fft(const float2 *__restrict__ A, float2 *__restrict__ F, int W,
            const float2 *__restrict__ tw, ScaleArgs sc) {
-  constexpr int NT = CTile<N>::NT, M = CTile<N>::M, E = CTile<N>::E;
+  constexpr int NT = CTile<N>::NT, E = CTile<N>::E;
   using PL = typename CTile<N>::PL;
   __shared__ float2 lds[M * N];
   const int m = threadIdx.x % M, t = threadIdx.x / M;
@@ -131,7 +140,7 @@ k_cols_fft(const float2 *__restrict__ A, float2 *__restrict__ F, int W,
   const unsigned img = blockIdx.y / sc.slices;
   float mx = 0.f;
   if (scaling)
-    for (int i = threadIdx.x; i < sc.n; i += CTile<N>::THREADS)
+    for (int i = threadIdx.x; i < sc.n; i += M * NT)
       mx = fmaxf(mx, sc.bmax[(size_t)img * sc.n + i]);
   fft_line_p<PL, INV>(v, t, LdsLine{lds + m, M}, tw);
   if (ok) {
@@ -140,8 +149,8 @@ k_cols_fft(const float2 *__restrict__ A, float2 *__restrict__ F, int W,
   }
   if (scaling) {
     __syncthreads();
-    mx = block_max<CTile<N>::THREADS>(mx, (float *)lds);
-    for (int i = threadIdx.x; i < sc.R; i += CTile<N>::THREADS) {
+    mx = block_max<M * NT>(mx, (float *)lds);
+    for (int i = threadIdx.x; i < sc.R; i += M * NT) {
       const float bound = mx * sc.l1[i];
       sc.scales[(size_t)img * sc.R + i] = bound > 0.f ? exp2f(ceilf(log2f(bound)) - 15.f) : 1.f;
     }
@@ -996,14 +1005,10 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
   }
 }
 
-// lines per block of k_rows_real_ifft where it adds partial sums
-template <int N>
-constexpr int sum_rows() { return Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT; }
-
 // x = Re row IDFT(V), V the column pass's accumulator and, with G > 1 pair
 // groups, G - 1 partial sums after it (pstride values apart), added in group
 // order while the rows are loaded.  G > 1 has few images: blocks of two waves
-// spread the rows over the compute units (M = sum_rows).  With one launch that
+// spread the rows over the compute units (M = few_rows).  With one launch that
 // adds partial spectra and another that transforms their columns in place of
 // the groups doing so themselves: denoise of one 512^2 image 103.6 us, now
 // 94.6; 16 x 256^2 in bf16, both directions, 281 and 275; 3 x 96 x 384 in fp16
@@ -1599,17 +1604,34 @@ static dim3 col_grid(int W, int y) {
   return dim3((W + CTile<N>::M - 1) / CTile<N>::M, y, 1);
 }
 
+// whether the rows of B planes take blocks of few_rows lines
+template <int N>
+static bool rows_few(const Sys2D &s, int B) {
+  const dim3 g = row_grid<N>(s.H, B);
+  return (long)g.x * g.y < s.num_cu;
+}
+
+template <int N, int MIX>
+static void rows_real_fft(const Sys2D &s, const float *x, float2 *A, float *bmax, const MixArgs &mix,
+                          int B, hipStream_t st) {
+  constexpr int M = few_rows<N>(), MT = Tile<N>::M;
+  if (rows_few<N>(s, B))
+    hipLaunchKernelGGL((k_rows_real_fft<N, MIX, M>), dim3((s.H + M - 1) / M, B),
+                       dim3(M * Tile<N>::NT), 0, st, x, A, bmax, s.H, s.twW, mix, B);
+  else
+    hipLaunchKernelGGL((k_rows_real_fft<N, MIX, MT>), row_grid<N>(s.H, B), dim3(Tile<N>::THREADS),
+                       0, st, x, A, bmax, s.H, s.twW, mix, B);
+}
+
 hipError_t launch_rows_real_fft_mix(const Sys2D &s, const MixArgs &mix, float2 *A, int B,
                                     hipStream_t st) {
   switch (s.W) {
-#define X(N)                                                                                  \
-  case N:                                                                                     \
-    if (mix.first)                                                                            \
-      hipLaunchKernelGGL((k_rows_real_fft<N, 1>), row_grid<N>(s.H, B), dim3(Tile<N>::THREADS), \
-                         0, st, nullptr, A, nullptr, s.H, s.twW, mix, B);                     \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_rows_real_fft<N, 2>), row_grid<N>(s.H, B), dim3(Tile<N>::THREADS), \
-                         0, st, nullptr, A, nullptr, s.H, s.twW, mix, B);                     \
+#define X(N)                                                        \
+  case N:                                                           \
+    if (mix.first)                                                  \
+      rows_real_fft<N, 1>(s, nullptr, A, nullptr, mix, B, st);      \
+    else                                                            \
+      rows_real_fft<N, 2>(s, nullptr, A, nullptr, mix, B, st);      \
     break;
     SL_FOR_EACH_N(X)
 #undef X
@@ -1622,10 +1644,9 @@ hipError_t launch_rows_real_fft_mix(const Sys2D &s, const MixArgs &mix, float2 *
 hipError_t launch_rows_real_fft(const Sys2D &s, const float *x, float2 *A, float *bmax, int B,
                                 hipStream_t st) {
   switch (s.W) {
-#define X(N)                                                                                  \
-  case N:                                                                                     \
-    hipLaunchKernelGGL((k_rows_real_fft<N, 0>), row_grid<N>(s.H, B), dim3(Tile<N>::THREADS), 0, \
-                       st, x, A, bmax, s.H, s.twW, MixArgs{}, 0);                             \
+#define X(N)                                                        \
+  case N:                                                           \
+    rows_real_fft<N, 0>(s, x, A, bmax, MixArgs{}, B, st);           \
     break;
     SL_FOR_EACH_N(X)
 #undef X
@@ -1635,11 +1656,12 @@ hipError_t launch_rows_real_fft(const Sys2D &s, const float *x, float2 *A, float
   return hipGetLastError();
 }
 
-int rows_real_blocks(const Sys2D &s) {
+int rows_real_blocks(const Sys2D &s, int B) {
   switch (s.W) {
-#define X(N) \
-  case N:    \
-    return (int)row_grid<N>(s.H, 1).x;
+#define X(N)                                                                          \
+  case N:                                                                             \
+    return rows_few<N>(s, B) ? (s.H + few_rows<N>() - 1) / few_rows<N>()              \
+                             : (int)row_grid<N>(s.H, 1).x;
     SL_FOR_EACH_N(X)
 #undef X
     default:
@@ -1647,23 +1669,37 @@ int rows_real_blocks(const Sys2D &s) {
   }
 }
 
+template <int N, bool INV, bool NT_>
+static void cols_fft(const Sys2D &s, const float2 *A, float2 *F, int B, const ScaleArgs &sc,
+                     hipStream_t st) {
+  const dim3 g = col_grid<N>(s.W, B);
+  if constexpr (!NT_) {
+    // fewer tiles than compute units: tiles of half the columns (measured at
+    // few_rows)
+    constexpr int M = CTile<N>::M / 2;
+    if ((long)g.x * g.y < s.num_cu) {
+      hipLaunchKernelGGL((k_cols_fft<N, INV, NT_, M>), dim3((s.W + M - 1) / M, B),
+                         dim3(M * CTile<N>::NT), 0, st, A, F, s.W, s.twH, sc);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_cols_fft<N, INV, NT_>), g, dim3(CTile<N>::THREADS), 0, st, A, F, s.W,
+                     s.twH, sc);
+}
+
 hipError_t launch_cols_fft(const Sys2D &s, const float2 *A, float2 *F, int B, bool inverse,
                            hipStream_t st, bool stream, const ScaleArgs &sc) {
   switch (s.H) {
-#define X(N)                                                                                  \
-  case N:                                                                                     \
-    if (inverse && stream)                                                                    \
-      hipLaunchKernelGGL((k_cols_fft<N, true, true>), col_grid<N>(s.W, B),                    \
-                         dim3(CTile<N>::THREADS), 0, st, A, F, s.W, s.twH, sc);               \
-    else if (inverse)                                                                         \
-      hipLaunchKernelGGL((k_cols_fft<N, true, false>), col_grid<N>(s.W, B),                   \
-                         dim3(CTile<N>::THREADS), 0, st, A, F, s.W, s.twH, sc);               \
-    else if (stream)                                                                          \
-      hipLaunchKernelGGL((k_cols_fft<N, false, true>), col_grid<N>(s.W, B),                   \
-                         dim3(CTile<N>::THREADS), 0, st, A, F, s.W, s.twH, sc);               \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_cols_fft<N, false, false>), col_grid<N>(s.W, B),                  \
-                         dim3(CTile<N>::THREADS), 0, st, A, F, s.W, s.twH, sc);               \
+#define X(N)                                             \
+  case N:                                                \
+    if (inverse && stream)                               \
+      cols_fft<N, true, true>(s, A, F, B, sc, st);       \
+    else if (inverse)                                    \
+      cols_fft<N, true, false>(s, A, F, B, sc, st);      \
+    else if (stream)                                     \
+      cols_fft<N, false, true>(s, A, F, B, sc, st);      \
+    else                                                 \
+      cols_fft<N, false, false>(s, A, F, B, sc, st);     \
     break;
     SL_FOR_EACH_N(X)
 #undef X
@@ -2039,7 +2075,7 @@ hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, const float2 *
   switch (s.W) {
 #define X(N)                                                                                   \
   case N: {                                                                                    \
-    constexpr int M = sum_rows<N>(), MT = Tile<N>::M;                                          \
+    constexpr int M = few_rows<N>(), MT = Tile<N>::M;                                          \
     if (G > 1)                                                                                 \
       hipLaunchKernelGGL((k_rows_real_ifft<N, M>), dim3((s.H + M - 1) / M, B),                 \
                          dim3(M *Tile<N>::NT), 0, st, V, part, G, pstride, x, s.H, inv_hw,     \

@@ -415,7 +415,8 @@ def test_streamed_accumulation(monkeypatch, dims, J, levels, Bn, chunk_mb):
 
 @pytest.mark.parametrize("dims,J,levels", [
     ((12, 24), 1, [1]), ((96, 16), 1, [1]), ((8, 48), 1, [1]), ((384, 48), 2, [1, 1]),
-    ((1024, 12), 1, [1]), ((96, 768), 2, [1, 1]), ((12, 16, 24), 1, [1]), ((24, 12, 96), 1, [1])])
+    ((1024, 12), 1, [1]), ((96, 768), 2, [1, 1]), ((12, 16, 24), 1, [1]), ((24, 12, 96), 1, [1]),
+    ((96, 48, 16), 1, [1])])
 def test_storage_scales(dims, J, levels):
     """Scales of 16-bit storage from the row blocks' maxima: partial wavefronts,
     one and many blocks per image, volumes; an extreme value in the first and
