@@ -1049,19 +1049,36 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
 // are bitwise those of the separate passes.  Slices of H x W with
 // H * row_lds_len(W) * 8 bytes of LDS (128 x 128: 144 KiB).
 // ---------------------------------------------------------------------------
-template <int H, int W>
+// Column lines lie inside a wave, so that columns need no block barriers; where
+// the y pass's plan has more than 8 threads per line, the radices are spread
+// over half of them: loads and stores of a wave stay 64 bytes wide.  Against
+// column tiles across the block: 128^3 (R = 99) forward rows 392 -> 365 us,
+// both directions of 96^3 691 -> 651, of 64 x 128 x 64 in fp16 322 -> 292.
+// The denoiser's pass (THR) loads and stores whole slices around its transforms
+// and keeps tiles across the block, of twice the waves, where a CU holds one
+// block of such a plan (128^3 denoised: 1282 us, with lines inside waves 1426;
+// 64 x 128 x 64, two blocks per CU: 329 -> 295).
+template <int H, int W, bool THR = false>
 struct PlaneTile {
   static constexpr int RL = row_lds_len<W>();
-  using PC = typename CTile<H>::PL;   // the y pass's plan
+  static constexpr size_t LDS = (size_t)H * RL * sizeof(float2);
+  static constexpr bool LONG = Plan<H>::NT > 8;
+  static constexpr bool WAVE = !(THR && LONG && LDS > 80 * 1024);
+  using PC = Plan<H, (WAVE && LONG ? 2 : 1)>;
   static constexpr int NTC = PC::NT, EC = PC::E;
   static constexpr int NTR = Plan<W>::NT, ER = Plan<W>::E;
   static constexpr int mn(int a, int b) { return a < b ? a : b; }
   // threads: every column (row) of a pass has its own NTC (NTR) threads
-  static constexpr int THREADS = mn(1024, mn(NTC * W, NTR * H));
+  static constexpr int THREADS = mn(WAVE && LONG ? 512 : 1024, mn(NTC * W, NTR * H));
   static constexpr int MC = THREADS / NTC, MR = THREADS / NTR;
-  static constexpr size_t LDS = (size_t)H * RL * sizeof(float2);
+  static constexpr int MW = WAVE ? 64 / NTC : MC;    // neighbouring columns of a row access
+  static __device__ __forceinline__ int col_of(int tid) {
+    return WAVE ? tid / 64 * MW + tid % MW : tid % MC;
+  }
+  static __device__ __forceinline__ int row_of(int tid) { return WAVE ? tid % 64 / MW : tid / MC; }
   static constexpr bool OK = LDS <= 150 * 1024 && THREADS % 64 == 0 && W % MC == 0 &&
-                             H % MR == 0 && THREADS % NTC == 0 && THREADS % NTR == 0;
+                             H % MR == 0 && THREADS % NTC == 0 && THREADS % NTR == 0 &&
+                             (!WAVE || wave_lines<NTC>());
 };
 
 template <int H, int W>
@@ -1076,16 +1093,16 @@ __device__ __forceinline__ LdsLine plane_row(float2 *pl, int y) {
 // y-line FFT of every column of the slice in LDS, in place
 template <int H, int W, bool INV>
 __device__ __forceinline__ void plane_cols(float2 *pl, const float2 *__restrict__ twH) {
-  using PT = PlaneTile<H, W>;
-  const int m = threadIdx.x % PT::MC, t = threadIdx.x / PT::MC;
+  using PT = PlaneTile<H, W, true>;
+  const int m = PT::col_of(threadIdx.x), t = PT::row_of(threadIdx.x);
 #pragma unroll 1
   for (int c0 = 0; c0 < W; c0 += PT::MC) {
     const LdsLine col = plane_col<H, W>(pl, c0 + m);
     float2 v[PT::EC];
 #pragma unroll
     for (int e = 0; e < PT::EC; ++e) v[e] = col[t + e * PT::NTC];
-    fft_line_p<typename PT::PC, INV>(v, t, col, twH);
-    __syncthreads();   // every read of the last exchange precedes the write-back
+    fft_line_p<typename PT::PC, INV, PT::WAVE>(v, t, col, twH);
+    line_sync<PT::WAVE>();   // every read of the last exchange precedes the write-back
 #pragma unroll
     for (int e = 0; e < PT::EC; ++e) col[t + e * PT::NTC] = v[e];
   }
@@ -1110,7 +1127,7 @@ k_plane_coef(const float2 *__restrict__ T, typename Store<DT>::T *__restrict__ c
   __shared__ float2 pl[H * PT::RL];
   const int items = D * np * nb;
   const size_t slice = (size_t)H * W, vol = slice * D;
-  const int mc = threadIdx.x % PT::MC, tc = threadIdx.x / PT::MC;
+  const int mc = PT::col_of(threadIdx.x), tc = PT::row_of(threadIdx.x);
   // column (ci, mc) of item i, values y = tc + e NTC: wave-uniform bases,
   // one 32-bit lane offset
   const unsigned lo = (unsigned)(tc * W + mc) * (unsigned)sizeof(float2);
@@ -1134,8 +1151,8 @@ k_plane_coef(const float2 *__restrict__ T, typename Store<DT>::T *__restrict__ c
       const int ni = last ? i + (int)gridDim.x : i;
       if (ni < items) fetch(nxt, ni, last ? 0 : ci + 1);
       const LdsLine col = plane_col<H, W>(pl, ci * PT::MC + mc);
-      fft_line_p<typename PT::PC, true>(cur, tc, col, twH);
-      __syncthreads();
+      fft_line_p<typename PT::PC, true, true>(cur, tc, col, twH);
+      line_sync<true>();
 #pragma unroll
       for (int e = 0; e < PT::EC; ++e) col[tc + e * PT::NTC] = cur[e];
 #pragma unroll
@@ -1204,7 +1221,7 @@ k_plane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *__
   Raw ca_[PT::ER], cb_[PT::ER], na[PT::ER], nb_[PT::ER];
   int i = blockIdx.x;
   if (i < items) fetch(ca_, cb_, i, 0);
-  const int mc = threadIdx.x % PT::MC, tc = threadIdx.x / PT::MC;
+  const int mc = PT::col_of(threadIdx.x), tc = PT::row_of(threadIdx.x);
   for (; i < items; i += gridDim.x) {
     const int z = i % D, pp = (i / D) % np, bl = i / (D * np), b = b0 + bl;
     const int ia = 2 * (p0 + pp), ib = ia + 1;
@@ -1241,7 +1258,7 @@ k_plane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *__
       }
       const LdsLine row = plane_row<H, W>(pl, ri * PT::MR + m);
       fft_line<W, false>(v, t, row, twW);
-      __syncthreads();
+      line_sync<wave_lines<Plan<W>::NT>()>();
 #pragma unroll
       for (int e = 0; e < PT::ER; ++e) row[t + e * PT::NTR] = v[e];
 #pragma unroll
@@ -1260,7 +1277,7 @@ k_plane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *__
       float2 v[PT::EC];
 #pragma unroll
       for (int e = 0; e < PT::EC; ++e) v[e] = col[tc + e * PT::NTC];
-      fft_line_p<typename PT::PC, false>(v, tc, col, twH);
+      fft_line_p<typename PT::PC, false, true>(v, tc, col, twH);
 #pragma unroll
       for (int e = 0; e < PT::EC; ++e) Us[(size_t)(tc + e * PT::NTC) * W + x] = v[e];
     }
@@ -1270,10 +1287,10 @@ k_plane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *__
 // fused denoise: y IDFT, x IDFT, scale, hard threshold, x DFT, y DFT of one
 // slice, in place
 template <int H, int W>
-__global__ void __launch_bounds__((PlaneTile<H, W>::THREADS))
+__global__ void __launch_bounds__((PlaneTile<H, W, true>::THREADS))
 k_plane_thr(float2 *__restrict__ T, int D, int R, int b0, int p0, int np, float inv_n,
             ThrArgs thr, const float2 *__restrict__ twH, const float2 *__restrict__ twW) {
-  using PT = PlaneTile<H, W>;
+  using PT = PlaneTile<H, W, true>;
   __shared__ float2 pl[H * PT::RL];
   const int z = blockIdx.x, pp = blockIdx.y, bl = blockIdx.z, b = b0 + bl;
   const int ia = 2 * (p0 + pp), ib = ia + 1;
@@ -1312,7 +1329,7 @@ k_plane_thr(float2 *__restrict__ T, int D, int R, int b0, int p0, int np, float 
       v[e] = make_float2(a, bb);
     }
     fft_line<W, false>(v, t, row, twW);
-    __syncthreads();
+    line_sync<wave_lines<Plan<W>::NT>()>();
 #pragma unroll
     for (int e = 0; e < PT::ER; ++e) row[t + e * PT::NTR] = v[e];
   }
@@ -1360,6 +1377,13 @@ struct HalfTile {
   static constexpr int THREADS = pick();
   static constexpr int MC = THREADS ? THREADS / NTC : 1, MR = THREADS ? THREADS / NTR : 1;
   static constexpr size_t LDS = (size_t)HH * RL * sizeof(float2);
+  // Column lines lie inside a wave, MW columns by NTC threads: neither lines nor
+  // columns need block barriers, so the waves' LDS and vector work overlap
+  // (each took 38% and 36% of the cycles, one after the other).  Against column
+  // tiles across the block, whose loads and stores are 512 instead of 64 bytes
+  // wide: 7008 slices of 192 x 192 forward 1349 -> 1238 us, inverse 1150 -> 1050.
+  static constexpr int MW = 64 / NTC;
+  static_assert(wave_lines<NTC>() && wave_lines<NTR>(), "lines inside a wave");
   static constexpr bool OK = H % 2 == 0 && THREADS > 0 && LDS <= 156 * 1024 && W % 16 == 0;
 };
 
@@ -1398,7 +1422,7 @@ k_hplane_coef(const float2 *__restrict__ T, typename Store<DT>::T *__restrict__ 
   const int G = gridDim.x;
   const int nslice = D * np * nb, items = 2 * nslice;
   const size_t slice = (size_t)H * W, vol = slice * D;
-  const int mc = threadIdx.x % HT::MC, tc = threadIdx.x / HT::MC;
+  const int mc = (int)threadIdx.x / 64 * HT::MW + threadIdx.x % HT::MW, tc = threadIdx.x % 64 / HT::MW;
   const unsigned lo = (unsigned)(tc * W + mc) * (unsigned)sizeof(float2);
   // raw rows m = tc + e NTC and m + Hh of column ci of item i
   auto fetch = [&](float2 (&ra)[HT::EC], float2 (&rc)[HT::EC], int i, int ci) {
@@ -1433,8 +1457,8 @@ k_hplane_coef(const float2 *__restrict__ T, typename Store<DT>::T *__restrict__ 
         v[e] = h ? cmulconj(csub(ca_[e], cc_[e]), twd[tc + e * HT::NTC]) : cadd(ca_[e], cc_[e]);
       const int x = ci * HT::MC + mc;
       const LdsLine col{pl + x + (x >> 4), HT::RL};
-      fft_line_p<typename HT::PC, true>(v, tc, col, TwStep<2>{twH});
-      __syncthreads();
+      fft_line_p<typename HT::PC, true, true>(v, tc, col, TwStep<2>{twH});
+      line_sync<true>();
 #pragma unroll
       for (int e = 0; e < HT::EC; ++e) col[tc + e * HT::NTC] = v[e];
 #pragma unroll
@@ -1508,7 +1532,7 @@ k_hplane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *_
   Raw cur[4][HT::ER], nxt[4][HT::ER];
   int i = blockIdx.x;
   if (i < items) fetch(cur, i, 0);
-  const int mc = threadIdx.x % HT::MC, tc = threadIdx.x / HT::MC;
+  const int mc = (int)threadIdx.x / 64 * HT::MW + threadIdx.x % HT::MW, tc = threadIdx.x % 64 / HT::MW;
   for (; i < items; i += G) {
     int sl, h;
     half_item(i, G, items, sl, h);
@@ -1557,7 +1581,7 @@ k_hplane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *_
 #pragma unroll
         for (int e = 0; e < HT::ER; ++e) v[e] = cmul(v[e], w);
       }
-      __syncthreads();
+      line_sync<true>();
 #pragma unroll
       for (int e = 0; e < HT::ER; ++e) row[t + e * HT::NTR] = v[e];
 #pragma unroll
@@ -1574,7 +1598,7 @@ k_hplane_coef_fft(const typename Store<DT>::T *__restrict__ coef, const float *_
       float2 v[HT::EC];
 #pragma unroll
       for (int e = 0; e < HT::EC; ++e) v[e] = col[tc + e * HT::NTC];
-      fft_line_p<typename HT::PC, false>(v, tc, col, TwStep<2>{twH});
+      fft_line_p<typename HT::PC, false, true>(v, tc, col, TwStep<2>{twH});
 #pragma unroll
       for (int e = 0; e < HT::EC; ++e) Us[(size_t)(2 * (tc + e * HT::NTC) + h) * W + x] = v[e];
     }
@@ -2247,7 +2271,7 @@ hipError_t launch_plane_thr(const Sys2D &s, int D, float2 *T, float inv_n, Chunk
   if constexpr (plane_ok<h, w>())                                                               \
     if (s.H == h && s.W == w) {                                                                 \
       hipLaunchKernelGGL((k_plane_thr<h, w>), dim3(D, c.np, c.nb),                      \
-                         dim3(PlaneTile<h, w>::THREADS), 0, st, T, D, s.R, c.b0, c.p0, c.np,    \
+                         dim3(PlaneTile<h, w, true>::THREADS), 0, st, T, D, s.R, c.b0, c.p0, c.np,    \
                          inv_n, thr, s.twH, s.twW);                                             \
       return hipGetLastError();                                                                 \
     }

@@ -468,3 +468,20 @@ def test_pair_groups_finish(dims, J, levels, Bn):
         for b in range(Bn):
             ref = T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)
             assert rel(x[b], ref) < 1e-5, (split, b)
+
+
+@pytest.mark.parametrize("dims,J,levels,Bn", [
+    ((256, 256), 3, [1, 1, 2], 16), ((512, 512), 2, [1, 1], 5), ((768, 256), 2, [1, 1], 9),
+    ((1024, 256), 2, [1, 1], 12)])
+def test_forward_round_split(dims, J, levels, Bn):
+    """Forward column passes whose grids fill the device one and a few times
+    over (pair loop split by rounds of resident blocks), an odd last image:
+    sampled subbands of the first and the last image against the oracle."""
+    print(f"case: forward round split {dims} B={Bn}", flush=True)
+    x = np.random.default_rng(15).standard_normal((Bn, *dims)).astype(np.float32)
+    o = S.build_2d(dims, J, levels)
+    c, _ = B.System(dims, J, levels).forward(_gpu(x))
+    for b in (0, Bn - 1):
+        for i in range(0, c.shape[1], 3):
+            ref = T.forward_one(x[b].astype(np.float64), o.filters[i])
+            assert rel(c[b, i].cpu().numpy(), ref) < 1e-5, (b, i)

@@ -271,3 +271,28 @@ def test_3d_inverse_adjoint(monkeypatch, dims, J, levels, Bn, plane):
     lhs = np.sum(x.cpu().numpy().astype(np.float64) * r)
     rhs = np.sum(c * an)
     assert abs(lhs - rhs) < 1e-5 * np.linalg.norm(c) * np.linalg.norm(an)
+
+
+@pytest.mark.parametrize("dims,Bn", [((8, 128, 64), 1), ((48, 128, 64), 2)])
+def test_plane_passes_of_long_columns(monkeypatch, dims, Bn):
+    """Slices whose column plan is spread over half the threads (column lines
+    inside a wave): fewer slices than compute units and several per block.
+    Against the line passes to float32 rounding (relative 1e-6) and, one image,
+    against the oracle to 1e-5."""
+    print(f"case: plane passes of long columns {dims} B={Bn}", flush=True)
+    monkeypatch.setenv("SL_PLANE3D", "0")
+    lines = B.System(dims, 1, [1])
+    monkeypatch.delenv("SL_PLANE3D")
+    plane = B.System(dims, 1, [1])
+    x = np.random.default_rng(64).standard_normal((Bn, *dims))
+    xg, sig = _gpu(x), _gpu(np.full(Bn, 0.5))
+    ca, _ = lines.forward(xg)
+    cb, _ = plane.forward(xg)
+    pairs = [(ca, cb), (lines.inverse(ca), plane.inverse(ca)),
+             (lines.denoise_fused(xg, sig, [3.0]), plane.denoise_fused(xg, sig, [3.0]))]
+    torch.cuda.synchronize()
+    for a, b in pairs:
+        assert rel(b.cpu().numpy(), a.cpu().numpy()) < 1e-6
+    if Bn == 1:
+        o = S.build_3d(dims, 1, [1])
+        assert rel(cb[0].cpu().numpy(), T.forward(x[0], o.filters)) < 1e-5
