@@ -73,7 +73,6 @@ __device__ __forceinline__ int dt_step(int a0, int d) {
 }
 
 // Radix stage S of a column (fft_core.hpp's stages; exchanges inside the wave).
-// hf: byte offset of the column in its chunk.
 template <int N, int S_, bool INV>
 __device__ __forceinline__ void col_stage(float2 (&v)[DTile<N>::E], int t, unsigned char *buf, int k,
                                           const float2 *tw) {

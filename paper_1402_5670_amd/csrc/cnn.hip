@@ -163,7 +163,8 @@ k_conv3x3(const uint16_t *__restrict__ in, const uint16_t *__restrict__ Wp,
 // 12 rows keep both within two blocks' share.
 // One 512-thread block per CU holding all 72 operand registers per wave, nine
 // LDS operands per 16 pixels and 48-channel pixel strides: 16.4 ms per
-// 32 x 512^2 images; this form 12.9 ms (8 images: 4.1 -> 3.2 ms).
+// 32 x 512^2 images; this form 12.9 ms (8 images denoised with the
+// network: 4713 -> 3723 us).
 constexpr int FTH = 12, FTW = 32;
 constexpr int X0H = FTH + 6, X0W = FTW + 6;
 constexpr int H1H = FTH + 4, H1W = FTW + 4;
@@ -447,7 +448,7 @@ k_sum_partials(const float *__restrict__ partial, int n, float *__restrict__ out
 // its 9 taps x 2 channels packed into one K = 32 operand (taps = 1).
 __global__ void k_pack(const float *__restrict__ params, int J, int layer, int mode,
                        uint16_t *__restrict__ Wp, int NB) {
-  const int taps = mode >= 2 ? 1 : 9;
+  const int taps = mode == 2 ? 1 : 9;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;   // over J*taps*NB*64*8
   const int total = J * taps * NB * 64 * 8;
   if (idx >= total) return;
@@ -465,13 +466,6 @@ __global__ void k_pack(const float *__restrict__ params, int J, int layer, int m
   if (mode == 2) {
     const int tt = k >> 1, cc = k & 1;
     if (n < 32 && tt < 9) v = P[off[0] + (n * 2 + cc) * 9 + tt];
-  } else if (mode == 3) {
-    // layer 3 with the taps as output rows: row n = tap.  Column k of lane
-    // group kg = k / 8 is the channel that the layer-2 accumulators of that
-    // group hold: 4 kg + k % 8 for k % 8 < 4, else 16 + 4 kg + k % 8 - 4.
-    const int kg = k >> 3, kj = k & 7;
-    const int ch = kj < 4 ? 4 * kg + kj : 16 + 4 * kg + (kj - 4);
-    if (n < 9) v = P[off[2] + ch * 9 + n];
   } else if (mode == 0) {
     if (n < cout[l] && k < cin[l]) v = P[off[l] + (n * cin[l] + k) * 9 + t];
   } else {

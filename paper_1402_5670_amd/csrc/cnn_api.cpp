@@ -23,13 +23,12 @@ using sl::kCnnParams;
 constexpr size_t kPackLayer2 = 9 * 2 * 512;   // u16 per scale, two output blocks
 constexpr size_t kPackLayer1 = 9 * 1 * 512;   // one output block
 constexpr size_t kPackK1 = 2 * 512;             // layer 1, taps packed into K
-constexpr size_t kPackTaps3 = 512;              // layer 3, taps on the M axis
 constexpr int kErrBlocks = SL_SQERR_SCRATCH - 1;
 
 size_t al(size_t v) { return (v + 255) / 256 * 256; }
 
 struct Packed {
-  const uint16_t *w1, *w2, *w3, *w2t, *w3t, *w1k, *w3m;
+  const uint16_t *w1, *w2, *w3, *w2t, *w1k;
 };
 
 Packed packed_view(const void *base, int J) {
@@ -39,9 +38,7 @@ Packed packed_view(const void *base, int J) {
   v.w2 = v.w1 + J * kPackLayer2;
   v.w3 = v.w2 + J * kPackLayer2;
   v.w2t = v.w3 + J * kPackLayer1;
-  v.w3t = v.w2t + J * kPackLayer2;
-  v.w1k = v.w3t + J * kPackLayer2;
-  v.w3m = v.w1k + J * kPackK1;
+  v.w1k = v.w2t + J * kPackLayer2;
   return v;
 }
 
@@ -116,10 +113,9 @@ void plane_hw(const sl_system *s, int &H, int &W) {
 extern "C" {
 
 size_t sl_cnn_packed_bytes(int J) {
-  // w1, w2, w2t, w3t: two output blocks each; w3: one; w1k: packed layer 1;
-  // w3m: layer 3 with the taps as output rows
+  // w1, w2, w2t: two output blocks each; w3: one; w1k: packed layer 1
   if (J < 1) return 0;
-  return (size_t)J * (4 * kPackLayer2 + kPackLayer1 + kPackK1 + kPackTaps3) * sizeof(uint16_t);
+  return (size_t)J * (3 * kPackLayer2 + kPackLayer1 + kPackK1) * sizeof(uint16_t);
 }
 
 int sl_cnn_pack(const float *params_dev, int J, void *packed_dev, void *stream) {
@@ -132,9 +128,7 @@ int sl_cnn_pack(const float *params_dev, int J, void *packed_dev, void *stream) 
   CK(sl::cnn_pack(params_dev, J, 2, 0, (uint16_t *)v.w2, 2, st));
   CK(sl::cnn_pack(params_dev, J, 3, 0, (uint16_t *)v.w3, 1, st));
   CK(sl::cnn_pack(params_dev, J, 2, 1, (uint16_t *)v.w2t, 2, st));
-  CK(sl::cnn_pack(params_dev, J, 3, 1, (uint16_t *)v.w3t, 2, st));
   CK(sl::cnn_pack(params_dev, J, 1, 2, (uint16_t *)v.w1k, 2, st));
-  CK(sl::cnn_pack(params_dev, J, 3, 3, (uint16_t *)v.w3m, 1, st));
   return SL_OK;
 }
 

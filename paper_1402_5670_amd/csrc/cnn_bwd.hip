@@ -31,6 +31,12 @@
 // leaves two waves per SIMD.  The 3x3 convolutions stream down 16-pixel
 // strips: an input row's three shifted operands feed three output rows, a
 // third of the LDS reads of a convolution that reads nine operands per row.
+//
+// 4 x 512^2 images, 48 subbands each: one training step 34.5 ms with the
+// layer-by-layer passes (about 30 of it backward), 6.5 ms with this kernel
+// (4.5 ms; 29 thousand cycles a tile, 10 thousand of them matrix products: the
+// rest is the LDS traffic of the operands, the element work and the barriers
+// between the chain's steps).  One block of 8 waves per CU; 161 KB of LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

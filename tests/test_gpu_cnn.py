@@ -127,6 +127,30 @@ def test_fused_and_layerwise_inference_agree(monkeypatch, dims):
     assert rel(g1[:, 1:].cpu().numpy(), g2[:, 1:].cpu().numpy()) < 1e-3
 
 
+@pytest.mark.parametrize("dims,Bn", [((8, 16), 1), ((12, 32), 2), ((16, 64), 1), ((32, 12), 1),
+                                     ((24, 96), 2), ((48, 48), 1)])
+def test_cnn_forward_tiles_match_oracle(dims, Bn):
+    """Gains where the 12 x 32 tiles of the fused inference begin and end:
+    planes smaller than a tile, exactly one tile, ragged in both directions,
+    narrower than a strip.  Relative L2 1e-3 of the bfloat16 reference, as
+    above."""
+    print(f"case: cnn tiles {dims} J=2 B={Bn}", flush=True)
+    sysg, sig, c, params, pg = _setup(dims=dims, Bn=Bn, seed=22)
+    gains = torch.zeros_like(c)
+    B.Shrinkage(sysg, pg).apply(c, _gpu(sig), gains=gains)
+    torch.cuda.synchronize()
+    cn, gn = c.cpu().numpy().astype(np.float64), gains.cpu().numpy()
+    l2 = np.array([s[4] for s in sysg.subbands], dtype=np.float32)
+    num = den = 0.0
+    for b in range(Bn):
+        for i in range(1, sysg.R):
+            j = sysg.subbands[i][1]
+            g, _ = OC.forward(params[j], cn[b, i], float(sig[b]), float(l2[i]), bf16=True)
+            num += np.sum((gn[b, i] - g) ** 2)
+            den += np.sum(g ** 2)
+    assert np.sqrt(num / den) < 1e-3
+
+
 def test_cnn_backward_matches_oracle():
     print("case: cnn backward 64x64 J=2 B=2", flush=True)
     sysg, sig, c, params, pg = _setup(seed=3)
