@@ -57,11 +57,14 @@ constexpr bool em2_length() { return N == 1024; }
 // forward
 // ---------------------------------------------------------------------------
 // Lines per block of the rows of single planes (k_rows_real_fft,
-// k_rows_real_ifft) where tiles of Tile<N>::M lines are fewer than the compute
-// units: blocks of two waves, of a quarter of the lines or fewer.  With
-// narrower column tiles as well (cols_fft): row and column pass of a 512^2 image
-// 6.1 + 6.5 -> 4.7 + 4.8 us, 3 x 96 x 384 in fp16, both directions, 56.1 -> 54.4
-// us, 2 x 192 x 768 97.6 -> 92.9; no difference at 256 blocks and more.
+// k_rows_real_ifft) where tiles of Tile<N>::M lines are few: blocks of two
+// waves, of a quarter of the lines or fewer.  With narrower column tiles as
+// well (cols_fft): row and column pass of a 512^2 image 6.1 + 6.5 -> 4.7 + 4.8
+// us, 3 x 96 x 384 in fp16, both directions, 56.1 -> 54.4 us, 2 x 192 x 768
+// 97.6 -> 92.9.  The forward passes take them below a quarter of a block per
+// compute unit: between that and one block there is little to gain alone (3 x
+// 96 x 384 54.3 against 54.7), and four classes in one captured graph, whose
+// branches share the device, lose 0.7% (1936 against 1922 us).
 template <int N>
 constexpr int few_rows() { return Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT; }
 
@@ -1632,7 +1635,7 @@ static dim3 col_grid(int W, int y) {
 template <int N>
 static bool rows_few(const Sys2D &s, int B) {
   const dim3 g = row_grid<N>(s.H, B);
-  return (long)g.x * g.y < s.num_cu;
+  return (long)g.x * g.y < s.num_cu / 4;
 }
 
 template <int N, int MIX>
@@ -1698,10 +1701,9 @@ static void cols_fft(const Sys2D &s, const float2 *A, float2 *F, int B, const Sc
                      hipStream_t st) {
   const dim3 g = col_grid<N>(s.W, B);
   if constexpr (!NT_) {
-    // fewer tiles than compute units: tiles of half the columns (measured at
-    // few_rows)
+    // few tiles: tiles of half the columns (rule and figures at few_rows)
     constexpr int M = CTile<N>::M / 2;
-    if ((long)g.x * g.y < s.num_cu) {
+    if ((long)g.x * g.y < s.num_cu / 4) {
       hipLaunchKernelGGL((k_cols_fft<N, INV, NT_, M>), dim3((s.W + M - 1) / M, B),
                          dim3(M * CTile<N>::NT), 0, st, A, F, s.W, s.twH, sc);
       return;
