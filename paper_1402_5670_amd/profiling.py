@@ -21,7 +21,8 @@ from collections import defaultdict
 PKG = os.path.dirname(os.path.abspath(__file__))
 
 
-TRANSFORM_SOURCES = ("kernels2d.hip", "kernels3d.hip", "fft_core.hpp", "dispatch.hpp")
+TRANSFORM_SOURCES = ("kernels2d.hip", "acc2d.hip", "plane2d.hip", "kernels3d.hip", "fft_core.hpp",
+                     "tiles.hpp", "dispatch.hpp")
 
 
 def source_hash():
