@@ -139,7 +139,7 @@ k_cols_fft(const float2 *__restrict__ A, float2 *__restrict__ F, int W,
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = ok ? stream_load<NT_>(&A[base + (size_t)(t + e * NT) * W]) : make_float2(0.f, 0.f);
   // (one slice per image in 2D, sc.slices in 3D)
-  const bool scaling = sc.scales && blockIdx.y % sc.slices == 0 && col_tile() == 0;
+  const bool scaling = !INV && !NT_ && sc.scales && blockIdx.y % sc.slices == 0 && col_tile() == 0;
   const unsigned img = blockIdx.y / sc.slices;
   float mx = 0.f;
   if (scaling)
@@ -1016,7 +1016,7 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
 // the groups doing so themselves: denoise of one 512^2 image 103.6 us, now
 // 94.6; 16 x 256^2 in bf16, both directions, 281 and 275; 3 x 96 x 384 in fp16
 // 59.2 and 56.1.
-template <int N, int M>
+template <int N, int M, bool SUM>
 __global__ void __launch_bounds__(M *Tile<N>::NT)
 k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, int G,
                  size_t pstride, float *__restrict__ x, int H, float inv_hw,
@@ -1030,11 +1030,13 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
   float2 v[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = V[off + t + e * NT];
+  if constexpr (SUM) {
 #pragma unroll 4
-  for (int z = 1; z < G; ++z) {
-    const float2 *p = part + (size_t)(z - 1) * pstride + off + t;
+    for (int z = 1; z < G; ++z) {
+      const float2 *p = part + (size_t)(z - 1) * pstride + off + t;
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = cadd(v[e], p[e * NT]);
+      for (int e = 0; e < E; ++e) v[e] = cadd(v[e], p[e * NT]);
+    }
   }
   fft_line<N, true>(v, t, LdsLine{lds + m * row_lds_len<N>(), 0}, tw);
   if (ok) {
@@ -2103,11 +2105,11 @@ hipError_t launch_rows_real_ifft(const Sys2D &s, const float2 *V, const float2 *
   case N: {                                                                                    \
     constexpr int M = few_rows<N>(), MT = Tile<N>::M;                                          \
     if (G > 1)                                                                                 \
-      hipLaunchKernelGGL((k_rows_real_ifft<N, M>), dim3((s.H + M - 1) / M, B),                 \
+      hipLaunchKernelGGL((k_rows_real_ifft<N, M, true>), dim3((s.H + M - 1) / M, B),           \
                          dim3(M *Tile<N>::NT), 0, st, V, part, G, pstride, x, s.H, inv_hw,     \
                          s.twW);                                                               \
     else                                                                                       \
-      hipLaunchKernelGGL((k_rows_real_ifft<N, MT>), row_grid<N>(s.H, B),                       \
+      hipLaunchKernelGGL((k_rows_real_ifft<N, MT, false>), row_grid<N>(s.H, B),                \
                          dim3(Tile<N>::THREADS), 0, st, V, nullptr, 1, pstride, x, s.H, inv_hw, \
                          s.twW);                                                               \
     break;                                                                                     \
