@@ -18,6 +18,7 @@
 // and write whole rows; column passes move M adjacent columns per row.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "dispatch.hpp"
@@ -1810,7 +1811,10 @@ static int inv_tile_m(const Sys2D &s, int nb) {
 // 1024^2 image denoised 356 -> 305 us; 4 and 16 images of 256^2 5% and 7%),
 // and not where the device is full (32 x 512^2 470 -> 490 us for the pass, its
 // row segments come at 4.3 TB/s even without the transforms; 6 x 1024^2 537 ->
-// 620 us; 16 of 256 x 512 2% slower) or a 256-point image is alone (2%).
+// 620 us; 16 of 256 x 512 2% slower) or a 256-point image is alone (one image of
+// 256 x 512, 768, 1024, R = 17, thresholded inverse: line pass 23.9, 28.2, 35.7
+// us, streamed with as many groups 25.7, 28.2, 36.9, with twice 27.7, 31.0,
+// 37.6).
 static int acc_stream_blocks(const Sys2D &s, int nb) {
   const int bt = inv_bt(s, nb);
   return s.W / (s.H == 1024 ? 8 : 16) * ((nb + bt - 1) / bt);
@@ -1818,7 +1822,7 @@ static int acc_stream_blocks(const Sys2D &s, int nb) {
 static bool acc_stream(const Sys2D &s, int nb) {
   if (!cols_acc_stream_supported(s.H, s.W)) return false;
   const int blocks = acc_stream_blocks(s, nb);
-  if (s.H == 256) return blocks >= 32 && blocks < s.num_cu;
+  if (s.H == 256) return nb > 1 && blocks >= 32 && blocks < s.num_cu;
   return blocks < (s.H == 1024 ? s.num_cu / 2 + 1 : s.num_cu);
 }
 
@@ -1833,10 +1837,13 @@ int inv_pair_groups(const Sys2D &s, int nb, int np) {
     SL_FOR_EACH_N(X)
 #undef X
   }
-  // (the streaming kernel runs one block per compute unit, two at 256 points)
-  if (acc_stream(s, nb)) return pair_groups(s, acc_stream_blocks(s, nb), np, s.H > 256 ? 1 : 2, 16);
   const int bt = inv_bt(s, nb);
-  return pair_groups(s, ((s.W + M - 1) / M) * ((nb + bt - 1) / bt), np, 2, 16);
+  const int line = pair_groups(s, ((s.W + M - 1) / M) * ((nb + bt - 1) / bt), np, 2, 16);
+  if (!acc_stream(s, nb)) return line;
+  // The streaming kernel runs one block per compute unit, two at 256 points,
+  // and takes at most the groups of the line pass: every group is a plane per
+  // image of the workspace, which callers hold in arrays of a fixed size.
+  return std::min(line, pair_groups(s, acc_stream_blocks(s, nb), np, s.H > 256 ? 1 : 2, 16));
 }
 
 template <int N, int MW, int EM = 1>

@@ -80,3 +80,25 @@ def test_noalloc_rejects_inputs_beyond_the_array():
     assert b"static array" in B.lib().sl_last_error()
     torch.cuda.synchronize()
     assert bool((out == 7.0).all())
+
+
+@pytest.mark.parametrize("dims,J,levels,full", [
+    ((256, 512), 4, [3, 4, 4, 4], False), ((256, 768), 3, [2, 4, 4], True),
+    ((256, 1024), 3, [2, 3, 4], False)])
+def test_noalloc_one_wide_image_fits(dims, J, levels, full):
+    # one image of 256 lines whose pair planes nearly fill the array: the line
+    # pass's pair groups (512 / its 8-column tiles) leave room for it, and the
+    # accumulation with streamed tiles may not take more of them
+    print(f"case: noalloc fused denoise 1x{dims} J={J} {levels} full={full}", flush=True)
+    s = B.System(dims, J, levels, full_system=full)
+    plane, groups = 8 * dims[0] * dims[1], -(-512 // (dims[1] // 8))
+    line = (2 + (s.R + 1) // 2 + groups - 1) * plane
+    assert line <= SCRATCH < line + 8 * plane
+    assert s.workspace_bytes(1) <= line
+    K = [3.0] * J
+    x = torch.rand((1, *dims), generator=torch.Generator().manual_seed(3)).to(DEV)
+    g = torch.full((1,), 0.05, device=DEV)
+    got = s.denoise_fused_noalloc(x, g, K)
+    ref = s.denoise(x, g, K)
+    torch.cuda.synchronize()
+    assert _rel(got, ref) <= 1e-6
