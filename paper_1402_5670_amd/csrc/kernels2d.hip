@@ -1011,8 +1011,13 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
 
 // x = Re row IDFT(V), V the column pass's accumulator and, with G > 1 pair
 // groups, G - 1 partial sums after it (pstride values apart), added in group
-// order while the rows are loaded.  G > 1 has few images: blocks of two waves
-// spread the rows over the compute units (M = few_rows).  With one launch that
+// order, in 64 bits, while the rows are loaded.  (In 32 bits each addition
+// rounds at the size of the lowpass group's sum: relative error of the inverse
+// against 64 bits of 2 x 192^2 1.28e-7, 3 x 256 x 64 1.22e-7, where adding
+// partial spectra before one transform had 1.20e-7 and 1.14e-7; now 1.11e-7 and
+// 1.05e-7, for half a microsecond.)
+// G > 1 has few images: blocks of two waves spread the rows over the compute
+// units (M = few_rows).  With one launch that
 // adds partial spectra and another that transforms their columns in place of
 // the groups doing so themselves: denoise of one 512^2 image 103.6 us, now
 // 94.6; 16 x 256^2 in bf16, both directions, 281 and 275; 3 x 96 x 384 in fp16
@@ -1032,12 +1037,24 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = V[off + t + e * NT];
   if constexpr (SUM) {
+    double re[E], im[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      re[e] = v[e].x;
+      im[e] = v[e].y;
+    }
 #pragma unroll 4
     for (int z = 1; z < G; ++z) {
       const float2 *p = part + (size_t)(z - 1) * pstride + off + t;
 #pragma unroll
-      for (int e = 0; e < E; ++e) v[e] = cadd(v[e], p[e * NT]);
+      for (int e = 0; e < E; ++e) {
+        const float2 q = p[e * NT];
+        re[e] += q.x;
+        im[e] += q.y;
+      }
     }
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = make_float2((float)re[e], (float)im[e]);
   }
   fft_line<N, true>(v, t, LdsLine{lds + m * row_lds_len<N>(), 0}, tw);
   if (ok) {

@@ -515,3 +515,14 @@ def test_whole_plane_shares_precision(dims, J, levels, Bn):
     print(f"case: shares of whole planes {dims} B={Bn}", flush=True)
     split, whole = _split_errors(dims, J, levels, Bn, 6)
     assert split <= 1.01 * whole
+
+
+@pytest.mark.parametrize("dims,J,levels,Bn", [
+    ((96, 64), 3, [1, 1, 2], 1), ((192, 192), 3, [1, 1, 2], 2), ((256, 64), 3, [1, 1, 2], 3),
+    ((384, 384), 3, [1, 1, 2], 1)])
+def test_pair_group_sums_precision(dims, J, levels, Bn):
+    """Pair groups of the line passes, added by the row pass in 64 bits: as for
+    whole planes, no larger an error than the undivided sum's."""
+    print(f"case: sums of pair groups {dims} B={Bn}", flush=True)
+    split, whole = _split_errors(dims, J, levels, Bn, 3)
+    assert split <= 1.01 * whole
