@@ -1011,11 +1011,11 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
 
 // x = Re row IDFT(V), V the column pass's accumulator and, with G > 1 pair
 // groups, G - 1 partial sums after it (pstride values apart), added in group
-// order, in 64 bits, while the rows are loaded.  (In 32 bits each addition
-// rounds at the size of the lowpass group's sum: relative error of the inverse
-// against 64 bits of 2 x 192^2 1.28e-7, 3 x 256 x 64 1.22e-7, where adding
-// partial spectra before one transform had 1.20e-7 and 1.14e-7; now 1.11e-7 and
-// 1.05e-7, for half a microsecond.)
+// order while the rows are loaded, the first group last: it holds the lowpass,
+// whose values are of the size of the sum, and added first it would have every
+// further addition round at that size (relative error of the inverse against 64
+// bits of 2 x 192^2 1.28e-7, 3 x 256 x 64 1.22e-7, now 1.12e-7 and 1.06e-7; 1.20e-7 and
+// 1.14e-7 when partial spectra were added before one transform).
 // G > 1 has few images: blocks of two waves spread the rows over the compute
 // units (M = few_rows).  With one launch that
 // adds partial spectra and another that transforms their columns in place of
@@ -1037,16 +1037,13 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = V[off + t + e * NT];
   if constexpr (SUM) {
-    double re[E], im[E];
+    float2 w[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      re[e] = v[e].x;
-      im[e] = v[e].y;
-    }
+    for (int e = 0; e < E; ++e) w[e] = make_float2(0.f, 0.f);
     // the loads of Q groups are issued before the first addition waits for one;
     // past the last group they repeat it.  (Left to itself the compiler gave
     // rows of 16 to 64 samples a load, a wait and an addition at a time: inverse
-    // of 96 x 64, R = 17, 22.3 us, now 12.7; 3 x 256 x 64 in fp16 29.7, 21.7; Q =
+    // of 96 x 64, R = 17, 19.7 us, now 12.1; 3 x 256 x 64 in fp16 27.6, 21.2; Q =
     // 8 measured 0 to 5% slower.)
     constexpr int Q = 4;
     for (int z = 1; z < G; z += Q) {
@@ -1062,12 +1059,12 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
       for (int u = 0; u < Q; ++u)
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          re[e] += z + u < G ? q[u][e].x : 0.f;
-          im[e] += z + u < G ? q[u][e].y : 0.f;
+          w[e].x += z + u < G ? q[u][e].x : 0.f;
+          w[e].y += z + u < G ? q[u][e].y : 0.f;
         }
     }
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = make_float2((float)re[e], (float)im[e]);
+    for (int e = 0; e < E; ++e) v[e] = cadd(w[e], v[e]);
   }
   fft_line<N, true>(v, t, LdsLine{lds + m * row_lds_len<N>(), 0}, tw);
   if (ok) {

@@ -464,23 +464,24 @@ k_plane2_thr(Plane2Args a, const float *__restrict__ x, ThrArgs thr, MixArgs mix
   p2_result<H, W>(s, acc, a, b);
 }
 
-// x = the shares of G groups, added in group order in 64 bits; n samples per
-// image (grid (blocks, B)).  Blocks of one wave, a sample per lane: an image has
-// few, and x may be aligned to 4 bytes only.
+// x = the shares of G groups, the first one last; n samples per image (grid
+// (blocks, B)).  Blocks of one wave, a sample per lane: an image has few, and x
+// may be aligned to 4 bytes only.
 //
-// The lowpass pair's share is about x itself, so in 32 bits every further
-// addition rounds at the size of x: relative error against 64 bits of one 64 x
-// 64 image, R = 33, 1.36e-7 with 17 shares (1.14e-7 when partial spectra were
-// added before one transform), 0.94e-7 with 64-bit sums, which cost 0.1 us.
+// The first group's share, the lowpass's, is about x itself: added first, every
+// further addition would round at the size of x.  Relative error against 64 bits
+// of one 64 x 64 image, R = 33: 1.36e-7 with the lowpass share first, 0.97e-7 now
+// (1.14e-7 when partial spectra were added before one transform).
 __global__ void __launch_bounds__(64)
 k_plane2_sum(const float *__restrict__ part, float *__restrict__ x, int G, int n) {
   const int i = blockIdx.x * 64 + threadIdx.x;
   if (i >= n) return;
   const float *src = part + (size_t)blockIdx.y * G * n + i;
-  double v = src[0];
+  const float low = src[0];
+  float v = 0.f;
 #pragma unroll 8
   for (int g = 1; g < G; ++g) v += src[(size_t)g * n];
-  x[(size_t)blockIdx.y * n + i] = (float)v;
+  x[(size_t)blockIdx.y * n + i] = v + low;
 }
 
 static hipError_t launch_plane2_sum(const Plane2Args &a, int n, int G, int B, hipStream_t st) {

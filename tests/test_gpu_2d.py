@@ -508,10 +508,11 @@ def _split_errors(dims, J, levels, Bn, seeds):
 @pytest.mark.parametrize("dims,J,levels,Bn", [
     ((64, 64), 3, [1, 1, 2], 1), ((48, 48), 3, [1, 1, 2], 3), ((32, 64), 2, [1, 1], 2)])
 def test_whole_plane_shares_precision(dims, J, levels, Bn):
-    """Pair groups of whole planes: their shares of the image are added in 64
-    bits, so splitting the pair loop takes float32 additions away and the error
-    is no larger than the undivided sum's (1% for the spread of a mean over a
-    few images of some thousand samples)."""
+    """Pair groups of whole planes: their shares of the image are added with the
+    large one, the lowpass group's, last, so splitting the pair loop leaves fewer
+    additions that round at the size of the sum and the error is no larger than
+    the undivided sum's (1% for the spread of a mean over a few images of some
+    thousand samples)."""
     print(f"case: shares of whole planes {dims} B={Bn}", flush=True)
     split, whole = _split_errors(dims, J, levels, Bn, 6)
     assert split <= 1.01 * whole
@@ -521,8 +522,8 @@ def test_whole_plane_shares_precision(dims, J, levels, Bn):
     ((96, 64), 3, [1, 1, 2], 1), ((192, 192), 3, [1, 1, 2], 2), ((256, 64), 3, [1, 1, 2], 3),
     ((384, 384), 3, [1, 1, 2], 1)])
 def test_pair_group_sums_precision(dims, J, levels, Bn):
-    """Pair groups of the line passes, added by the row pass in 64 bits: as for
-    whole planes, no larger an error than the undivided sum's."""
+    """Pair groups of the line passes, added by the row pass: as for whole
+    planes, no larger an error than the undivided sum's."""
     print(f"case: sums of pair groups {dims} B={Bn}", flush=True)
     split, whole = _split_errors(dims, J, levels, Bn, 3)
     assert split <= 1.01 * whole
