@@ -23,28 +23,11 @@
 
 #include "dispatch.hpp"
 #include "fft_core.hpp"
+#include "launch_rules.hpp"
 #include "tiles.hpp"
 
 namespace sl {
 
-// Row tiles: M rows per block.  Column tiles: M adjacent columns per block;
-// with SL_COL_EMUL > 1 each thread of a column pass owns SL_COL_EMUL times
-// more values, halving the threads per column and doubling the columns per
-// block (wider coalesced segments) for lengths 256..512.
-// EM (line plan): each thread holds EM times the plan's values, so a line
-// takes EM times fewer threads (EM = 2 makes a 1024-point row one wavefront,
-// whose radix exchanges need no block barrier); the coefficient row passes
-// take it per system (sl_system_set_line_plan, autotuned for uneven
-// batches), and so does the inverse accumulation of 1024-point columns
-// (launch_cols_fft_acc); the other column passes keep EM = 1.
-template <int N, int EM = 1>
-struct Tile {
-  using PL = Plan<N, EM>;
-  static constexpr int NT = PL::NT;
-  static constexpr int E = PL::E;
-  static constexpr int M = NT >= 128 ? 8 : 16;     // lines per block
-  static constexpr int THREADS = M * NT;
-};
 // row FFT of a Tile line: wavefront-local exchanges when the line fits a wave
 template <int N, int EM, bool INV>
 __device__ __forceinline__ void row_fft(float2 (&v)[(Tile<N, EM>::E)], int t, const LdsLine &lds,
@@ -57,18 +40,6 @@ constexpr bool em2_length() { return N == 1024; }
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-// Lines per block of the rows of single planes (k_rows_real_fft,
-// k_rows_real_ifft) where tiles of Tile<N>::M lines are few: blocks of two
-// waves, of a quarter of the lines or fewer.  With narrower column tiles as
-// well (cols_fft): row and column pass of a 512^2 image 6.1 + 6.5 -> 4.7 + 4.8
-// us, 3 x 96 x 384 in fp16, both directions, 56.1 -> 54.4 us, 2 x 192 x 768
-// 97.6 -> 92.9.  The forward passes take them below a quarter of a block per
-// compute unit: between that and one block there is little to gain alone (3 x
-// 96 x 384 54.3 against 54.7), and four classes in one captured graph, whose
-// branches share the device, lose 0.7% (1936 against 1922 us).
-template <int N>
-constexpr int few_rows() { return Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT; }
-
 // MIX = 0: rows of x; MIX = 1 / 2: rows of the inpainting input (MixArgs),
 // first iteration / later ones.  bmax (16-bit storage): max |x| of each
 // block's rows, [image][block], which the column pass turns into the storage

@@ -1,0 +1,43 @@
+// Block shapes and grid splits of the 2D passes (internal, host side).
+#pragma once
+
+#include "fft_core.hpp"
+
+namespace sl {
+
+// Row tiles: M rows per block.
+// EM (line plan): each thread holds EM times the plan's values, so a line
+// takes EM times fewer threads (EM = 2 makes a 1024-point row one wavefront,
+// whose radix exchanges need no block barrier); the coefficient row passes
+// take it per system (sl_system_set_line_plan, autotuned for uneven
+// batches), and so does the inverse accumulation of 1024-point columns
+// (launch_cols_fft_acc); the other column passes keep EM = 1.
+template <int N, int EM = 1>
+struct Tile {
+  using PL = Plan<N, EM>;
+  static constexpr int NT = PL::NT;
+  static constexpr int E = PL::E;
+  static constexpr int M = NT >= 128 ? 8 : 16;     // lines per block
+  static constexpr int THREADS = M * NT;
+};
+
+// Lines per block of the rows of single planes (k_rows_real_fft,
+// k_rows_real_ifft) where tiles of Tile<N>::M lines are few: blocks of two
+// waves, a quarter of the lines for rows of 256 to 384 samples, an eighth from
+// 512 on, half for 128 and 192.  Shorter rows keep their tile, which is two waves
+// or less.  With narrower column tiles as well (cols_fft): row and column pass of
+// a 512^2 image 6.1 + 6.5 -> 4.7 + 4.8 us, 3 x 96 x 384 in fp16, both
+// directions, 56.1 -> 54.4 us, 2 x 192 x 768 97.6 -> 92.9.  (Rows of up to 48
+// samples in blocks of two waves, which take two to eight times the lines, for
+// the inverse, R = 17: 96 x 16 11.5 us against 10.8, 512 x 48 20.5 against
+// 19.6, 384 x 32 15.3 against 14.7.)  The forward passes take them below a quarter of
+// a block per compute unit: between that and one block there is little to gain
+// alone (3 x 96 x 384 54.3 against 54.7), and four classes in one captured graph,
+// whose branches share the device, lose 0.7% (1936 against 1922 us).
+template <int N>
+constexpr int few_rows() {
+  constexpr int two_waves = Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT;
+  return two_waves < Tile<N>::M ? two_waves : Tile<N>::M;
+}
+
+}  // namespace sl

@@ -10,6 +10,10 @@
 
 namespace sl {
 
+// Column tiles: M adjacent columns per block; with SL_COL_EMUL > 1 each thread
+// of a column pass owns SL_COL_EMUL times more values, halving the threads per
+// column and doubling the columns per block (wider coalesced segments) for
+// lengths 256..512.
 #ifndef SL_COL_EMUL
 #define SL_COL_EMUL 1
 #endif
