@@ -19,7 +19,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 
 #include "dispatch.hpp"
 #include "fft_core.hpp"
@@ -1751,41 +1750,6 @@ static int pair_groups(const Sys2D &s, int blocks, int np, int per_cu, int cap) 
   return (np + per - 1) / per;
 }
 
-// Blocks of a kernel resident on the device at once (0 if unknown); slot caches
-// the occupancy of the kernel instance.
-template <class Kernel>
-static long resident_blocks(Kernel k, int threads, int num_cu, std::atomic<int> &slot) {
-  int per = slot.load(std::memory_order_relaxed);
-  if (per < 0) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, threads, 0) != hipSuccess || n < 1) n = 1;
-    per = n;
-    slot.store(per, std::memory_order_relaxed);
-  }
-  return (long)per * num_cu;
-}
-
-// Parts to split a column pass's pair loop into when its grid has at least a
-// block per compute unit: blocks run their whole loop in one round, so a grid
-// that is not a multiple of the resident blocks leaves a partly idle last
-// round (6 x 1024^2: 384 blocks on 256, two rounds for one and a half).  The
-// split with the fewest rounds per unit of work wins; a further part has to
-// save 5%, since each re-reads its tile of the spectrum.
-static int round_split(long blocks, long resident, int np, int cap) {
-  int best = 1;
-  double best_cost = 1e30;
-  for (int sp = 1; sp <= cap && sp <= np; ++sp) {
-    const long per = (np + sp - 1) / sp;
-    if ((np + per - 1) / per != sp) continue;              // no empty part
-    const double cost = (double)((blocks * sp + resident - 1) / resident) * (double)per / np;
-    if (cost < 0.95 * best_cost) {
-      best_cost = cost;
-      best = sp;
-    }
-  }
-  return best;
-}
-
 // images per block of the inverse accumulation: the system's choice, else
 // two (one for a single image, which does not fill a two-image block)
 static int inv_bt(const Sys2D &s, int nb) {
@@ -1793,13 +1757,24 @@ static int inv_bt(const Sys2D &s, int nb) {
   return nb >= 2 ? kInvBT : 1;
 }
 
-// columns per block of the inverse accumulation pass
+// columns per block of the inverse accumulation's line pass, and its blocks
+// resident on the device at once
+struct InvTile {
+  int m;
+  long resident;
+};
+template <int N, int MW, int EM = 1>
+static InvTile inv_tile(const Sys2D &s, int bt) {
+  using IT = ITile<N, MW, EM>;
+  return {IT::M, bt == 1 ? resident_blocks<k_cols_fft_acc<N, 1, MW, EM>>(IT::THREADS, s.num_cu)
+                         : resident_blocks<k_cols_fft_acc<N, kInvBT, MW, EM>>(IT::THREADS, s.num_cu)};
+}
 template <int N>
-static int inv_tile_m(const Sys2D &s, int nb) {
+static InvTile inv_tile(const Sys2D &s, int nb, int bt) {
   if constexpr (em2_length<N>()) {
-    if (s.line_em == 2) return ITile<N, kInvNarrow, 2>::M;
+    if (s.line_em == 2) return inv_tile<N, kInvNarrow, 2>(s, bt);
   }
-  return nb == 1 ? ITile<N, kInvNarrow>::M : ITile<N, kInvWide>::M;
+  return nb == 1 ? inv_tile<N, kInvNarrow>(s, 1) : inv_tile<N, kInvWide>(s, bt);
 }
 
 // Whether the inverse accumulation takes the tile-streaming kernel (acc2d.hip),
@@ -1824,24 +1799,34 @@ static bool acc_stream(const Sys2D &s, int nb) {
   return blocks < (s.H == 1024 ? s.num_cu / 2 + 1 : s.num_cu);
 }
 
+// Every group divides and inverse transforms its own sum, about one more pair:
+// with groups up to the cap whatever the rounds, 3 x 384^2 (R = 17: nine groups
+// of one pair, two rounds of one block per compute unit) took 66.4 us per
+// inverse, 61.9 where one launch transformed the groups' sum, and takes 52.7
+// with five; 3 x 512 x 768 (96 streamed blocks, three groups in two rounds) took
+// 120.6, 115.9 and takes 103.8 with two.  The streaming kernel runs one block per
+// compute unit, two at 256 points.  Never more groups than the rule of the line
+// pass alone, two blocks per compute unit, allows: each is a plane per image of
+// the workspace, which callers hold in arrays of a fixed size.
 int inv_pair_groups(const Sys2D &s, int nb, int np) {
   if (SL_COL_V3_INV || !lines_supported(s.H)) return 1;
-  int M = 0;
+  const int bt = inv_bt(s, nb);
+  InvTile tile{};
   switch (s.H) {
 #define X(N) \
   case N:    \
-    M = inv_tile_m<N>(s, nb); \
+    tile = inv_tile<N>(s, nb, bt); \
     break;
     SL_FOR_EACH_N(X)
 #undef X
   }
-  const int bt = inv_bt(s, nb);
-  const int line = pair_groups(s, ((s.W + M - 1) / M) * ((nb + bt - 1) / bt), np, 2, 16);
-  if (!acc_stream(s, nb)) return line;
-  // The streaming kernel runs one block per compute unit, two at 256 points,
-  // and takes at most the groups of the line pass: every group is a plane per
-  // image of the workspace, which callers hold in arrays of a fixed size.
-  return std::min(line, pair_groups(s, acc_stream_blocks(s, nb), np, s.H > 256 ? 1 : 2, 16));
+  long blocks = (long)((s.W + tile.m - 1) / tile.m) * ((nb + bt - 1) / bt);
+  const int cap = pair_groups(s, (int)blocks, np, 2, 16);
+  if (acc_stream(s, nb)) {
+    blocks = acc_stream_blocks(s, nb);
+    tile.resident = (s.H > 256 ? 1L : 2L) * s.num_cu;
+  }
+  return round_split(blocks, tile.resident, np, 1, cap);
 }
 
 template <int N, int MW, int EM = 1>
@@ -1854,10 +1839,8 @@ static void launch_fwd3(const Sys2D &s, const float2 *F, float2 *T, Chunk c, hip
   const int tiles = (s.W + FT::M - 1) / FT::M, ny = (c.nb + BT - 1) / BT;
   int groups = pair_groups(s, tiles * ny, c.np, 4, 32);
   if (s.split_pairs && tiles * ny >= s.num_cu) {
-    static std::atomic<int> occ{-1};
-    groups = round_split((long)tiles * ny,
-                         resident_blocks(k_cols_filter_ifft3<N, BT, MW, EM>, FT::THREADS, s.num_cu, occ),
-                         c.np, 8);
+    const long resident = resident_blocks<k_cols_filter_ifft3<N, BT, MW, EM>>(FT::THREADS, s.num_cu);
+    groups = round_split((long)tiles * ny, resident, c.np, 0, 8);
   }
   hipLaunchKernelGGL((k_cols_filter_ifft3<N, BT, MW, EM>), dim3(tiles, ny, groups),
                      dim3(FT::THREADS), 0, st, F, s.filt, T, s.W, s.R, c.b0, c.nb, c.p0, c.np, s.twH);

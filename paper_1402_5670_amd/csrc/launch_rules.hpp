@@ -1,6 +1,10 @@
 // Block shapes and grid splits of the 2D passes (internal, host side).
 #pragma once
 
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+
 #include "fft_core.hpp"
 
 namespace sl {
@@ -38,6 +42,42 @@ template <int N>
 constexpr int few_rows() {
   constexpr int two_waves = Tile<N>::NT >= 128 ? 1 : 128 / Tile<N>::NT;
   return two_waves < Tile<N>::M ? two_waves : Tile<N>::M;
+}
+
+// Blocks of a kernel resident on the device at once; the occupancy of a kernel
+// instance is queried once (one block per compute unit if that fails).
+template <auto K>
+long resident_blocks(int threads, int num_cu) {
+  static std::atomic<int> slot{-1};
+  int per = slot.load(std::memory_order_relaxed);
+  if (per < 0) {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, threads, 0) != hipSuccess || n < 1) n = 1;
+    per = n;
+    slot.store(per, std::memory_order_relaxed);
+  }
+  return (long)per * num_cu;
+}
+
+// Parts to split the loop of a grid over np pairs into: blocks run their whole
+// loop in one round, so a grid that is not a multiple of the resident blocks
+// leaves a partly idle last round (6 x 1024^2: 384 blocks on 256, two rounds for
+// one and a half).  The split with the fewest rounds per unit of work wins, each
+// part costing `extra` pairs on top of its own; a further part has to save 5%,
+// since each re-reads or writes a tile.
+inline int round_split(long blocks, long resident, int np, int extra, int cap) {
+  int best = 1;
+  double best_cost = 1e30;
+  for (int sp = 1; sp <= cap && sp <= np; ++sp) {
+    const long per = (np + sp - 1) / sp;
+    if ((np + per - 1) / per != sp) continue;              // no empty part
+    const double cost = (double)((blocks * sp + resident - 1) / resident) * (double)(per + extra);
+    if (cost < 0.95 * best_cost) {
+      best_cost = cost;
+      best = sp;
+    }
+  }
+  return best;
 }
 
 }  // namespace sl

@@ -527,3 +527,22 @@ def test_pair_group_sums_precision(dims, J, levels, Bn):
     print(f"case: sums of pair groups {dims} B={Bn}", flush=True)
     split, whole = _split_errors(dims, J, levels, Bn, 3)
     assert split <= 1.01 * whole
+
+
+@pytest.mark.parametrize("dims,Bn,resident", [
+    ((512, 512), 6, 256), ((512, 128), 24, 256), ((1024, 384), 3, 256), ((512, 256), 8, 256),
+    ((256, 256), 16, 512)])
+def test_pair_groups_fill_rounds(dims, Bn, resident):
+    """Pair groups of the streamed accumulation: one block per compute unit, two
+    at 256 lines, each group's blocks take its pairs and about one more to finish
+    its sum; no other group count up to the chosen one takes less than 0.95 of
+    its rounds.  Read from the workspace, which holds a plane per image for every
+    group after the first."""
+    print(f"case: pair groups of {dims} B={Bn}", flush=True)
+    sysg = B.System(dims, 2, [1, 1])
+    P, plane = (sysg.R + 1) // 2, 8 * dims[0] * dims[1] * Bn
+    G = sysg.workspace_bytes(Bn) // plane - 2 - P + 1
+    blocks = dims[1] // (8 if dims[0] == 1024 else 16) * ((Bn + 1) // 2)
+    cost = {g: -(-blocks * g // resident) * (-(-P // g) + 1) for g in range(1, P + 1)}
+    print(f"{blocks} blocks, {G} groups of {P} pairs, cost {cost}", flush=True)
+    assert 1 <= G <= P and all(cost[g] >= 0.95 * cost[G] for g in range(1, G + 1))
