@@ -393,9 +393,10 @@ int sl_multi_graph_launch(sl_multi *m, void *stream);
  *   with zero padding, 2 -> 32 -> 32 -> 1 channels; output g * c.
  * Parameters: params_dev [J][SL_CNN_PARAMS] float32, one blob per scale:
  *   W1[32][2][9] b1[32] W2[32][32][9] b2[32] W3[1][32][9] b3[1], weights
- *   indexed [out][in][3 dy + dx].  The matrix-core kernels read bfloat16
- *   operand copies built by sl_cnn_pack (call it after every update); they
- *   accumulate in float32.  Coefficients must be SL_F32; 2D systems only.    */
+ *   indexed [out][in][3 dy + dx].  The matrix-core kernels read the weights as
+ *   bfloat16 operand copies built by sl_cnn_pack (call it after every update)
+ *   and the biases from params_dev; they accumulate in float32.  Coefficients
+ *   must be SL_F32; 2D systems only.                                          */
 #define SL_CNN_PARAMS 10145
 size_t sl_cnn_packed_bytes(int J);
 int sl_cnn_pack(const float *params_dev, int J, void *packed_dev, void *stream);

@@ -196,8 +196,8 @@ __device__ __forceinline__ FusedTile fused_tile(const CnnPlanes &pl, int tile, i
 __global__ void __launch_bounds__(kFusedThreads, 4)
 k_cnn_fused(const float *__restrict__ coef, CnnPlanes pl, int H, int W, int ntiles,
             const uint16_t *__restrict__ W1k, const uint16_t *__restrict__ W2p,
-            const float *__restrict__ params, float *__restrict__ coef_out,
-            float *__restrict__ gain) {
+            const uint16_t *__restrict__ W3p, const float *__restrict__ params,
+            float *__restrict__ coef_out, float *__restrict__ gain) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsFused];
   float *d3 = (float *)(smem + kFOD3);
   uint32_t *x0s = (uint32_t *)(smem + kFOX0);
@@ -256,11 +256,12 @@ k_cnn_fused(const float *__restrict__ coef, CnnPlanes pl, int H, int W, int ntil
     for (int t = 0; t < 9; ++t)
       w2[t] = *(const bf16x8 *)(W2p + ((((size_t)j * 9 + t) * 2 + nb) * 64 + lane) * 8);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      bias2[e] = P[kOffB2 + 16 * nb + 4 * g0 + e];
-      // layer 3, taps on M, this wave's 16 channels on K: row n, k = 4 g + e
-      w3[e] = n0 < 9 ? (short)f2bf(P[kOffW3 + (16 * nb + 4 * g0 + e) * 9 + n0]) : (short)0;
-    }
+    for (int e = 0; e < 4; ++e) bias2[e] = P[kOffB2 + 16 * nb + 4 * g0 + e];
+    // layer 3, taps on M, this wave's 16 channels on K: row n, k = 4 g + e (four
+    // channels of a tap lie together in the pack)
+    const int tap = fresh(n0);
+    w3 = s16x4{0, 0, 0, 0};
+    if (tap < 9) w3 = *(const s16x4 *)packed_w3(W3p, j, 16 * nb + 4 * fresh(g0), tap);
     b3 = P[kOffB3];
   };
   // relu and layer 3 of 16 pixels at d3 index q of lane n
@@ -519,14 +520,15 @@ hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float 
 }
 
 hipError_t cnn_fused(const float *coef, const CnnPlanes &pl, int P, int H, int W,
-                     const uint16_t *W1k, const uint16_t *W2p, const float *params,
-                     float *coef_out, float *gain, int nblocks, hipStream_t st) {
+                     const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W3p,
+                     const float *params, float *coef_out, float *gain, int nblocks,
+                     hipStream_t st) {
   const int ntiles = P * ((W + FTW - 1) / FTW) * ((H + FTH - 1) / FTH);
   nblocks *= kFusedBlocksPerCU;
   const int grid = nblocks < ntiles ? nblocks : ntiles;
   if (grid < 1) return hipSuccess;
   hipLaunchKernelGGL(k_cnn_fused, dim3(grid), dim3(kFusedThreads), 0, st, coef, pl, H, W, ntiles,
-                     W1k, W2p, params, coef_out, gain);
+                     W1k, W2p, W3p, params, coef_out, gain);
   return hipGetLastError();
 }
 

@@ -38,6 +38,18 @@ __device__ __forceinline__ void plane_info(const CnnPlanes &pl, int p, int &b, i
   i = pl.first[j] + q % pl.nsub[j];
 }
 
+// Weights come from the packed operands, biases from params.  Packed element of
+// layer 3's channel ci and tap t (W3p) and of layer 1's output channel co, input
+// channel c and tap t (W1k) of scale j, for kernels whose operands lie another
+// way round than the packs.
+__device__ __forceinline__ const uint16_t *packed_w3(const uint16_t *W3p, int j, int ci, int t) {
+  return W3p + (j * 9 + t) * 512 + (ci >> 3) * 128 + (ci & 7);
+}
+__device__ __forceinline__ uint16_t packed_w1(const uint16_t *W1k, int j, int co, int c, int t) {
+  const int k = 2 * t + c;
+  return W1k[(2 * j + (co >> 4)) * 512 + ((k >> 3) * 16 + (co & 15)) * 8 + (k & 7)];
+}
+
 hipError_t cnn_x0(const float *coef, const CnnPlanes &pl, int P, int H, int W, uint16_t *x0,
                   hipStream_t st);
 hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float *bias,
@@ -47,8 +59,9 @@ hipError_t cnn_conv(const uint16_t *in, const uint16_t *Wp, int NB, const float 
 // fused inference over P planes; a persistent grid (two blocks per
 // compute unit; nblocks = compute units) walks the output tiles
 hipError_t cnn_fused(const float *coef, const CnnPlanes &pl, int P, int H, int W,
-                     const uint16_t *W1k, const uint16_t *W2p, const float *params,
-                     float *coef_out, float *gain, int nblocks, hipStream_t st);
+                     const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W3p,
+                     const float *params, float *coef_out, float *gain, int nblocks,
+                     hipStream_t st);
 // Blocks of the fused backward kernel: scale j owns blocks
 // [first[j], first[j + 1]); cnn_bwd_blocks fills bk and returns their number
 // (one partial gradient of kCnnParams floats each).
@@ -58,8 +71,9 @@ struct CnnBwdBlocks {
 int cnn_bwd_blocks(const CnnPlanes &pl, int H, int W, int num_cu, CnnBwdBlocks &bk);
 // weight gradients grads [J][kCnnParams] from coefficients and dL/d(coef_out)
 hipError_t cnn_bwd(const float *coef, const float *dcoef, const CnnPlanes &pl, int H, int W,
-                   const uint16_t *W2p, const uint16_t *W2tp, const float *params, int num_cu,
-                   float *partial, float *grads, hipStream_t st);
+                   const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W2tp,
+                   const uint16_t *W3p, const float *params, int num_cu, float *partial,
+                   float *grads, hipStream_t st);
 hipError_t cnn_pack(const float *params, int J, int layer, int mode, uint16_t *Wp, int NB,
                     hipStream_t st);
 hipError_t cnn_adam(float *p, const float *g, float *m, float *v, int n, float lr, double b1,

@@ -164,8 +164,8 @@ int sl_cnn_apply(const sl_system *s, const float *params_dev, const void *packed
   sl::CnnPlanes pl0 = planes(s, batch, sigma_dev);
   if (!layerwise()) {
     CK(sl::cnn_copy_lowpass(coeffs_dev, coeffs_out_dev, batch, s->R, (int)s->cfg.npix(), st));
-    CK(sl::cnn_fused(coeffs_dev, pl0, P, H, W, pk.w1k, pk.w2, params_dev, coeffs_out_dev,
-                     gains_dev, s->num_cu, st));
+    CK(sl::cnn_fused(coeffs_dev, pl0, P, H, W, pk.w1k, pk.w2, pk.w3, params_dev,
+                     coeffs_out_dev, gains_dev, s->num_cu, st));
     return SL_OK;
   }
   uint16_t *A = (uint16_t *)workspace_dev;
@@ -205,8 +205,8 @@ int sl_cnn_backward(const sl_system *s, const float *params_dev, const void *pac
   sl::CnnPlanes pl = planes(s, batch, sigma_dev);
   for (int j = 0; j < s->cfg.J; ++j)
     if (pl.start[j + 1] == pl.start[j]) return sl::set_error(SL_EINVAL, "a scale without planes");
-  CK(sl::cnn_bwd(coeffs_dev, dcoeffs_dev, pl, H, W, pk.w2, pk.w2t, params_dev, s->num_cu,
-                 (float *)workspace_dev, grads_dev, st));
+  CK(sl::cnn_bwd(coeffs_dev, dcoeffs_dev, pl, H, W, pk.w1k, pk.w2, pk.w2t, pk.w3, params_dev,
+                 s->num_cu, (float *)workspace_dev, grads_dev, st));
   return SL_OK;
 }
 

@@ -82,9 +82,10 @@ __device__ __forceinline__ uint32_t keep_nonzero(uint32_t v, uint32_t h) {
 
 __global__ void __launch_bounds__(kBwdThreads)
 k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPlanes pl,
-          CnnBwdBlocks bk, int H, int W, const uint16_t *__restrict__ W2p,
-          const uint16_t *__restrict__ W2tp,
-          const float *__restrict__ params, float *__restrict__ partial) {
+          CnnBwdBlocks bk, int H, int W, const uint16_t *__restrict__ W1k,
+          const uint16_t *__restrict__ W2p, const uint16_t *__restrict__ W2tp,
+          const uint16_t *__restrict__ W3p, const float *__restrict__ params,
+          float *__restrict__ partial) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsBwd];
   const int lane = threadIdx.x & 63, n0 = lane & 15, g0 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -114,7 +115,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const bool used = g < 3 && e < 6;
-      const uint16_t h = used ? f2bf(P[kOffW1 + ((16 * b + n) * 2 + (e & 1)) * 9 + (used ? 3 * g + (e >> 1) : 0)]) : (uint16_t)0;
+      const uint16_t h = used ? packed_w1(W1k, j, 16 * b + n, e & 1, 3 * g + (e >> 1)) : (uint16_t)0;
       w1[b][e] = *(const __bf16 *)&h;
     }
 #pragma unroll
@@ -124,7 +125,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const bool used = g < 3 && e < 3;
-      const uint16_t h = used ? f2bf(P[kOffW3 + (16 * b + n) * 9 + (used ? 8 - 3 * g - e : 0)]) : (uint16_t)0;
+      const uint16_t h = used ? *packed_w3(W3p, j, 16 * b + n, 8 - 3 * g - e) : (uint16_t)0;
       w3t[b][e] = *(const __bf16 *)&h;
     }
   }
@@ -138,7 +139,7 @@ k_cnn_bwd(const float *__restrict__ coef, const float *__restrict__ dcoef, CnnPl
   // layer 3 with the taps on M: row n = tap, k = channel
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const uint16_t h = n < 9 ? f2bf(P[kOffW3 + (8 * g + e) * 9 + (n < 9 ? n : 0)]) : (uint16_t)0;
+    const uint16_t h = n < 9 ? *packed_w3(W3p, j, 8 * g + e, n) : (uint16_t)0;
     w3f[e] = *(const __bf16 *)&h;
   }
   const float b3 = P[kOffB3];
@@ -630,12 +631,13 @@ int cnn_bwd_blocks(const CnnPlanes &pl, int H, int W, int num_cu, CnnBwdBlocks &
 }
 
 hipError_t cnn_bwd(const float *coef, const float *dcoef, const CnnPlanes &pl, int H, int W,
-                   const uint16_t *W2p, const uint16_t *W2tp, const float *params, int num_cu,
-                   float *partial, float *grads, hipStream_t st) {
+                   const uint16_t *W1k, const uint16_t *W2p, const uint16_t *W2tp,
+                   const uint16_t *W3p, const float *params, int num_cu, float *partial,
+                   float *grads, hipStream_t st) {
   CnnBwdBlocks bk{};
   const int nblk = cnn_bwd_blocks(pl, H, W, num_cu, bk);
   hipLaunchKernelGGL(k_cnn_bwd, dim3(nblk), dim3(kBwdThreads), 0, st, coef, dcoef, pl, bk, H, W,
-                     W2p, W2tp, params, partial);
+                     W1k, W2p, W2tp, W3p, params, partial);
   hipLaunchKernelGGL(k_cnn_bwd_sum, dim3((kCnnParams + 255) / 256, pl.J), dim3(256), 0, st,
                      partial, bk, grads);
   return hipGetLastError();

@@ -352,3 +352,28 @@ def test_sq_error_grad_matches_float64(n):
     loss = float(scratch[0].item())
     ref_loss = float(np.sum(d * d))
     assert abs(loss - ref_loss) < 1e-5 * ref_loss, (loss, ref_loss)
+
+
+def test_weights_come_from_the_pack():
+    # the kernels read every layer's weights from the operand pack and the biases
+    # from the parameters: master weights that change without a new pack change
+    # no output, bit for bit, and a new pack takes them all
+    print("case: parameters changed without a pack, 48x64 J=2 B=2", flush=True)
+    sysg, sig, c, params, pg = _setup((48, 64), 2, (1, 1), 2, seed=5)
+    net = B.Shrinkage(sysg, pg)
+    sg, dc = _gpu(sig), torch.randn(c.shape, generator=torch.Generator().manual_seed(7)).to(DEV)
+
+    def outputs():
+        out, grads = net.apply(c, sg), net.backward(c, sg, dc)
+        torch.cuda.synchronize()
+        return out.cpu(), grads.cpu()
+
+    before = outputs()
+    old = net.params.clone()
+    for a, b in ((0, 576), (608, 9824), (9856, 10144)):       # W1, W2, W3
+        net.params.copy_(old)
+        net.params[:, a:b] *= -0.5
+        for was, now in zip(before, outputs()):
+            assert torch.equal(was, now), (a, b)
+    net.pack()
+    assert not torch.equal(before[0], outputs()[0])
