@@ -350,6 +350,28 @@ bool whole_planes(const sl_system *s) {
   return s->cfg.ndim == 2 && sl::plane2_supported((int)s->cfg.dims[0], (int)s->cfg.dims[1]);
 }
 
+// Whole-plane kernels write results while other blocks still read inputs; the
+// line passes read every input before the launch that writes a result.  Calls
+// whose results share memory with their inputs therefore take the line passes.
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return a && b && p < q + nb && q < p + na;
+}
+size_t image_bytes(const sl_system *s, int B) { return 4 * (size_t)s->cfg.npix() * B; }
+bool whole_coef(const sl_system *s, int B, const float *x, const void *coef, const float *scales) {
+  const size_t n = image_bytes(s, B) * s->R / (s->cfg.dtype == SL_F32 ? 1 : 2);
+  return whole_planes(s) && !overlap(x, image_bytes(s, B), coef, n) &&
+         !overlap(x, image_bytes(s, B), scales, 4 * (size_t)B * s->R);
+}
+// (in place is safe: a block reads the images that it writes, all of them first)
+bool whole_denoise(const sl_system *s, int B, const float *x, const float *out,
+                   const sl::MixArgs *mix) {
+  const size_t n = image_bytes(s, B);
+  auto apart = [&](const float *in) { return in == out || !overlap(in, n, out, n); };
+  if (!whole_planes(s)) return false;
+  return mix ? apart(mix->fm) && apart(mix->f) && !overlap(mix->mask, n / 4, out, n) : apart(x);
+}
+
 // Inverse of small images; the groups' shares take the chunk's pair planes.
 int inverse_whole_planes(const sl_system *s, const void *coef, const float *scales,
                          const sl::ThrArgs &thr, int batch, float *x, char *ws, hipStream_t st) {
@@ -406,7 +428,7 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
     return SL_OK;
   }
   const sl::Sys2D v = view2d(s);
-  if (whole_planes(s)) {
+  if (whole_denoise(s, batch, x_dev, out_dev, mix)) {
     const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
     SL_LAUNCH(P_PLANE_THR, st,
               sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, (float *)T, G, batch, st));
@@ -588,11 +610,16 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
   if (!multi2d_supported(cls, n)) return fail(SL_EUNSUPPORTED, "classes not supported by run_multi2d");
   std::vector<std::vector<sl::Chunk>> chunks(n);
   size_t steps = 0;
+  // classes whose planes are taken whole, one pass per direction without chunks
+  auto whole = [&](const MultiClass2D &c) {
+    return (!(what & 1) || whole_coef(c.s, c.B, c.x, c.coef, c.scales)) &&
+           (!(what & 2) || whole_coef(c.s, c.B, c.out, c.coef, c.scales));
+  };
   for (int i = 0; i < n; ++i) {
     const MultiClass2D &c = cls[i];
     int rc = check_call(c.s, c.B, c.x ? (const void *)c.x : c.coef, c.coef, c.ws, c.ws_bytes);
     if (rc) return rc;
-    if (whole_planes(c.s)) continue;   // one pass per direction, no chunks
+    if (whole(c)) continue;
     int nb, np;
     chunk_plan(c.s, c.B, nb, np);
     const int P = (c.s->R + 1) / 2;
@@ -613,7 +640,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
       const sl::Sys2D v = view2d(c.s);
       const bool scaled = dtype != SL_F32;
       if (scaled && !c.scales) return fail(SL_EINVAL, "scales are required for F16/BF16 storage");
-      if (whole_planes(c.s)) {
+      if (whole(c)) {
         SL_LAUNCH(P_PLANE_FWD, st,
                   sl::launch_plane2_fwd(v, c.x, c.coef, c.scales, c.B, false, st));
         continue;
@@ -653,7 +680,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
     for (int i = 0; i < n; ++i) groups[i] = inv_groups(cls[i].s, cls[i].B);
     for (int i = 0; i < n; ++i) {
       const MultiClass2D &c = cls[i];
-      if (!whole_planes(c.s)) continue;
+      if (!whole(c)) continue;
       int rc = inverse_whole_planes(c.s, c.coef, c.scales, multi_thresholds(c, K), c.B, c.out,
                                     (char *)c.ws, st);
       if (rc) return rc;
@@ -689,7 +716,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
     }
     for (int i = 0; i < n; ++i) {
       const MultiClass2D &c = cls[i];
-      if (whole_planes(c.s)) continue;
+      if (whole(c)) continue;
       const Layout L = layout(c.s, c.B);
       char *ws = (char *)c.ws;
       const sl::Sys2D v = view2d(c.s);
@@ -1103,7 +1130,7 @@ static int forward_impl(const sl_system *s, const float *x_dev, int batch, void 
                                  s->xcd_err_dev, batch, s->xcd_spin, st));
     return SL_OK;
   }
-  if (whole_planes(s)) {
+  if (whole_coef(s, batch, x_dev, coeffs_dev, scales_dev)) {
     SL_LAUNCH(P_PLANE_FWD, st,
               sl::launch_plane2_fwd(v, x_dev, coeffs_dev, scales_dev, batch, dual, st));
     return SL_OK;
@@ -1169,7 +1196,7 @@ int sl_inverse(const sl_system *s, const void *coeffs_dev, const float *scales_d
   }
   int nb, np;
   chunk_plan(s, batch, nb, np);
-  if (whole_planes(s))
+  if (whole_coef(s, batch, x_dev, coeffs_dev, scales_dev))
     return inverse_whole_planes(s, coeffs_dev, scales_dev, thr, batch, x_dev, ws, st);
   const int P = (s->R + 1) / 2;
   const int G = inv_groups(s, batch);

@@ -546,3 +546,36 @@ def test_pair_groups_fill_rounds(dims, Bn, resident):
     cost = {g: -(-blocks * g // resident) * (-(-P // g) + 1) for g in range(1, P + 1)}
     print(f"{blocks} blocks, {G} groups of {P} pairs, cost {cost}", flush=True)
     assert 1 <= G <= P and all(cost[g] >= 0.95 * cost[G] for g in range(1, G + 1))
+
+
+@pytest.mark.parametrize("dims,Bn,dtype", [((64, 64), 1, "f32"), ((32, 48), 3, "f16"),
+                                           ((32, 32), 600, "f32")])
+def test_small_images_in_shared_memory(dims, Bn, dtype):
+    """Small images whose results lie in the memory of their inputs (an image in
+    the coefficient tensor it is transformed to or from, a denoised batch one
+    image further on): the same as in memory of their own, up to float32 rounding
+    (such calls take the line passes)."""
+    print(f"case: shared memory {dims} B={Bn} {dtype}", flush=True)
+    n = Bn * dims[0] * dims[1]
+    sysg = B.System(dims, 2, [1, 1], dtype=dtype)
+    x = _gpu(np.random.default_rng(17).random((Bn, *dims)))
+    # (nothing thresholded: the two paths may decide a near tie differently)
+    sg, K = torch.zeros(Bn, device=DEV), [0.0, 0.0]
+    c, sc = sysg.forward(x)
+    xr = sysg.inverse(c, sc)
+    xd = sysg.denoise_fused(x, sg, K)
+    mem = torch.empty_like(c)
+    tail = mem.view(-1).view(torch.float32)[-n:].view(x.shape)
+    tail.copy_(x)
+    c2, sc2 = sysg.forward(tail, coeffs=mem, scales=torch.empty_like(sc))
+    dec = lambda c, s: _decode(c, s if dtype != "f32" else None)
+    # 16-bit storage may round a value the other way: half a unit of 11 bits
+    tol = 1e-6 if dtype == "f32" else 2.0 ** -11
+    assert rel(dec(c2, sc2), dec(c, sc)) < tol
+    head = c.view(-1).view(torch.float32)[:n].view(x.shape)
+    assert rel(sysg.inverse(c, sc, out=head).cpu().numpy(), xr.cpu().numpy()) < 1e-6
+    two = torch.empty((Bn + 1, *dims), device=DEV)
+    two[:Bn] = x
+    assert rel(sysg.denoise_fused(two[:Bn], sg, K, out=two[1:]).cpu().numpy(), xd.cpu().numpy()) < 1e-6
+    two[:Bn] = x
+    assert rel(sysg.denoise_fused(two[:Bn], sg, K, out=two[:Bn]).cpu().numpy(), xd.cpu().numpy()) < 1e-6
