@@ -372,15 +372,19 @@ bool whole_denoise(const sl_system *s, int B, const float *x, const float *out,
   return mix ? apart(mix->fm) && apart(mix->f) && !overlap(mix->mask, n / 4, out, n) : apart(x);
 }
 
-// Inverse of small images; the groups' shares take the chunk's pair planes.
+// Pair groups of a whole-plane call.  Its groups' shares of the images are all
+// that it keeps in the workspace, so they may take the whole of it.
+int whole_groups(const sl_system *s, int B) {
+  const size_t plane = 8ull * (size_t)s->cfg.npix();
+  return sl::plane2_inv_groups(view2d(s), B, layout(s, B).total / plane);
+}
+
+// Inverse of small images.
 int inverse_whole_planes(const sl_system *s, const void *coef, const float *scales,
                          const sl::ThrArgs &thr, int batch, float *x, char *ws, hipStream_t st) {
-  const sl::Sys2D v = view2d(s);
-  int nb, np;
-  chunk_plan(s, batch, nb, np);
-  const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
-  float *part = (float *)(ws + layout(s, batch).off_chunk);
-  SL_LAUNCH(P_PLANE_INV, st, sl::launch_plane2_inv(v, coef, scales, thr, x, part, G, batch, st));
+  SL_LAUNCH(P_PLANE_INV, st,
+            sl::launch_plane2_inv(view2d(s), coef, scales, thr, x, (float *)ws,
+                                  whole_groups(s, batch), batch, st));
   return SL_OK;
 }
 
@@ -429,9 +433,9 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
   }
   const sl::Sys2D v = view2d(s);
   if (whole_denoise(s, batch, x_dev, out_dev, mix)) {
-    const int G = sl::plane2_inv_groups(v, batch, (size_t)nb * np);
     SL_LAUNCH(P_PLANE_THR, st,
-              sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, (float *)T, G, batch, st));
+              sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, (float *)ws,
+                                    whole_groups(s, batch), batch, st));
     return SL_OK;
   }
   const int G = inv_groups(s, batch);

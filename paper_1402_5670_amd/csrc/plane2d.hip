@@ -517,8 +517,11 @@ int plane2_inv_groups(const Sys2D &s, int B, size_t part_planes) {
   if (s.H == h && s.W == w) G = plane2_groups(s, B, sizeof(Plane2Lds<h, w>), Plane2<h, w>::WPE * 256 / Plane2<h, w>::THREADS);
   SL_FOR_EACH_PLANE2(X)
 #undef X
-  if (!s.split_pairs || (size_t)G * B > 2 * part_planes) G = 1;
-  return G;
+  // as many of them as the scratch holds shares for
+  const size_t fit = 2 * part_planes / B;
+  if (!s.split_pairs || fit < 2) return 1;
+  const int P = (s.R + 1) / 2, g = (int)std::min<size_t>(G, fit), per = (P + g - 1) / g;
+  return (P + per - 1) / per;
 }
 
 static Plane2Args plane2_args(const Sys2D &s) {

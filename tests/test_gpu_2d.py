@@ -579,3 +579,20 @@ def test_small_images_in_shared_memory(dims, Bn, dtype):
     assert rel(sysg.denoise_fused(two[:Bn], sg, K, out=two[1:]).cpu().numpy(), xd.cpu().numpy()) < 1e-6
     two[:Bn] = x
     assert rel(sysg.denoise_fused(two[:Bn], sg, K, out=two[:Bn]).cpu().numpy(), xd.cpu().numpy()) < 1e-6
+
+
+@pytest.mark.parametrize("Bn", [3, 4, 8])
+def test_whole_planes_keep_their_groups(monkeypatch, Bn):
+    """The chunk of the line passes does not bound the pair groups of whole
+    planes: with a chunk of 1 MiB (32 planes) the same groups, so the same bits,
+    as with the default one, of which the workspace holds every share."""
+    print(f"case: whole planes 64x64 B={Bn}, chunk 1 MiB", flush=True)
+    a = B.System((64, 64), 3, [1, 1, 2])
+    monkeypatch.setenv("SL_CHUNK_MB", "1")
+    b = B.System((64, 64), 3, [1, 1, 2])
+    assert b.workspace_bytes(Bn) >= (b.R + 1) // 2 * Bn * 4 * 64 * 64   # a share per pair
+    x = _gpu(np.random.default_rng(18).random((Bn, 64, 64)))
+    sg, K = torch.full((Bn,), 0.1, device=DEV), [2.0, 2.0, 2.0]
+    c, _ = a.forward(x)
+    assert torch.equal(a.inverse(c), b.inverse(c))
+    assert torch.equal(a.denoise_fused(x, sg, K), b.denoise_fused(x, sg, K))
