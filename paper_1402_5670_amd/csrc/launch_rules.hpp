@@ -52,7 +52,11 @@ long resident_blocks(int threads, int num_cu) {
   int per = slot.load(std::memory_order_relaxed);
   if (per < 0) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, threads, 0) != hipSuccess || n < 1) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, threads, 0) != hipSuccess) {
+      (void)hipGetLastError();   // or the next launch's check would report it
+      n = 0;
+    }
+    n = n < 1 ? 1 : n;
     per = n;
     slot.store(per, std::memory_order_relaxed);
   }

@@ -29,3 +29,9 @@ def test_few_rows_are_fewer_rows(rules):
     for n, tile, few in rules["rows"]:
         assert 1 <= few <= tile, n
         assert n < 256 or few <= tile // 4, n
+
+
+def test_failed_occupancy_query_leaves_no_error(rules):
+    # one block per compute unit, and no error left for the check after the next
+    # launch
+    assert rules["resident"] == [[256, 0]]
