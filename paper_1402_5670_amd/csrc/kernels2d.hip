@@ -1701,9 +1701,13 @@ static void cols_fft(const Sys2D &s, const float2 *A, float2 *F, int B, const Sc
                      hipStream_t st) {
   const dim3 g = col_grid<N>(s.W, B);
   if constexpr (!NT_) {
-    // few tiles: tiles of half the columns (rule and figures at few_rows)
+    // few tiles: tiles of half the columns (rule and figures at few_rows).  The
+    // four columns that 1024 points leave are 32 bytes of a row, and narrow
+    // planes' tiles share their lines across XCDs: those take them below an
+    // eighth only (forward of 24 x 1024 x 16, 48 tiles, 46.4 us with half tiles,
+    // 44.1 without; 6 x 1024 x 16 28.1 and 29.3; 6 x 1024 x 64 40.7 and 42.2)
     constexpr int M = CTile<N>::M / 2;
-    if ((long)g.x * g.y < s.num_cu / 4) {
+    if ((long)g.x * g.y < s.num_cu / (M < 8 && s.W < 64 ? 8 : 4)) {
       hipLaunchKernelGGL((k_cols_fft<N, INV, NT_, M>), dim3((s.W + M - 1) / M, B),
                          dim3(M * CTile<N>::NT), 0, st, A, F, s.W, s.twH, sc);
       return;
