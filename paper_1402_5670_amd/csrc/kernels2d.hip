@@ -1844,7 +1844,7 @@ static void launch_fwd3(const Sys2D &s, const float2 *F, float2 *T, Chunk c, hip
   int groups = pair_groups(s, tiles * ny, c.np, 4, 32);
   if (s.split_pairs && tiles * ny >= s.num_cu) {
     const long resident = resident_blocks<k_cols_filter_ifft3<N, BT, MW, EM>>(FT::THREADS, s.num_cu);
-    groups = round_split((long)tiles * ny, resident, c.np, 0, 8);
+    groups = forward_split((long)tiles * ny, resident, s.num_cu, c.np);
   }
   hipLaunchKernelGGL((k_cols_filter_ifft3<N, BT, MW, EM>), dim3(tiles, ny, groups),
                      dim3(FT::THREADS), 0, st, F, s.filt, T, s.W, s.R, c.b0, c.nb, c.p0, c.np, s.twH);

@@ -84,4 +84,16 @@ inline int round_split(long blocks, long resident, int np, int extra, int cap) {
   return best;
 }
 
+// Parts of the forward column pass's pair loop for a grid of at least a block per
+// compute unit.  One that is resident at once with two blocks or more per
+// compute unit keeps its memory busy, and a split only has its tiles of the
+// spectrum read again and its planes written further apart: 16 x 96 x 1024
+// denoised (R = 17) 173.6 us in two parts, 167.5 whole, 64 x 128^2 95.9 and 93.0,
+// 32 x 128 x 256 100.5 and 97.2 (the forward alone 104.1 and 101.9, 57.0 and
+// 57.5, 58.6 and 58.4; 24 x 192 x 384 loses, 100.7 and 103.4).
+inline int forward_split(long blocks, long resident, int num_cu, int np) {
+  if (blocks >= 2L * num_cu && blocks <= resident) return 1;
+  return round_split(blocks, resident, np, 0, 8);
+}
+
 }  // namespace sl

@@ -32,5 +32,7 @@ int main() {
   rows<128>(), rows<192>(), rows<256>(), rows<384>(), rows<512>(), rows<768>(), rows<1024>();
   const long blocks = sl::resident_blocks<k_nothing>(64, 256);
   std::printf("resident %ld %d\n", blocks, (int)hipGetLastError());
+  for (long blocks : {256, 384, 512, 1024, 1030})
+    std::printf("forward %ld %d\n", blocks, sl::forward_split(blocks, 1024, 256, 9));
   return 0;
 }

@@ -35,3 +35,12 @@ def test_failed_occupancy_query_leaves_no_error(rules):
     # one block per compute unit, and no error left for the check after the next
     # launch
     assert rules["resident"] == [[256, 0]]
+
+
+def test_forward_split(rules):
+    # 256 compute units of 4 resident blocks, 9 pairs; the cost of a split is its
+    # rounds times the pairs of a part.  256 blocks: 3 parts (1 round of 3, for 9
+    # whole and 1 x 5 in two); 384: 5 parts (2 x 2, for 1 x 5 in two); 512 and 1024
+    # blocks are resident at once, two or four per unit, and left whole; 1030 take
+    # 3 parts (4 x 3, for 2 x 9 whole)
+    assert dict(rules["forward"]) == {256: 3, 384: 5, 512: 1, 1024: 1, 1030: 3}
