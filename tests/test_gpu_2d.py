@@ -596,3 +596,78 @@ def test_whole_planes_keep_their_groups(monkeypatch, Bn):
     c, _ = a.forward(x)
     assert torch.equal(a.inverse(c), b.inverse(c))
     assert torch.equal(a.denoise_fused(x, sg, K), b.denoise_fused(x, sg, K))
+
+
+@pytest.mark.parametrize("dims,Bn,dtype", [
+    ((32, 48), 2, "f32"), ((48, 32), 3, "f16"), ((48, 48), 2, "bf16"), ((32, 64), 5, "f16"),
+    ((64, 32), 2, "f32"), ((48, 48), 1, "f32"), ((32, 48), 700, "bf16")])
+def test_whole_plane_shapes(dims, Bn, dtype):
+    """The whole-plane kernels at the other shapes, each with threads and column
+    and row iterations of its own, with pair groups and with all pairs of an image
+    in one block: against the oracle, tolerances as in test_whole_plane_passes."""
+    print(f"case: whole-plane shapes {dims} B={Bn} {dtype}", flush=True)
+    J = 2
+    o = S.build_2d(dims, J, [1, 1])
+    sysg = B.System(dims, J, [1, 1], dtype=dtype)
+    x = np.random.default_rng(19).random((Bn, *dims)).astype(np.float32)
+    xg, sg, K = _gpu(x), torch.full((Bn,), 0.1, device=DEV), [2.0] * J
+    l2 = np.array([s[4] for s in sysg.subbands], dtype=np.float32)
+    for split in (1, 0):
+        sysg.set_block_shape(0, split)
+        c, sc = sysg.forward(xg)
+        xr, xt = sysg.inverse(c, sc), sysg.inverse(c, sc, sigma=sg, K=K)
+        xd = sysg.denoise_fused(xg, sg, K)
+        torch.cuda.synchronize()
+        for b in sorted({0, Bn - 1}):
+            cg = _decode(c[b:b + 1], sc[b:b + 1] if dtype != "f32" else None)[0]
+            ref = T.forward(x[b].astype(np.float64), o.filters)
+            assert rel(cg, ref) < (1e-5 if dtype == "f32" else 2e-3), (split, b)
+            assert rel(xr[b].cpu().numpy(), T.inverse(cg, o.filters, o.dual_weight)) < 1e-5
+            ct = cg.copy()
+            for i in range(1, sysg.R):
+                d = np.float32(np.float32(K[sysg.subbands[i][1]]) * np.float32(0.1)) * l2[i]
+                ct[i] *= np.abs(cg[i].astype(np.float32)) >= d
+            want = T.inverse(ct, o.filters, o.dual_weight)
+            assert rel(xt[b].cpu().numpy(), want) < 1e-5, (split, b)
+            if dtype == "f32":
+                assert rel(xd[b].cpu().numpy(), want) < 1e-5, (split, b)
+
+
+def _launches(name, call):
+    """Launches of a pass during call()."""
+    B.timing_enable(True)
+    B.timing_reset()
+    try:
+        call()
+        torch.cuda.synchronize()
+        return B.timing_report().get(name, (0.0, 0))[1]
+    finally:
+        B.timing_enable(False)
+        B.timing_reset()
+
+
+@pytest.mark.parametrize("Bn,chunks", [(3, 6), (12, 34)])
+def test_chunked_line_passes_match(monkeypatch, Bn, chunks):
+    """The chunked schedule of the line passes: 17 pairs of 96 x 128 planes, of
+    which a chunk of 1 MiB holds ten.  3 images take chunks of three pairs, 12
+    images chunks of ten and two images and one pair each; the launches of the
+    column passes are counted.  The coefficients are the same bits, the sums the
+    same up to float32 rounding."""
+    print(f"case: chunked line passes 96x128 B={Bn}", flush=True)
+    dims, J, levels = (96, 128), 3, [1, 1, 2]
+    a = B.System(dims, J, levels)
+    monkeypatch.setenv("SL_CHUNK_MB", "1")
+    b = B.System(dims, J, levels)
+    x = _gpu(np.random.default_rng(9).standard_normal((Bn, *dims)))
+    sg, K = torch.full((Bn,), 0.2, device=DEV), [3.0] * J
+    out = {}
+    for name, s, n in (("whole", a, 1), ("chunked", b, chunks)):
+        c, _ = s.forward(x)
+        assert _launches("cols_filter_ifft", lambda: s.forward(x)) == n
+        assert _launches("cols_fft_acc", lambda: s.inverse(c)) == n
+        assert _launches("rows_thr", lambda: s.denoise_fused(x, sg, K)) == n
+        out[name] = (c, s.inverse(c), s.denoise_fused(x, sg, K))
+    torch.cuda.synchronize()
+    assert torch.equal(out["whole"][0], out["chunked"][0])
+    for u, v in zip(out["whole"][1:], out["chunked"][1:]):
+        assert rel(v.cpu().numpy(), u.cpu().numpy()) < 1e-6

@@ -227,3 +227,15 @@ def test_inpaint_error_paths():
     sysg.inpaint(fm, m, d, 0.1, 5, t_begin=3, t_end=3, f=f)
     torch.cuda.synchronize()
     assert bool((f == 7.0).all())
+
+
+@pytest.mark.parametrize("dims,J,levels,chunk_mb", [
+    ((96, 128), 3, [1, 1, 2], 1),           # line passes, pair planes split over chunks
+    ((48, 32), 2, [1, 1], None), ((32, 64), 2, [1, 1], None),   # whole planes, oblong
+])
+def test_inpaint_iterations_line_and_oblong_planes(monkeypatch, dims, J, levels, chunk_mb):
+    # as test_inpaint_iterations_exact_decisions, whose 64 x 64 planes are whole
+    # ones at any chunk size; 17 pairs of three 96 x 128 planes are 4.8 MiB
+    if chunk_mb:
+        assert 3 * 17 * 8 * dims[0] * dims[1] > chunk_mb << 20
+    test_inpaint_iterations_exact_decisions(monkeypatch, dims, J, levels, 3, chunk_mb)
