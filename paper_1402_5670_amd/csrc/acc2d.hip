@@ -17,9 +17,9 @@
 // Row n of a tile keeps its 16-byte chunk k (two columns) at k ^ h(n), h(n) =
 // n ^ n/8 ^ n/64, which spreads the rows that one instruction touches
 // (consecutive ones, or every 8th) over the banks; h is linear over disjoint
-// bits, so the rows of one thread differ by constants.  The arithmetic is that
-// of k_cols_fft_acc, bit for bit in the tests.  Measured sides of the choice:
-// acc_stream (kernels2d.hip).
+// bits, so the rows of one thread differ by constants.  The plans, products and
+// sums are those of k_cols_fft_acc, with which it agrees to float32 rounding.
+// Measured sides of the choice: acc_stream (kernels2d.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -302,12 +302,12 @@ k_cols_acc_stream(const float2 *__restrict__ U, const float *__restrict__ filt,
 
 #define SL_FOR_EACH_STREAM(X) X(256) X(512) X(1024)
 
-bool cols_acc_stream_supported(int H, int W) {
+int cols_acc_stream_cols(int H) {
 #define X(N) \
-  if (H == N) return W % DTile<N>::COLS == 0;
+  if (H == N) return DTile<N>::COLS;
   SL_FOR_EACH_STREAM(X)
 #undef X
-  return false;
+  return 0;
 }
 
 hipError_t launch_cols_acc_stream(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,

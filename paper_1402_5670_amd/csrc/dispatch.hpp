@@ -103,7 +103,7 @@ hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, flo
                                int Btot, Chunk c, bool first, bool last, hipStream_t st);
 // The same with tiles streamed to LDS, columns of 256, 512 or 1024 points
 // (acc2d.hip); launch_cols_fft_acc chooses.
-bool cols_acc_stream_supported(int H, int W);
+int cols_acc_stream_cols(int H);   // columns per tile; 0: not this length
 hipError_t launch_cols_acc_stream(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
                                int Btot, Chunk c, int bt, bool first, bool last, hipStream_t st);
 // x = Re row IDFT of V + part[0] + ... + part[G - 2] ([B] planes each)

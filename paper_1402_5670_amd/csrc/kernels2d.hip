@@ -1781,26 +1781,35 @@ static InvTile inv_tile(const Sys2D &s, int nb, int bt) {
   return nb == 1 ? inv_tile<N, kInvNarrow>(s, 1) : inv_tile<N, kInvWide>(s, bt);
 }
 
-// Whether the inverse accumulation takes the tile-streaming kernel (acc2d.hip),
-// and its blocks before the pair loop is split.  It wins where few blocks
-// leave the pass waiting for its loads (512 points: 1, 2, 4, 8 images 78.6 ->
-// 69.3, 127 -> 110, 201 -> 184, 326 -> 315 us per thresholded inverse; one
-// 1024^2 image denoised 356 -> 305 us; 4 and 16 images of 256^2 5% and 7%),
-// and not where the device is full (32 x 512^2 470 -> 490 us for the pass, its
-// row segments come at 4.3 TB/s even without the transforms; 6 x 1024^2 537 ->
-// 620 us; 16 of 256 x 512 2% slower) or a 256-point image is alone (one image of
-// 256 x 512, 768, 1024, R = 17, thresholded inverse: line pass 23.9, 28.2, 35.7
-// us, streamed with as many groups 25.7, 28.2, 36.9, with twice 27.7, 31.0,
-// 37.6).
-static int acc_stream_blocks(const Sys2D &s, int nb) {
-  const int bt = inv_bt(s, nb);
-  return s.W / (s.H == 1024 ? 8 : 16) * ((nb + bt - 1) / bt);
+// Blocks of the tile-streaming inverse accumulation (acc2d.hip) before the pair
+// loop is split; 0 where it does not take the planes.
+static long acc_stream_blocks(const Sys2D &s, int nb) {
+  const int cols = cols_acc_stream_cols(s.H), bt = inv_bt(s, nb);
+  return cols && s.W % cols == 0 ? (long)s.W / cols * ((nb + bt - 1) / bt) : 0;
 }
-static bool acc_stream(const Sys2D &s, int nb) {
-  if (!cols_acc_stream_supported(s.H, s.W)) return false;
-  const int blocks = acc_stream_blocks(s, nb);
-  if (s.H == 256) return nb > 1 && blocks >= 32 && blocks < s.num_cu;
-  return blocks < (s.H == 1024 ? s.num_cu / 2 + 1 : s.num_cu);
+
+// Whether the inverse accumulation takes it.  Its loads run ahead of the
+// transforms, which pays where a block has several tiles to stream but the grid
+// leaves the device waiting: not where the grid fills it (32 x 512^2 470 -> 490 us
+// for the pass, its row segments come at 4.3 TB/s even without the transforms; 6
+// x 1024^2 537 -> 620), and not below so many tiles per compute unit (pairs times
+// blocks): nine at 256 lines, one and a half at 512, a half at 1024.  Inverse, line
+// pass and streamed, us, at 16 to 1024 columns and 1 to 32 images:
+//   256   12 x 256^2, R = 49, 9.4 tiles: 131.7, 118.4;  24 x 256^2, R = 33, 12.8:
+//         175.0, 159.8;  16 x 256^2, R = 33, 8.5: 113.1, 115.4;  8 x 256^2, R = 49,
+//         6.3: 77.0, 86.5;  16 x 256^2, R = 17, 4.5: 62.4, 67.8
+//   512   6 x 512^2, R = 17, 3.4: 110.1, 106.3;  512 x 256, R = 49, 1.6: 37.9, 36.9;
+//         512^2, R = 17, 1.1: 35.1, 36.5;  512 x 128, R = 49, 0.8: 26.7, 29.5
+//   1024  4 x 1024 x 128, R = 49, 3.1: 136.2, 124.1;  4 x 1024 x 64, R = 33, 1.1:
+//         76.2, 72.4;  12 x 1024 x 16, R = 17, 0.4: 48.8, 51.0
+// A single image of 256 lines is the line pass's at any size: its 8-column tiles
+// make twice the blocks (256 x 512, R = 17, 23.9 and 25.7).
+static bool acc_stream(const Sys2D &s, int nb, int np) {
+  const long blocks = acc_stream_blocks(s, nb), tiles = 2 * blocks * np;   // in halves
+  if (!blocks) return false;
+  if (s.H == 256) return nb > 1 && blocks < s.num_cu && tiles >= 18L * s.num_cu;
+  if (s.H == 512) return blocks < s.num_cu && tiles >= 3L * s.num_cu;
+  return blocks <= s.num_cu / 2 && tiles >= s.num_cu;
 }
 
 // Every group divides and inverse transforms its own sum, about one more pair:
@@ -1826,7 +1835,7 @@ int inv_pair_groups(const Sys2D &s, int nb, int np) {
   }
   long blocks = (long)((s.W + tile.m - 1) / tile.m) * ((nb + bt - 1) / bt);
   const int cap = pair_groups(s, (int)blocks, np, 2, 16);
-  if (acc_stream(s, nb)) {
+  if (acc_stream(s, nb, np)) {
     blocks = acc_stream_blocks(s, nb);
     tile.resident = (s.H > 256 ? 1L : 2L) * s.num_cu;
   }
@@ -2050,7 +2059,7 @@ static dim3 acc_grid(int W, int M, int groups, int G) {
 hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part,
                                int G, int Btot, Chunk c, bool first, bool last, hipStream_t st) {
   if (G < 1 || (G > 1 && (!part || SL_COL_V3_INV))) return hipErrorInvalidValue;
-  if (acc_stream(s, c.nb))
+  if (acc_stream(s, c.nb, c.np))
     return launch_cols_acc_stream(s, U, ACC, part, G, Btot, c, inv_bt(s, c.nb), first, last, st);
   switch (s.H) {
 #define X(N)                                                                                    \

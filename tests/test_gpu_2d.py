@@ -671,3 +671,34 @@ def test_chunked_line_passes_match(monkeypatch, Bn, chunks):
     assert torch.equal(out["whole"][0], out["chunked"][0])
     for u, v in zip(out["whole"][1:], out["chunked"][1:]):
         assert rel(v.cpu().numpy(), u.cpu().numpy()) < 1e-6
+
+
+@pytest.mark.parametrize("dims,J,levels,Bn,chunk_mb,tiles", [
+    ((256, 256), 3, [1, 1, 2], 24, None, 9.0), ((256, 64), 4, [1, 1, 2, 2], 47, None, 9.0),
+    ((512, 48), 2, [1, 1], 29, None, 1.5), ((512, 64), 2, [1, 1], 23, None, 1.5),
+    ((512, 256), 2, [1, 1], 8, None, 1.5), ((512, 256), 2, [1, 1], 16, 50, 1.5),
+    ((512, 256), 2, [1, 1], 8, 50, 1.5), ((512, 512), 4, [1, 1, 2, 2], 1, None, 1.5),
+    ((1024, 8), 2, [1, 1], 29, None, 0.5), ((1024, 24), 2, [1, 1], 9, None, 0.5),
+    ((1024, 256), 2, [1, 1], 3, None, 0.5)])
+def test_streamed_accumulation_range(monkeypatch, dims, J, levels, Bn, chunk_mb, tiles):
+    """The accumulation with streamed tiles where it is chosen, from `tiles`
+    pairs times blocks per compute unit on: one tile per row of the image, tile
+    counts off the multiple of 8 that groups them, an odd last image, several
+    chunks, and chunks of which only the first has enough pairs (its sums are then
+    taken up by the line pass).  Random coefficients against the oracle, float32
+    tolerance of the precision policy; every run the same bits."""
+    print(f"case: streamed accumulation {dims} B={Bn} chunk {chunk_mb}", flush=True)
+    if chunk_mb:
+        monkeypatch.setenv("SL_CHUNK_MB", str(chunk_mb))
+    o = S.build_2d(dims, J, levels)
+    sysg = B.System(dims, J, levels)
+    P, plane = (sysg.R + 1) // 2, 8 * dims[0] * dims[1]
+    np_ = min(P, (chunk_mb << 20) // (Bn * plane)) if chunk_mb else P
+    blocks = dims[1] // (8 if dims[0] == 1024 else 16) * ((Bn + 1) // 2)
+    assert blocks * np_ >= tiles * 256 and blocks < 256
+    c = np.random.default_rng(12).standard_normal((Bn, sysg.R, *dims)).astype(np.float32)
+    cg = _gpu(c)
+    x = sysg.inverse(cg).cpu().numpy()
+    assert np.array_equal(x, sysg.inverse(cg).cpu().numpy())
+    for b in sorted({0, Bn // 2, Bn - 1}):
+        assert rel(x[b], T.inverse(c[b].astype(np.float64), o.filters, o.dual_weight)) < 1e-5
