@@ -27,17 +27,11 @@
 
 #include "dispatch.hpp"
 #include "fft_core.hpp"
+#include "fresh.hpp"
 
 namespace sl {
 
 namespace {
-
-// The value of x, computed anew (the LDS addresses derived from it are not kept
-// in registers across the loop over tiles).
-__device__ __forceinline__ int anew(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
 
 template <int N>
 struct DTile {
@@ -140,7 +134,7 @@ __device__ __forceinline__ void col_stages(float2 (&v)[DTile<N>::E], int t, unsi
 template <int N, bool INV>
 __device__ __forceinline__ void tile_dft(unsigned char *buf, const float2 *tw) {
   constexpr int E = DTile<N>::E, NT = DTile<N>::NT;
-  const int tid = anew(threadIdx.x), t = tid % NT, col = tid / NT, k = col >> 1;
+  const int tid = fresh(threadIdx.x), t = tid % NT, col = tid / NT, k = col >> 1;
   unsigned char *bc = buf + (col & 1) * 8;
   const int a0 = dt_addr<N>(t, k);
   float2 v[E];
@@ -165,7 +159,7 @@ __device__ __forceinline__ void tile_fetch(unsigned lds, const float2 *src, int 
 #pragma unroll
   for (int u = 0; u < DT::UPT; ++u) {
     const char *base = (const char *)src + (size_t)u * DT::RPU * W * 8;
-    const unsigned v = (unsigned)anew((int)v0) ^ (unsigned)hx<N>(u * DT::RPU);
+    const unsigned v = (unsigned)fresh((int)v0) ^ (unsigned)hx<N>(u * DT::RPU);
     const unsigned m = lds + (unsigned)(u * DT::THREADS * 16) + wave * 1024u;
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
@@ -261,7 +255,7 @@ k_cols_acc_stream(const float2 *__restrict__ U, const float *__restrict__ filt,
       unsigned char *b = buf + cur * DT::TILE;
       tile_dft<N, false>(b, twl);
       __syncthreads();
-      const int ar = anew(a0);
+      const int ar = fresh(a0);
 #pragma unroll
       for (int u = 0; u < UPT; ++u) {
         const float4 v = *(const float4 *)(b + dt_step<N>(ar, u * DT::RPU));

@@ -99,6 +99,8 @@ void chunk_plan(const sl_system *s, int B, int &nb, int &np) {
 // chunk of pair planes.
 // Partial sums of the 2D inverse accumulation when its pair loop is split
 // into groups (small batches): [groups - 1][B] complex planes.
+// Whole-plane calls of small images keep nothing but their groups' shares of the
+// images, from its beginning.
 struct Layout {
   size_t off_F, off_acc, off_chunk, off_part, total;
 };
@@ -374,17 +376,17 @@ bool whole_denoise(const sl_system *s, int B, const float *x, const float *out,
 
 // Pair groups of a whole-plane call.  Its groups' shares of the images are all
 // that it keeps in the workspace, so they may take the whole of it.
-int whole_groups(const sl_system *s, int B) {
-  const size_t plane = 8ull * (size_t)s->cfg.npix();
-  return sl::plane2_inv_groups(view2d(s), B, layout(s, B).total / plane);
+int whole_groups(const sl_system *s, int B, const Layout &L) {
+  return sl::plane2_inv_groups(view2d(s), B, L.total / (8ull * (size_t)s->cfg.npix()));
 }
 
 // Inverse of small images.
 int inverse_whole_planes(const sl_system *s, const void *coef, const float *scales,
-                         const sl::ThrArgs &thr, int batch, float *x, char *ws, hipStream_t st) {
+                         const sl::ThrArgs &thr, int batch, float *x, char *ws, const Layout &L,
+                         hipStream_t st) {
   SL_LAUNCH(P_PLANE_INV, st,
             sl::launch_plane2_inv(view2d(s), coef, scales, thr, x, (float *)ws,
-                                  whole_groups(s, batch), batch, st));
+                                  whole_groups(s, batch, L), batch, st));
   return SL_OK;
 }
 
@@ -435,7 +437,7 @@ int denoise_fused_run(const sl_system *s, const float *x_dev, int batch, const s
   if (whole_denoise(s, batch, x_dev, out_dev, mix)) {
     SL_LAUNCH(P_PLANE_THR, st,
               sl::launch_plane2_thr(v, x_dev, mix, thr, out_dev, (float *)ws,
-                                    whole_groups(s, batch), batch, st));
+                                    whole_groups(s, batch, L), batch, st));
     return SL_OK;
   }
   const int G = inv_groups(s, batch);
@@ -686,7 +688,7 @@ int sl::run_multi2d(const MultiClass2D *cls, int n, int what, const float *K, hi
       const MultiClass2D &c = cls[i];
       if (!whole(c)) continue;
       int rc = inverse_whole_planes(c.s, c.coef, c.scales, multi_thresholds(c, K), c.B, c.out,
-                                    (char *)c.ws, st);
+                                    (char *)c.ws, layout(c.s, c.B), st);
       if (rc) return rc;
     }
     for (size_t k = 0; k < steps; ++k) {
@@ -1201,7 +1203,7 @@ int sl_inverse(const sl_system *s, const void *coeffs_dev, const float *scales_d
   int nb, np;
   chunk_plan(s, batch, nb, np);
   if (whole_coef(s, batch, x_dev, coeffs_dev, scales_dev))
-    return inverse_whole_planes(s, coeffs_dev, scales_dev, thr, batch, x_dev, ws, st);
+    return inverse_whole_planes(s, coeffs_dev, scales_dev, thr, batch, x_dev, ws, L, st);
   const int P = (s->R + 1) / 2;
   const int G = inv_groups(s, batch);
   float2 *part = (float2 *)(ws + L.off_part);

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "fresh.hpp"
+
 namespace sl {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -49,16 +51,6 @@ __device__ __forceinline__ uint2 relu_pack(f32x4 d, uint32_t in) {
   const s16x2 a = __builtin_elementwise_max(*(const s16x2 *)&u.x, z);
   const s16x2 b = __builtin_elementwise_max(*(const s16x2 *)&u.y, z);
   return make_uint2(*(const uint32_t *)&a & in, *(const uint32_t *)&b & in);
-}
-
-// The value of x, computed anew: addresses derived from it stay inside their
-// phase of the tile loop instead of being kept in registers across it (the
-// operands and accumulators that live through the loop leave no room: in the
-// backward kernel hoisted addresses spilled 79 registers, 12.0 against 8.1 ms
-// per 4 x 512^2 training step).
-__device__ __forceinline__ int fresh(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 __device__ __forceinline__ bf16x8 frag(uint2 a, uint2 b) {

@@ -102,7 +102,7 @@ int inv_pair_groups(const Sys2D &s, int nb, int np);
 hipError_t launch_cols_fft_acc(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
                                int Btot, Chunk c, bool first, bool last, hipStream_t st);
 // The same with tiles streamed to LDS, columns of 256, 512 or 1024 points
-// (acc2d.hip); launch_cols_fft_acc chooses.
+// (acc2d.hip); launch_cols_fft_acc chooses where the planes allow it.
 int cols_acc_stream_cols(int H);   // columns per tile; 0: not this length
 hipError_t launch_cols_acc_stream(const Sys2D &s, const float2 *U, float2 *ACC, float2 *part, int G,
                                int Btot, Chunk c, int bt, bool first, bool last, hipStream_t st);
@@ -206,7 +206,7 @@ hipError_t launch_z_filter_ifft(const Sys3D &s, const float2 *F, float2 *T, Chun
 // Plane passes: the y and x line FFTs of each z-slice of a chunk's pair
 // volumes in LDS (s: the slice view, H x W with twiddles of both lengths;
 // D slices per volume).  plane_supported(H, W) tells which slice shapes
-// have them.  Results equal the separate line passes bit for bit.
+// have them.  Results agree with the separate line passes to float32 rounding.
 bool plane_supported(int H, int W);
 // T (after the z IDFT) -> y IDFT -> x IDFT -> coefficients (as rows_coef)
 hipError_t launch_plane_coef(const Sys2D &s, int D, const float2 *T, void *coef,
@@ -214,7 +214,6 @@ hipError_t launch_plane_coef(const Sys2D &s, int D, const float2 *T, void *coef,
 // coefficients (decode, threshold) -> x DFT -> y DFT -> U (for z_fft_acc)
 hipError_t launch_plane_coef_fft(const Sys2D &s, int D, const void *coef, const float *scales,
                                  float2 *U, Chunk c, const ThrArgs &thr, hipStream_t st);
-// T -> y IDFT, x IDFT, scale, threshold, x DFT, y DFT -> T (fused denoise)
 // Half-plane passes: slices too large for LDS, split in y into two halves
 // (one decimation-in-frequency step); forward and inverse only.  Results
 // agree with the line passes to float32 rounding.
@@ -223,6 +222,7 @@ hipError_t launch_hplane_coef(const Sys2D &s, int D, const float2 *T, void *coef
                               const float *scales, Chunk c, float inv_n, hipStream_t st);
 hipError_t launch_hplane_coef_fft(const Sys2D &s, int D, const void *coef, const float *scales,
                                   float2 *U, Chunk c, const ThrArgs &thr, hipStream_t st);
+// T -> y IDFT, x IDFT, scale, threshold, x DFT, y DFT -> T (fused denoise)
 hipError_t launch_plane_thr(const Sys2D &s, int D, float2 *T, float inv_n, Chunk c,
                             const ThrArgs &thr, hipStream_t st);
 hipError_t launch_z_fft_acc(const Sys3D &s, const float2 *U, float2 *ACC, Chunk c, bool first,

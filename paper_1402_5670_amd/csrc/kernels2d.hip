@@ -987,11 +987,10 @@ k_cols_fft_acc(const float2 *__restrict__ U, const float *__restrict__ filt,
 // bits of 2 x 192^2 1.28e-7, 3 x 256 x 64 1.22e-7, now 1.12e-7 and 1.06e-7; 1.20e-7 and
 // 1.14e-7 when partial spectra were added before one transform).
 // G > 1 has few images: blocks of two waves spread the rows over the compute
-// units (M = few_rows).  With one launch that
-// adds partial spectra and another that transforms their columns in place of
-// the groups doing so themselves: denoise of one 512^2 image 103.6 us, now
-// 94.6; 16 x 256^2 in bf16, both directions, 281 and 275; 3 x 96 x 384 in fp16
-// 59.2 and 56.1.
+// units (M = few_rows).  With one launch that adds partial spectra and another
+// that transforms their columns in place of the groups doing so themselves:
+// denoise of one 512^2 image 103.6 us, now 94.6; 16 x 256^2 in bf16, both
+// directions, 281 and 275; 3 x 96 x 384 in fp16 59.2 and 56.1.
 template <int N, int M, bool SUM>
 __global__ void __launch_bounds__(M *Tile<N>::NT)
 k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, int G,
@@ -1046,11 +1045,11 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
 // ---------------------------------------------------------------------------
 // Plane passes of a volume: the y and x line FFTs of one z-slice of a pair
 // volume in LDS (the slice, rows padded as the row kernels pad them), so the
-// slice crosses HBM once instead of once per axis.  They run the same plans
-// and line FFTs as the y column pass (k_cols_fft) and the x row passes
-// (k_rows_coef, k_rows_coef_fft, k_rows_thr), on the same values, so results
-// are bitwise those of the separate passes.  Slices of H x W with
-// H * row_lds_len(W) * 8 bytes of LDS (128 x 128: 144 KiB).
+// slice crosses HBM once instead of once per axis.  The line FFTs are those of
+// the y column pass (k_cols_fft) and the x row passes (k_rows_coef,
+// k_rows_coef_fft, k_rows_thr), on the same values (long columns with twice the
+// values per thread), so results agree to float32 rounding.  Slices of H x W
+// with H * row_lds_len(W) * 8 bytes of LDS (128 x 128: 144 KiB).
 // ---------------------------------------------------------------------------
 // Column lines lie inside a wave, so that columns need no block barriers; where
 // the y pass's plan has more than 8 threads per line, the radices are spread

@@ -11,13 +11,17 @@
 //   inverse   block (group, image): per pair coefficient load, threshold, row
 //             and column DFT, filter product, sum in registers, inverse
 //             DFT of the sum: x, or with several groups a share of it that
-//             k_plane2_sum adds in group order.
+//             k_plane2_sum adds, the lowpass's last.
 //   denoise   both around the threshold, without coefficients.
 // Measured on MI355X against the line passes, forward + inverse: one 64 x 64
 // image 38 -> 17 us, 64 of them (R = 33) 76 -> 41 us; denoise of 8 such images
-// 31 -> 14 us.  The line ends at 64 x 64: from 96 x 64
-// on the work of one plane outweighs the launches saved (128 x 128, R = 49:
-// one image 38 us in line passes, 103 us here; 30 images 142 against 195 us).
+// 31 -> 14 us.  The line ends at 64 x 64: a larger plane is a longer chain for its
+// block than the launches saved, and with many images the line passes' exchange
+// costs less than repeating the image's DFT (R = 17, denoised, line passes and
+// whole planes, us: 96 x 64, 1, 32 and 300 images 21.3, 45.0, 147 and 32.2, 43.7,
+// 204; 64 x 96 21.1, 42.2, 139 and 27.7, 39.4, 166; 96 x 96 24.6, 51.7, 217 and
+// 44.1, 68.1, 412; 128 x 128, both directions, R = 49, 1 and 30 images 38, 142 and
+// 103, 195).  Only batches of 16 to 32 of the first two would gain.
 //
 // Plans, line FFTs and products are those of the line passes, applied to the
 // same values, so results agree to float32 rounding.
@@ -26,6 +30,7 @@
 #include <algorithm>
 
 #include "dispatch.hpp"
+#include "fresh.hpp"
 #include "tiles.hpp"
 
 namespace sl {
@@ -88,13 +93,6 @@ template <int H, int W, bool INV>
 __device__ __forceinline__ void row_dft(float2 (&v)[(Plane2<H, W>::ER)], int t, const LdsLine &row,
                                         const Plane2Lds<H, W> &s) {
   fft_line_p<typename Plane2<H, W>::PR, INV, Plane2<H, W>::WAVE>(v, t, row, TwLds{s.tw});
-}
-
-// The value of x, computed anew (addresses derived from it are not kept in
-// registers across the pair loop).
-__device__ __forceinline__ int anew(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 // Spectrum of image b (columns in registers): row DFT of the real rows
@@ -172,7 +170,7 @@ __device__ __forceinline__ void p2_pair_cols(Plane2Lds<H, W> &s, const ColVals<H
                                              float (&fa)[Plane2<H, W>::EC],
                                              float (&fb)[Plane2<H, W>::EC]) {
   using PT = Plane2<H, W>;
-  const int tid = anew(threadIdx.x), mc = tid % PT::MC, tc = tid / PT::MC;
+  const int tid = fresh(threadIdx.x), mc = tid % PT::MC, tc = tid / PT::MC;
 #pragma unroll
   for (int ci = 0; ci < PT::NCI; ++ci) {
     float2 v[PT::EC];
@@ -195,7 +193,7 @@ template <int H, int W>
 __device__ __forceinline__ void p2_acc_cols(Plane2Lds<H, W> &s, ColVals<H, W> &acc,
                                             const Plane2Args &a, int p) {
   using PT = Plane2<H, W>;
-  const int tid = anew(threadIdx.x), mc = tid % PT::MC, tc = tid / PT::MC;
+  const int tid = fresh(threadIdx.x), mc = tid % PT::MC, tc = tid / PT::MC;
 #pragma unroll
   for (int ci = 0; ci < PT::NCI; ++ci) {
     float fa[PT::EC], fb[PT::EC];
@@ -310,7 +308,7 @@ k_plane2_fwd(Plane2Args a, const float *__restrict__ x, typename Store<DT>::T *_
   for (int p = blockIdx.x; p < P; p += gridDim.x) {
     const int ia = 2 * p, ib = ia + 1;
     p2_pair_cols<H, W>(s, f, a, p, fa, fb);
-    const int tid = anew(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
+    const int tid = fresh(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
     // (lands during the rows below)
     if (p + (int)gridDim.x < P)
       p2_filters<H, W>(a.filt, p + gridDim.x, a.R, 0, (tid / PT::MC) * W + tid % PT::MC, fa, fb);
@@ -366,7 +364,7 @@ k_plane2_inv(Plane2Args a, const typename Store<DT>::T *__restrict__ coef,
     for (int e = 0; e < PT::EC; ++e) acc[ci][e] = make_float2(0.f, 0.f);
   Raw ra[PT::NRI][PT::ER], rb[PT::NRI][PT::ER];
   auto fetch = [&](int p) {
-    const int tid = anew(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
+    const int tid = fresh(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
     const int ia = 2 * p, ib = ia + 1;
     const Raw *pa = (const Raw *)(coef + ((size_t)b * a.R + ia) * H * W);
     const Raw *pb = (const Raw *)(coef + ((size_t)b * a.R + (ib < a.R ? ib : ia)) * H * W);
@@ -390,7 +388,7 @@ k_plane2_inv(Plane2Args a, const typename Store<DT>::T *__restrict__ coef,
     }
     if (thr.sigma) p2_thresholds(thr, thr.sigma[b], ia, a.R, da, db);
     __syncthreads();   // the previous pair's column pass has left LDS
-    const int tid = anew(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
+    const int tid = fresh(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
 #pragma unroll
     for (int ri = 0; ri < PT::NRI; ++ri) {
       float2 v[PT::ER];
@@ -434,7 +432,7 @@ k_plane2_thr(Plane2Args a, const float *__restrict__ x, ThrArgs thr, MixArgs mix
     for (int e = 0; e < PT::EC; ++e) acc[ci][e] = make_float2(0.f, 0.f);
   for (int p = blockIdx.x; p < P; p += gridDim.x) {
     const int ia = 2 * p;
-    const int tid = anew(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
+    const int tid = fresh(threadIdx.x), t = tid % PT::NTR, m = tid / PT::NTR;
     float fa[PT::EC], fb[PT::EC], da, db;
     p2_filters<H, W>(a.filt, p, a.R, 0, (tid / PT::MC) * W + tid % PT::MC, fa, fb);
     p2_thresholds(thr, sg, ia, a.R, da, db);

@@ -22,7 +22,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 
 
 TRANSFORM_SOURCES = ("kernels2d.hip", "acc2d.hip", "plane2d.hip", "kernels3d.hip", "fft_core.hpp",
-                     "tiles.hpp", "launch_rules.hpp", "dispatch.hpp")
+                     "tiles.hpp", "fresh.hpp", "launch_rules.hpp", "dispatch.hpp")
 
 
 def source_hash():
