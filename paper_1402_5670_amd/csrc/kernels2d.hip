@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "dispatch.hpp"
 #include "fft_core.hpp"
@@ -1009,17 +1010,17 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
     float2 w[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) w[e] = make_float2(0.f, 0.f);
-    // the loads of Q groups are issued before the first addition waits for one;
-    // past the last group they repeat it.  (Left to itself the compiler gave
-    // rows of 16 to 64 samples a load, a wait and an addition at a time: inverse
-    // of 96 x 64, R = 17, 19.7 us, now 12.1; 3 x 256 x 64 in fp16 27.6, 21.2; Q =
-    // 8 measured 0 to 5% slower.)
-    constexpr int Q = 4;
-    for (int z = 1; z < G; z += Q) {
+    // the loads of four groups (of all that are left at the end) are issued before
+    // the first addition waits for one.  (Left to itself the compiler gave rows of
+    // 16 to 64 samples a load, a wait and an addition at a time: inverse of 96 x 64,
+    // R = 17, 19.7 us, now 12.1; 3 x 256 x 64 in fp16 27.6, 21.2; eight at a time
+    // measured 0 to 5% slower.)
+    auto add = [&](int z, auto count) {
+      constexpr int Q = decltype(count)::value;
       float2 q[Q][E];
 #pragma unroll
       for (int u = 0; u < Q; ++u) {
-        const float2 *p = part + (size_t)(min(z + u, G - 1) - 1) * pstride + off + t;
+        const float2 *p = part + (size_t)(z + u - 1) * pstride + off + t;
 #pragma unroll
         for (int e = 0; e < E; ++e) q[u][e] = p[e * NT];
       }
@@ -1027,11 +1028,13 @@ k_rows_real_ifft(const float2 *__restrict__ V, const float2 *__restrict__ part, 
 #pragma unroll
       for (int u = 0; u < Q; ++u)
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          w[e].x += z + u < G ? q[u][e].x : 0.f;
-          w[e].y += z + u < G ? q[u][e].y : 0.f;
-        }
-    }
+        for (int e = 0; e < E; ++e) w[e] = cadd(w[e], q[u][e]);
+    };
+    int z = 1;
+    for (; z + 4 <= G; z += 4) add(z, std::integral_constant<int, 4>{});
+    if (G - z == 3) add(z, std::integral_constant<int, 3>{});
+    else if (G - z == 2) add(z, std::integral_constant<int, 2>{});
+    else if (G - z == 1) add(z, std::integral_constant<int, 1>{});
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = cadd(w[e], v[e]);
   }
@@ -1761,23 +1764,25 @@ static int inv_bt(const Sys2D &s, int nb) {
 }
 
 // columns per block of the inverse accumulation's line pass, and its blocks
-// resident on the device at once
+// resident on the device at once: of the kernel that launch_cols_fft_acc takes
 struct InvTile {
   int m;
   long resident;
 };
-template <int N, int MW, int EM = 1>
-static InvTile inv_tile(const Sys2D &s, int bt) {
+template <int N, int BT, int MW, int EM = 1>
+static InvTile inv_tile_of(const Sys2D &s) {
   using IT = ITile<N, MW, EM>;
-  return {IT::M, bt == 1 ? resident_blocks<k_cols_fft_acc<N, 1, MW, EM>>(IT::THREADS, s.num_cu)
-                         : resident_blocks<k_cols_fft_acc<N, kInvBT, MW, EM>>(IT::THREADS, s.num_cu)};
+  return {IT::M, resident_blocks<k_cols_fft_acc<N, BT, MW, EM>>(IT::THREADS, s.num_cu)};
 }
 template <int N>
-static InvTile inv_tile(const Sys2D &s, int nb, int bt) {
+static InvTile inv_tile(const Sys2D &s, int nb) {
+  const bool one = nb == 1 || inv_bt(s, nb) == 1;
   if constexpr (em2_length<N>()) {
-    if (s.line_em == 2) return inv_tile<N, kInvNarrow, 2>(s, bt);
+    if (s.line_em == 2)
+      return one ? inv_tile_of<N, 1, kInvNarrow, 2>(s) : inv_tile_of<N, 2, kInvNarrow, 2>(s);
   }
-  return nb == 1 ? inv_tile<N, kInvNarrow>(s, 1) : inv_tile<N, kInvWide>(s, bt);
+  if (nb == 1) return inv_tile_of<N, 1, kInvNarrow>(s);
+  return one ? inv_tile_of<N, 1, kInvWide>(s) : inv_tile_of<N, kInvBT, kInvWide>(s);
 }
 
 // Blocks of the tile-streaming inverse accumulation (acc2d.hip) before the pair
@@ -1827,7 +1832,7 @@ int inv_pair_groups(const Sys2D &s, int nb, int np) {
   switch (s.H) {
 #define X(N) \
   case N:    \
-    tile = inv_tile<N>(s, nb, bt); \
+    tile = inv_tile<N>(s, nb); \
     break;
     SL_FOR_EACH_N(X)
 #undef X
