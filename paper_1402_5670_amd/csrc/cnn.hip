@@ -246,6 +246,12 @@ k_cnn_fused(const float *__restrict__ coef, CnnPlanes pl, int H, int W, int ntil
   float b3 = 0.f;
   auto load_weights = [&](int j) {
     const float *P = params + (size_t)j * kCnnParams;
+    // layer 3, taps on M, this wave's 16 channels on K: row n, k = 4 g + e (four
+    // channels of a tap lie together in the pack)
+    const int tap = fresh(n0);
+    const s16x4 w3p = *(const s16x4 *)packed_w3(W3p, j, 16 * nb + 4 * fresh(g0), min(tap, 8));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w3[e] = tap < 9 ? w3p[e] : (short)0;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       w1[b] = *(const bf16x8 *)(W1k + (((size_t)j * 2 + b) * 64 + lane) * 8);
@@ -257,11 +263,6 @@ k_cnn_fused(const float *__restrict__ coef, CnnPlanes pl, int H, int W, int ntil
       w2[t] = *(const bf16x8 *)(W2p + ((((size_t)j * 9 + t) * 2 + nb) * 64 + lane) * 8);
 #pragma unroll
     for (int e = 0; e < 4; ++e) bias2[e] = P[kOffB2 + 16 * nb + 4 * g0 + e];
-    // layer 3, taps on M, this wave's 16 channels on K: row n, k = 4 g + e (four
-    // channels of a tap lie together in the pack)
-    const int tap = fresh(n0);
-    w3 = s16x4{0, 0, 0, 0};
-    if (tap < 9) w3 = *(const s16x4 *)packed_w3(W3p, j, 16 * nb + 4 * fresh(g0), tap);
     b3 = P[kOffB3];
   };
   // relu and layer 3 of 16 pixels at d3 index q of lane n
