@@ -530,12 +530,10 @@ def test_pair_group_sums_precision(dims, J, levels, Bn):
 
 
 @pytest.mark.parametrize("dims,Bn,resident", [
-    ((512, 512), 6, 256), ((512, 128), 24, 256), ((1024, 384), 3, 256), ((512, 256), 8, 256),
-    ((256, 256), 16, 512)])
+    ((512, 512), 6, 256), ((512, 128), 24, 256), ((1024, 384), 3, 256), ((512, 256), 8, 256)])
 def test_pair_groups_fill_rounds(dims, Bn, resident):
-    """Pair groups of the streamed accumulation: one block per compute unit, two
-    at 256 lines, each group's blocks take its pairs and about one more to finish
-    its sum; no other group count up to the chosen one takes less than 0.95 of
+    """Pair groups of the streamed accumulation: one block per compute unit, each
+    group's blocks take its pairs and about one more to finish its sum; no other group count up to the chosen one takes less than 0.95 of
     its rounds.  Read from the workspace, which holds a plane per image for every
     group after the first."""
     print(f"case: pair groups of {dims} B={Bn}", flush=True)
