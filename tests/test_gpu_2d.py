@@ -533,9 +533,10 @@ def test_pair_group_sums_precision(dims, J, levels, Bn):
     ((512, 512), 6, 256), ((512, 128), 24, 256), ((1024, 384), 3, 256), ((512, 256), 8, 256)])
 def test_pair_groups_fill_rounds(dims, Bn, resident):
     """Pair groups of the streamed accumulation: one block per compute unit, each
-    group's blocks take its pairs and about one more to finish its sum; no other group count up to the chosen one takes less than 0.95 of
-    its rounds.  Read from the workspace, which holds a plane per image for every
-    group after the first."""
+    group's blocks take its pairs and about one more to finish its sum; no other
+    group count up to the chosen one takes less than 0.95 of its rounds.  Read
+    from the workspace, which holds a plane per image for every group after the
+    first."""
     print(f"case: pair groups of {dims} B={Bn}", flush=True)
     sysg = B.System(dims, 2, [1, 1])
     P, plane = (sysg.R + 1) // 2, 8 * dims[0] * dims[1] * Bn
